@@ -19,6 +19,7 @@ RESOURCES = os.path.join(OBJDIR, "kernel_resources.txt")
 UNITS = [
     ("sage_quant.hip", ["-ffp-contract=off"]),
     ("sage_attn.hip", []),
+    ("sage_prefill.hip", []),
     ("sage_decode.hip", []),
     ("sage_api.hip", []),
     ("sage_diag.hip", []),
@@ -93,14 +94,10 @@ def build(verbose: bool = False) -> str:
     bad = {n: u for n, u in usage.items() if u.get("ScratchSize", 0) or u.get("VGPRs Spill", 0)}
     if bad:
         raise RuntimeError("kernels spill registers to scratch memory: " + repr(bad))
-    # (the 4+8 variant at d = 128 is built for fewer wavefronts per SIMD on purpose; in the mangled name its
-    # template arguments <128, ..., Q4 = true, SPLIT = false> read "attn_kernelILi128E ... Lb1ELb0EEEv")
-    def four_bit_d128(name: str) -> bool:
-        return "attn_kernelILi128E" in name and "ELb1ELb0EEEv" in name
     slow = {n: u for n, u in usage.items()
-            if "attn_kernel" in n and u.get("Occupancy", 0) < 4 and not four_bit_d128(n)}
+            if ("attn_kernel" in n and u.get("Occupancy", 0) < 4) or ("prefill_kernel" in n and u.get("Occupancy", 0) < 2)}
     if slow:
-        raise RuntimeError("attention kernels below 4 wavefronts per SIMD: " + repr(slow))
+        raise RuntimeError("attention kernels below the wavefronts per SIMD they are built for: " + repr(slow))
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     subprocess.run(cmd, check=True)
     return LIB

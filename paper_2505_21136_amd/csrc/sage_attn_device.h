@@ -8,6 +8,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace sage {
 namespace {
 
@@ -71,6 +73,17 @@ __device__ __forceinline__ float to_f32(uint32_t u) {
     return (float)__builtin_bit_cast(_Float16, (uint16_t)u);
 }
 
+// eight packed 16-bit values -> binary32
+template <bool BF16>
+__device__ __forceinline__ void unpack8(const uint4 &u, float (&f)[8]) {
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        f[2 * i] = to_f32<BF16>(w[i] & 0xffffu);
+        f[2 * i + 1] = to_f32<BF16>(w[i] >> 16);
+    }
+}
+
 template <bool BF16>
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
     if constexpr (BF16) {
@@ -92,6 +105,61 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 // binary32 numbers kh + kl; then fma(bits, c, kh) = fl(c*S - kl) and adding (kl + offset) restores c*S.
 constexpr int kMagic = 0x4B400000;
 constexpr float kMagicF = 12582912.0f;
+
+// Eight INT8 codes rne(fl(x * rcp)), one per byte: adding 1.5*2^23 to the (separately rounded) product rounds it to the
+// nearest integer, ties to even, and leaves the code's two's-complement byte in the low byte of the sum's bit pattern;
+// three byte permutes pack four codes.
+__device__ __forceinline__ uint2 int8_codes(const float (&x)[8], float rcp) {
+    uint32_t w[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        uint32_t b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float y = x[4 * e + i] * rcp;
+            asm volatile("" : "+v"(y));  // keeps the product a rounded binary32 value (no FMA)
+            b[i] = __builtin_bit_cast(uint32_t, y + kMagicF);
+        }
+        const uint32_t lo2 = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u);
+        const uint32_t hi2 = __builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u);
+        w[e] = __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
+    }
+    return make_uint2(w[0], w[1]);
+}
+
+// Workgroup id -> (batch and query head, query tile) of a one-dimensional grid of n_items = heads * n_qt workgroups.
+// The hardware deals consecutive workgroup ids round-robin to the 8 XCDs, each with an L2 of its own: workgroup id is
+// the `slot`-th of XCD `xcd`.  Co-resident workgroups of an XCD should stream through the same K^/V^ tiles (its L2 then
+// serves every fetch after the first), and a causal launch must also end on its short tiles.
+template <bool CAUSAL>
+__device__ __forceinline__ void map_workgroup(int id, int n_items, int n_qt, int &bh, int &qtile) {
+    const int n_bh = n_items / n_qt, xcd = id % 8, slot = id / 8;
+    if (!CAUSAL && n_qt >= 128) {
+        // a head has 16 or more tiles per XCD anyway: ids in order (query tile fastest), every XCD works
+        // on the same one or two heads, and a tile missed by one L2 is likely still in the last-level cache
+        bh = id / n_qt;
+        qtile = id % n_qt;
+    } else if (!CAUSAL) {
+        // shorter sequences: head-major items cut into 8 contiguous ranges, one per XCD, walked in order
+        // (otherwise an XCD would hold only n_qt/8 tiles of each of many heads at a time)
+        const int pos = xcd * (n_items / 8) + min(xcd, n_items % 8) + slot;
+        bh = pos / n_qt;
+        qtile = pos % n_qt;
+    } else if (n_bh % 8 == 0) {
+        // an XCD owns n_bh/8 adjacent heads and takes them in windows of G heads -- enough tiles to fill
+        // its 64 workgroup slots twice --, inside a window the longest tiles of all heads first
+        const int hp = n_bh / 8;
+        const int G = max(1, min(hp, (127 + n_qt) / n_qt));
+        const int w = slot / (G * n_qt), r = slot - w * G * n_qt;
+        const int hw = min(G, hp - w * G);  // heads in this window (the last one may be short)
+        bh = xcd * hp + w * G + r % hw;
+        qtile = n_qt - 1 - r / hw;
+    } else {
+        // any other head count: longest tiles first over all heads
+        bh = id % n_bh;
+        qtile = n_qt - 1 - id / n_bh;
+    }
+}
 
 // One online-softmax step for one 16-query tile: biased scores s[t] (t<8: 16-key tiles of the
 // 128-key step) -> P^ packed as the FP8 MFMA operand; updates m, l; returns alpha.

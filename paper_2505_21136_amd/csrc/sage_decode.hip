@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void decode_kernel(const uint
 
 // Combine the S ranges of one row: m = max_s m_s, l = sum_s 2^(m_s - m) l_s, acc likewise, then the epilogue of the
 // prefill kernel, O = acc * (delta_V / l) (l carries the factor P_r), rounded to the output type.
-// T > 0: the partial results come from decode_kernel (T row tiles); T = 0: from attn_kernel<..., SPLIT> (query tiles
+// T > 0: the partial results come from decode_kernel (T row tiles); T = 0: from prefill_kernel<..., SPLIT> (query tiles
 // of 128 rows).  One workgroup of 256 threads per row (grid B*Hq*Nq): thread t owns channels 4*(t % (D/4)) .. +3 and the ranges
 // t / (D/4), + 256/(D/4), ...; the shares are added in a fixed order through LDS, so the result does not depend on
 // timing.  (A row's ranges are read by many threads at once: with one thread walking them the launch is a chain
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ pa
         p0 = (((size_t)b * Hkv + kvh) * S * T + ri / 16) * 16 + ri % 16;
         ps = (size_t)T * 16;
     } else {
-        // attn_kernel<..., SPLIT>: row r of the head sits in query tile r / 128, row r % 128 of workgroup
+        // prefill_kernel<..., SPLIT>: row r of the head sits in query tile r / 128, row r % 128 of workgroup
         // ((b*Hq + hq)*tiles + tile)*S + s
         const int tiles = (Nq + kBQ - 1) / kBQ;
         p0 = (((size_t)bh * tiles + r / kBQ) * S) * kBQ + r % kBQ;
@@ -390,8 +390,10 @@ hipError_t launch_attn_ranges(const void *q, const int8_t *k_i8, const uint8_t *
         return launch_attn(q, true, st, k_i8, v_fp8, nullptr, k_scale, v_scale, out, st, B, Hq, Hkv, Nq, Nk, d, causal,
                            sm_scale, p_r, bf16, stream);
     }
-    hipError_t e = launch_attn_split(q, k_i8, v_fp8, k_scale, v_scale, B, Hq, Hkv, Nq, Nk, d, causal, sm_scale, p_r, bf16,
-                                     S, steps_per_split, ws.part_acc, ws.part_ml, stream);
+    const Strides st = contiguous_bhnd(Hq, Nq, d);
+    hipError_t e = launch_prefill(q, true, st, k_i8, v_fp8, nullptr, k_scale, v_scale, nullptr, st, B, Hq, Hkv, Nq, Nk, d,
+                                  causal, sm_scale, p_r, bf16, stream, nullptr, nullptr, S, steps_per_split, ws.part_acc,
+                                  ws.part_ml);
     if (e != hipSuccess) return e;
     uint16_t *o16 = static_cast<uint16_t *>(out);
     const int n_rows = B * Hq * Nq, group = Hq / Hkv;

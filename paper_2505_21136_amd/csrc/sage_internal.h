@@ -74,6 +74,16 @@ hipError_t launch_attn(const void *q, bool q_raw, Strides q_st, const int8_t *k_
                        int Nq, int Nk, int d, bool causal, float sm_scale, float p_r, bool bf16_out,
                        hipStream_t stream, const float *q_mean = nullptr, const float *dsx = nullptr);
 
+// The kernel behind launch_attn for more than kSmallRows query rows and for the 4+8 variant (sage_prefill.hip).
+// part_acc != NULL: the key steps are cut into n_splits ranges of steps_per_split steps on separate workgroups, which
+// write partial results ([B*Hq*tiles][n_splits][128 rows][d] and [...][2] floats) instead of `out`.
+constexpr int kSmallRows = 64;
+hipError_t launch_prefill(const void *q, bool q_raw, Strides q_st, const int8_t *k_i8, const uint8_t *v_fp8,
+                          const float *q_scale, const float *k_scale, const float *v_scale, void *out, Strides o_st, int B,
+                          int Hq, int Hkv, int Nq, int Nk, int d, bool causal, float sm_scale, float p_r, bool bf16,
+                          hipStream_t stream, const float *q_mean, const float *dsx, int n_splits, int steps_per_split,
+                          float *part_acc, float *part_ml);
+
 // Decode-shaped attention (sage_decode.hip): (Hq/Hkv)*Nq <= 64 query rows per K/V head in T = ceil(rows/16) row
 // tiles, the keys cut into ranges of `steps_per_split` key steps; one wavefront per (batch, K/V head, range, row
 // tile) writes its (m, l, acc) per row into the scratch, a second launch combines the ranges.  q and out are
@@ -92,12 +102,8 @@ hipError_t launch_decode(const void *q, const int8_t *k_i8, const uint8_t *v_fp8
                          const DecodeScratch &ws);
 
 // The same idea for calls with more than 64 query rows per K/V head but too few (head, query tile) pairs to fill
-// the GPU: attn_kernel with its key steps cut into ranges on separate workgroups (sage_attn.hip), then the
-// combination launch of sage_decode.hip.  Partial results: [B*Hq*tiles][S][128 rows][d] and [...][2] floats.
-hipError_t launch_attn_split(const void *q, const int8_t *k_i8, const uint8_t *v_fp8, const float *k_scale,
-                             const float *v_scale, int B, int Hq, int Hkv, int Nq, int Nk, int d, bool causal,
-                             float sm_scale, float p_r, bool bf16, int n_splits, int steps_per_split, float *part_acc,
-                             float *part_ml, hipStream_t stream);
+// the GPU: launch_prefill with its key steps cut into ranges on separate workgroups, then the combination launch of
+// sage_decode.hip.
 int ranges_auto_steps_per_split(int B, int Hq, int Nq, int Nk);
 DecodeScratch ranges_scratch_layout(void *base, int B, int Hq, int Nq, int Nk, int d, int steps_per_split);
 hipError_t launch_attn_ranges(const void *q, const int8_t *k_i8, const uint8_t *v_fp8, const float *k_scale,
