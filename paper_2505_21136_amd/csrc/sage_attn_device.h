@@ -41,6 +41,9 @@ __device__ __forceinline__ int imax3(int a, int b, int c) { return max(max(a, b)
 __device__ __forceinline__ void swap16(float &a, float &b) {
     asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
 }
+__device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b) {
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
 __device__ __forceinline__ void swap32(float &a, float &b) {
     asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
 }
@@ -57,6 +60,19 @@ __device__ __forceinline__ float rowgroup_max(float x) {
     a = b = max_no_nan(a, b);
     swap32(a, b);
     return fmaxf(a, b);
+}
+// x of another lane of the same row of 16 (DPP control word CTRL); the vector ALU reads it directly, LDS is not involved
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+// maximum over all 64 lanes (no NaN)
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp<0xb1>(x));   // quad_perm [1,0,3,2]
+    x = fmaxf(x, dpp<0x4e>(x));   // quad_perm [2,3,0,1]
+    x = fmaxf(x, dpp<0x141>(x));  // row_half_mirror
+    x = fmaxf(x, dpp<0x140>(x));  // row_mirror
+    return rowgroup_max(x);
 }
 __device__ __forceinline__ float rowgroup_sum(float x) {
     float a = x, b = x;

@@ -71,10 +71,10 @@ __device__ __forceinline__ int lane_now() {
 }
 
 // Wavefronts per SIMD the register budget is set for: at d = 64 the accumulator is half as large and a third wavefront fits
-// (N = 777: 60.7 -> 57.0 us, N = 8192: 906 -> 885 us with 2 -> 3); the 4+8 variant and the ranges need a few registers more.
-template <int D, bool Q4, bool SPLIT>
+// (B 16, H 16, N 777: 60.7 -> 57.0 us, B 2, H 32, N 8192: 906 -> 885 us with 2 -> 3); the 4+8 variant needs a few registers more.
+template <int D, bool Q4>
 constexpr int prefill_waves_per_simd() {
-    return D == 128 || Q4 || SPLIT ? 2 : 3;
+    return D == 128 || Q4 ? 2 : 3;
 }
 
 // QRAW: Q arrives unquantised and the workgroup quantises its block in the prologue (the stand-alone quantiser's binary32
@@ -86,7 +86,7 @@ constexpr int prefill_waves_per_simd() {
 // one workgroup per (head, query tile, range), which runs the recurrence on its range alone and writes (m, l, acc) per row
 // to `part_ml` / `part_acc` ([item][range][128 rows][2] and [...][D] floats); merge_kernel (sage_decode.hip) combines them.
 template <int D, bool CAUSAL, bool BF16, bool QRAW, bool Q4, bool SPLIT>
-__global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void prefill_kernel(
+__global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefill_kernel(
     const void *__restrict__ Qsrc, const int8_t *__restrict__ Kc, const uint8_t *__restrict__ Vt,
     const float *__restrict__ dq, const float *__restrict__ dk, const float *__restrict__ dv,
     uint16_t *__restrict__ out, Strides q_st, Strides o_st, int Nq, int Nk, int nT, int nQblk, int nKblk, int Hq,
@@ -185,8 +185,6 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
 #pragma unroll
         for (int k = 0; k < NP; ++k) copy_k(jb, k);
         copy_ds(jb);
-#pragma unroll
-        for (int k = 0; k < NP; ++k) copy_k(jb + 1, k);
     }
     // the first step's "P^ V^ of the step before" multiplies zeros: its V^ buffer must hold numbers
 #pragma unroll
@@ -224,8 +222,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
                     for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(f[i]));
                 }
             }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+        amax = wave_max(amax);
         if (lane == 0) q_wave_max[wave] = amax;
     } else {
         const int8_t *Qr = static_cast<const int8_t *>(Qsrc) + (bh / Hq) * q_st.b + (bh % Hq) * q_st.h + qrow * q_st.n;
@@ -238,8 +235,13 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
     // the output scales are fetched now and parked in LDS: the epilogue then waits for no global load
     if (tid < D / 4)
         *reinterpret_cast<float4 *>(dv_lds + 4 * tid) = *reinterpret_cast<const float4 *>(dv + (size_t)bhk * D + 4 * tid);
+    const float *dkh = dk + (size_t)bhk * nKblk;
+    const float dk_first = dkh[min(64 * (jb >> 5) + lane, nKblk - 1)];
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): K^(jb) has landed
     __syncthreads();
+    // (not before: the loads above would be waited for behind it)
+#pragma unroll
+    for (int k = 0; k < NP; ++k) copy_k(jb + 1, k);
 
     float delta_q;
     if constexpr (QRAW) {
@@ -268,7 +270,6 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
     delta_q = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, delta_q)));
     // de-quantisation constants delta_Q * delta_K * sm_scale * log2(e): every 32 steps each lane computes that of one K block
     // and parks it in this wavefront's own strip of LDS, from which a step takes its two
-    const float *dkh = dk + (size_t)bhk * nKblk;
     const auto park_constants = [&](int j) {
         // (the product is made each time: kept, it would cost registers of every lane)
         float f, sm;
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
         const int blk = min(64 * (j >> 5) + ln, nKblk - 1);
         cst_lds[wave][ln] = (float)(cq * (double)dkh[blk]);
     };
-    park_constants(jb);
+    cst_lds[wave][lane] = (float)((double)delta_q * (double)sm_scale * 1.4426950408889634 * (double)dk_first);
 
     // ---- state of the recurrence ----
     float m = -INFINITY, l = 0.0f, alpha = 1.0f;
@@ -330,81 +331,48 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
         for (int n = 0; n < 4 * KC; ++n) mfma_qk(read_k(base, n), n);
     }
 
-    // One key step: P^ of step j from its scores, with P^V^ of step j-1 and Q.K^T of step j+1 in between.
-    const auto step = [&](auto masked, int j) __attribute__((always_inline)) {
+    // ---- the arithmetic of a step, in pieces ----
+    // Maximum over the scores of key tile t (MASKED: keys beyond this lane's limit count as minus infinity from here on; `lim`
+    // is counted from this lane's first key of the step).  im: integer maxima, two chains per K block; fm: the 4+8 variant's,
+    // whose scores become finished exponents here (ds: the step's correction terms).
+    const auto max_tile = [&](auto masked, int t, int lim, float cb, const float *ds, int (&im)[4], float (&fm)[4])
+                              __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked)::value;
-        constexpr int NQK = 4 * KC, NPV = 2 * CT;
-        const int key0 = j * kW;
-        // operands read ahead: VA P^V^ tiles, KA Q.K^T tiles (d = 64 has half as many of both, and 168 registers)
-        constexpr int VA = D == 128 ? 2 : 1, KA = D == 128 ? 4 : 2;
-        v8i vf[VA];
-        v4i kf[KA];
 #pragma unroll
-        for (int r = 0; r < VA; ++r) vf[r] = read_v(par, r);
-        const float2 cc = *reinterpret_cast<const float2 *>(&cst_lds[wave][(2 * j) & 63]);
-        const float c0 = cc.x, c1 = cc.y;
-        rescale();  // (by the factor of the step before, whose P^V^ follows now)
-
-        // MASKED: last visible key of this lane's row, counted from this lane's first key of the step
-        int lim = 0;
-        bool blind = false;  // the row sees no key of this step
-        if constexpr (MASKED) {
-            const int ln = lane_now();
-            lim = Nk - 1;
-            if constexpr (CAUSAL) lim = min(lim, row0 + (ln & 31) + shift);
-            blind = lim < key0;
-            lim -= key0 + 4 * (ln >> 5);
-        }
-
-        // ---- maximum of the step, P^V^ of the first 64 keys of step j-1 in between ----
-        int im[4] = {INT_MIN, INT_MIN, INT_MIN, INT_MIN};
-        float fm[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        for (int b = 0; b < 4; ++b) {
+            if constexpr (Q4) {
+                // position 32g' + 4t' + i of a tile is key 16t' + 4g' + i: here t' = 2t + (b >> 1), g' = 2(b & 1) + h
+                const float4 d4 = *reinterpret_cast<const float4 *>(ds + 32 * (2 * (b & 1) + h) + 4 * (2 * t + (b >> 1)));
+                const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            {
+                for (int i = 0; i < 4; ++i) {
+                    const int sv = s[t][4 * b + i];
+                    float x = __builtin_fmaf((float)sv, cb, dd[i]);
+                    if constexpr (MASKED) x = 32 * t + 8 * b + i > lim ? -INFINITY : x;
+                    fm[2 * (t & 1) + (i & 1)] = fmaxf(fm[2 * (t & 1) + (i & 1)], x);
+                    s[t][4 * b + i] = __builtin_bit_cast(int, x);
+                }
+            } else {
+                if constexpr (MASKED) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    if constexpr (Q4) {
-                        // position 32g' + 4t' + i of a tile is key 16t' + 4g' + i: here t' = 2t + (b >> 1), g' = 2(b & 1) + h
-                        const float4 d4 = *reinterpret_cast<const float4 *>(
-                            &ds_lds[j & 1][32 * (2 * (b & 1) + h) + 4 * (2 * t + (b >> 1))]);
-                        const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
-                        const float cb = t < 2 ? c0 : c1;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int sv = s[t][4 * b + i];
-                            float x = __builtin_fmaf((float)sv, cb, dd[i]);
-                            if constexpr (MASKED) {
-                                if (32 * t + 8 * b + i > lim) x = -INFINITY;
-                            }
-                            fm[2 * (t & 1) + (i & 1)] = fmaxf(fm[2 * (t & 1) + (i & 1)], x);
-                            s[t][4 * b + i] = __builtin_bit_cast(int, x);
-                        }
-                    } else {
-                        if constexpr (MASKED) {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                if (32 * t + 8 * b + i > lim) s[t][4 * b + i] = INT_MIN;
-                        }
-                        // (two chains per K block)
-                        int &a = im[2 * (t >> 1) + (b & 1)];
-                        if (!(t & 1) && b < 2) {
-                            a = imax3(s[t][4 * b], s[t][4 * b + 1], s[t][4 * b + 2]);
-                            a = max(a, s[t][4 * b + 3]);
-                        } else {
-                            a = imax3(a, s[t][4 * b], s[t][4 * b + 1]);
-                            a = imax3(a, s[t][4 * b + 2], s[t][4 * b + 3]);
-                        }
-                    }
+                    for (int i = 0; i < 4; ++i)
+                        if (32 * t + 8 * b + i > lim) s[t][4 * b + i] = INT_MIN;
+                }
+                int &a = im[2 * (t >> 1) + (b & 1)];
+                if (!(t & 1) && b < 2) {
+                    a = imax3(s[t][4 * b], s[t][4 * b + 1], s[t][4 * b + 2]);
+                    a = max(a, s[t][4 * b + 3]);
+                } else {
+                    a = imax3(a, s[t][4 * b], s[t][4 * b + 1]);
+                    a = imax3(a, s[t][4 * b + 2], s[t][4 * b + 3]);
                 }
             }
-            if (t < CT) {
-                mfma_pv(vf[t % VA], t);
-                if (t + VA < NPV) vf[t % VA] = read_v(par, t + VA);
-            }
-            if (t < NP) copy_v(j, t);
-            __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    // The row's new running maximum; alpha becomes the factor of this step.
+    const auto new_max = [&](auto masked, float c0, float c1, const int (&im)[4], const float (&fm)[4])
+                             __attribute__((always_inline)) {
+        constexpr bool MASKED = decltype(masked)::value;
         float mc;
         if constexpr (Q4) {
             mc = fmaxf(fmaxf(fm[0], fm[1]), fmaxf(fm[2], fm[3]));
@@ -419,6 +387,57 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
         }
         const float m_new = max_no_nan(m, halves_max(mc));
         alpha = __builtin_amdgcn_exp2f(m - m_new);
+        return m_new;
+    };
+    // P^ of the four keys 32t + 8b + 4h .. + 3, and their share of the row sum.  mo = log2 P_r - m.
+    const auto exp_quad = [&](auto masked, int t, int b, float cb, float mo, float &lsum0, float &lsum1)
+                              __attribute__((always_inline)) {
+        constexpr bool MASKED = decltype(masked)::value;
+        float p[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int sbits = s[t][4 * b + i];
+            p[i] = __builtin_amdgcn_exp2f(Q4 ? __builtin_bit_cast(float, sbits) + mo : __builtin_fmaf((float)sbits, cb, mo));
+            if constexpr (MASKED && !Q4) p[i] = sbits == INT_MIN ? 0.0f : p[i];
+        }
+        lsum0 += p[0] + p[1];
+        lsum1 += p[2] + p[3];
+        int w;  // both halves are overwritten below: an opaque undefined seed saves the v_mov of a zero
+        asm volatile("" : "=v"(w));
+        w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], w, false);
+        w = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
+        // (pinned to their place: nothing else keeps the arithmetic from sinking to its use a step later)
+        asm volatile("" : "+v"(w), "+v"(lsum0), "+v"(lsum1));
+        pb[t >> 1][4 * (b & 1) + 2 * (t & 1) + (b >> 1)] = w;
+    };
+
+    // One key step without a mask: P^ of step j from its scores, with P^V^ of step j-1 and Q.K^T of step j+1 in between.
+    const auto step = [&](int j) __attribute__((always_inline)) {
+        constexpr std::false_type no_mask{};
+        constexpr int NQK = 4 * KC, NPV = 2 * CT;
+        // operands read ahead: VA P^V^ tiles, KA Q.K^T tiles (d = 64 has half as many of both, and 168 registers)
+        constexpr int VA = D == 128 ? 2 : 1, KA = D == 128 ? 4 : 2;
+        v8i vf[VA];
+        v4i kf[KA];
+#pragma unroll
+        for (int r = 0; r < VA; ++r) vf[r] = read_v(par, r);
+        const float2 cc = *reinterpret_cast<const float2 *>(&cst_lds[wave][(2 * j) & 63]);
+        rescale();  // (by the factor of the step before, whose P^V^ follows now)
+
+        // ---- maximum of the step, P^V^ of the first 64 keys of step j-1 in between ----
+        int im[4] = {INT_MIN, INT_MIN, INT_MIN, INT_MIN};
+        float fm[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            max_tile(no_mask, t, 0, t < 2 ? cc.x : cc.y, ds_lds[j & 1], im, fm);
+            if (t < CT) {
+                mfma_pv(vf[t % VA], t);
+                if (t + VA < NPV) vf[t % VA] = read_v(par, t + VA);
+            }
+            if (t < NP) copy_v(j, t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const float m_new = new_max(no_mask, cc.x, cc.y, im, fm);
         const float mo = log2_pr - m_new;  // P~ * P_r = 2^(x - m' + log2 P_r)
         float lsum0 = -0.0f, lsum1 = -0.0f;  // x + (-0) is x for every x: the first addition folds away
 #pragma unroll
@@ -429,28 +448,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
         constexpr int SPT = 4 / KC;  // slots per Q.K^T MFMA (1 at d = 128, 2 at d = 64)
 #pragma unroll
         for (int sl = 0; sl < 16; ++sl) {
-            const int t = sl >> 2, b = sl & 3;
-            const int pi = 4 * (b & 1) + 2 * (t & 1) + (b >> 1);  // where these four keys sit in the operand
-            {
-                const float cb = t < 2 ? c0 : c1;
-                float p[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int sbits = s[t][4 * b + i];
-                    p[i] = __builtin_amdgcn_exp2f(Q4 ? __builtin_bit_cast(float, sbits) + mo
-                                                     : __builtin_fmaf((float)sbits, cb, mo));
-                    if constexpr (MASKED && !Q4) p[i] = sbits == INT_MIN ? 0.0f : p[i];
-                }
-                lsum0 += p[0] + p[1];
-                lsum1 += p[2] + p[3];
-                int w;  // both halves are overwritten below: an opaque undefined seed saves the v_mov of a zero
-                asm volatile("" : "=v"(w));
-                w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], w, false);
-                w = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
-                // (pinned to their slot: nothing else keeps the arithmetic from sinking to its use a step later)
-                asm volatile("" : "+v"(w), "+v"(lsum0), "+v"(lsum1));
-                pb[t >> 1][pi] = w;
-            }
+            exp_quad(no_mask, sl >> 2, sl & 3, sl < 8 ? cc.x : cc.y, mo, lsum0, lsum1);
             // P^V^ of the last 64 keys of step j-1 in the slots of the first two tiles (their registers are rewritten by the
             // last two)
             constexpr int EVERY = 8 / CT;
@@ -472,8 +470,57 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
 #pragma unroll
         for (int n = NQK - KC; n < NQK; ++n) mfma_qk(kf[n % KA], n);
         static_assert(KA <= KC, "the last tile's operands are all read ahead");
+        l = l * alpha + (lsum0 + lsum1);
+        m = m_new;
+        if (((j + 1) & 31) == 0) park_constants(j + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // A step with a mask (the causal diagonal, the ragged end: at most the last two of a wavefront), without the fine
+    // interleaving.  Key tiles that no row of the wavefront sees (t >= t_hi) cost no arithmetic.
+    const auto masked_step = [&](int j) __attribute__((always_inline)) {
+        constexpr std::true_type mask{};
+        const int key0 = j * kW;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) copy_v(j, k);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) copy_k(j + 2, k);
+        copy_ds(j + 1);
+        const float2 cc = *reinterpret_cast<const float2 *>(&cst_lds[wave][(2 * j) & 63]);
+        rescale();
+#pragma unroll
+        for (int r = 0; r < 2 * CT; ++r) mfma_pv(read_v(par, r), r);
+        const int ln = lane_now();
+        int lim = Nk - 1;  // last visible key of this lane's row
+        if constexpr (CAUSAL) lim = min(lim, row0 + (ln & 31) + shift);
+        const bool blind = lim < key0;  // the row sees no key of this step
+        lim -= key0 + 4 * (ln >> 5);
+        const int lim_max = CAUSAL ? min(Nk - 1, row0 + 31 + shift) : Nk - 1;
+        const int t_hi = min(4, ((lim_max - key0) >> 5) + 1);
+        int im[4] = {INT_MIN, INT_MIN, INT_MIN, INT_MIN};
+        float fm[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (t < t_hi) max_tile(mask, t, lim, t < 2 ? cc.x : cc.y, ds_lds[j & 1], im, fm);
+        const float m_new = new_max(mask, cc.x, cc.y, im, fm);
+        const float mo = log2_pr - m_new;
+        float lsum0 = -0.0f, lsum1 = -0.0f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (t < t_hi) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) exp_quad(mask, t, b, t < 2 ? cc.x : cc.y, mo, lsum0, lsum1);
+            } else {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) pb[t >> 1][4 * (b & 1) + 2 * (t & 1) + (b >> 1)] = 0;
+            }
+        }
+        if (j + 1 < my_steps) {
+#pragma unroll
+            for (int n = 0; n < 4 * KC; ++n) mfma_qk(read_k(par, n), n);
+        }
         float l_new = l * alpha + (lsum0 + lsum1);
-        if constexpr (SPLIT && MASKED) {
+        if constexpr (SPLIT) {
             // a row that has seen no key of this range yet and sees none in this step keeps its empty state (the step's
             // arithmetic on (-inf) - (-inf) is undefined; its P^ is zero either way); without ranges every row sees key 0
             if (blind && m == -INFINITY) {
@@ -484,7 +531,6 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
         l = l_new;
         m = m_new;
         if (((j + 1) & 31) == 0) park_constants(j + 1);
-        __builtin_amdgcn_sched_barrier(0);
     };
 
     // Step j's iteration starts with a barrier: K^(j+1) and V^(j-1) have landed for every wavefront, and the buffers of K^(j)
@@ -499,12 +545,12 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
     int j = jb;
     for (; j < full_steps; ++j) {
         arrive();
-        step(std::false_type{}, j);
+        step(j);
         par ^= TILE;
     }
     for (; j < my_steps; ++j) {
         arrive();
-        step(std::true_type{}, j);
+        masked_step(j);
         par ^= TILE;
     }
     arrive();
@@ -539,18 +585,29 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4, SPLIT>())) void
         return;
     }
     // ---- epilogue: O = acc * delta_V / (P_r * l); l already carries the factor P_r ----
-    const float inv = 1.0f / lsum;
-    if (erow < Nq) {
+    {
+        const float inv = 1.0f / lsum;
         uint16_t *orow = out + (bh / Hq) * o_st.b + (bh % Hq) * o_st.h + erow * o_st.n;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int c = 32 * ct + 8 * b + 4 * eh;
-                const float4 sc = *reinterpret_cast<const float4 *>(dv_lds + c);
-                const float y0 = o[ct][4 * b] * (sc.x * inv), y1 = o[ct][4 * b + 1] * (sc.y * inv);
-                const float y2 = o[ct][4 * b + 2] * (sc.z * inv), y3 = o[ct][4 * b + 3] * (sc.w * inv);
-                *reinterpret_cast<uint2 *>(orow + c) = make_uint2(pack2<BF16>(y0, y1), pack2<BF16>(y2, y3));
+            for (int b2 = 0; b2 < 2; ++b2) {
+                // channels 32ct + 8b + 4h .. + 3 for b = 2*b2 and 2*b2 + 1; after the exchange between the wavefront's halves a
+                // lane holds the eight channels of b = 2*b2 + h and stores 16 bytes
+                uint32_t w[2][2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int b = 2 * b2 + e;
+                    const float4 sc = *reinterpret_cast<const float4 *>(dv_lds + 32 * ct + 8 * b + 4 * eh);
+                    const float y0 = o[ct][4 * b] * (sc.x * inv), y1 = o[ct][4 * b + 1] * (sc.y * inv);
+                    const float y2 = o[ct][4 * b + 2] * (sc.z * inv), y3 = o[ct][4 * b + 3] * (sc.w * inv);
+                    w[e][0] = pack2<BF16>(y0, y1);
+                    w[e][1] = pack2<BF16>(y2, y3);
+                }
+                swap32(w[0][0], w[1][0]);
+                swap32(w[0][1], w[1][1]);
+                if (erow < Nq)
+                    *reinterpret_cast<uint4 *>(orow + 32 * ct + 16 * b2 + 8 * eh) = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
             }
     }
 #endif  // __HIP_DEVICE_COMPILE__
