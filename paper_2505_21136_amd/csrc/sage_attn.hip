@@ -403,9 +403,22 @@ hipError_t launch_attn(const void *q, bool q_raw, Strides q_st, const int8_t *k_
                        const float *q_scale, const float *k_scale, const float *v_scale, void *out, Strides o_st, int B,
                        int Hq, int Hkv, int Nq, int Nk, int d, bool causal, float sm_scale, float p_r, bool bf16_out,
                        hipStream_t stream, const float *q_mean, const float *dsx) {
-    if (dsx || Nq > kSmallRows)
+    // Which kernel: by how many workgroups the query rows make.  Up to one workgroup of 32 rows per CU, a key step is spread
+    // over a workgroup's wavefronts (sage_spread.hip); then with 64 rows per workgroup; beyond one of those per CU the CUs are
+    // filled better by whole steps per wavefront and two workgroups of 128 rows each (sage_prefill.hip).  Measured, us, at
+    // 1024 x 1024 and 1024 x 16384 (rows x keys, d 128, full), spread 32 / spread 64 / prefill: 128 tiles of 32 rows
+    // 10.6 / 13.7 / 16.5 and 76 / 104 / 172; 512 tiles 20.3 / 14.5 / 16.8 and 152 / 111 / 173; 1024 tiles 38.5 / 27.8 / 17.8
+    // and 301 / 220 / 181.  Up to kSmallRows rows the kernel of this file remains (16 rows per wavefront: half the padding),
+    // and the 4+8 variant exists in the prefill kernel only.
+    if (Nq > kSmallRows || dsx) {
+        const long heads = (long)B * Hq;
+        const int row_groups = dsx ? 0 : heads * cdiv(Nq, 32) <= kCUs ? 1 : heads * cdiv(Nq, 64) <= kCUs ? 2 : 0;
+        if (row_groups)
+            return launch_spread(q, q_raw, q_st, k_i8, v_fp8, q_scale, k_scale, v_scale, out, o_st, B, Hq, Hkv, Nq, Nk, d,
+                                 causal, sm_scale, p_r, bf16_out, stream, row_groups);
         return launch_prefill(q, q_raw, q_st, k_i8, v_fp8, q_scale, k_scale, v_scale, out, o_st, B, Hq, Hkv, Nq, Nk, d, causal,
                               sm_scale, p_r, bf16_out, stream, q_mean, dsx, 1, 0, nullptr, nullptr);
+    }
     const float log2_pr = (float)log2((double)p_r);
     if (d == 128)
         return launch_d<128, 1, 8, 4>(q, q_raw, q_st, k_i8, v_fp8, q_scale, k_scale, v_scale, out, o_st, B, Hq, Hkv, Nq, Nk,

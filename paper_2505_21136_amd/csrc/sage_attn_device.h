@@ -31,6 +31,25 @@ __device__ __forceinline__ int v_off(int row, int c16) { return row * 128 + ((c1
 
 __device__ __forceinline__ int imax3(int a, int b, int c) { return max(max(a, b), c); }
 
+#if defined(__HIP_DEVICE_COMPILE__)
+// A global -> LDS copy: 64 lanes x 16 (or 4) bytes from the buffer at per-lane offset `voff` to LDS at `dst` + 16 (4) * lane.
+// Written as asm because of the compiler's wait insertion: it cannot tell the two buffers of a tile apart and makes every LDS
+// read behind such a copy wait for it.  The kernel waits itself (vmcnt(0) in front of the barrier that ends a step).
+__device__ __forceinline__ v4i lds_copy_rsrc(const void *base, int bytes) {
+    const uint64_t a = (uint64_t)base;
+    return v4i{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xffffu), bytes, 0x00020000};
+}
+__device__ __forceinline__ int lds_address(const void *p) {
+    return (int)(uint32_t)(uint64_t)(const __attribute__((address_space(3))) void *)p;
+}
+__device__ __forceinline__ void lds_copy16(v4i rsrc, int voff, int dst) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(rsrc), "s"(dst) : "m0");
+}
+__device__ __forceinline__ void lds_copy4(v4i rsrc, int voff, int dst) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds" ::"v"(voff), "s"(rsrc), "s"(dst) : "m0");
+}
+#endif  // __HIP_DEVICE_COMPILE__
+
 // Cross-lane exchange over the four 16-lane rows of a wavefront (lanes l, l^16, l^32, l^48).
 // v_permlane16_swap exchanges the odd rows of its first register with the even rows of its second,
 // v_permlane32_swap the upper half of the first with the lower half of the second: starting from
@@ -78,6 +97,18 @@ __device__ __forceinline__ float rowgroup_sum(float x) {
     float a = x, b = x;
     swap16(a, b);
     a = b = a + b;
+    swap32(a, b);
+    return a + b;
+}
+
+// max (no NaN) / sum of a value over the two halves of the wavefront (lanes l and l ^ 32)
+__device__ __forceinline__ float halves_max(float x) {
+    float a = x, b = x;
+    swap32(a, b);
+    return max_no_nan(a, b);
+}
+__device__ __forceinline__ float halves_sum(float x) {
+    float a = x, b = x;
     swap32(a, b);
     return a + b;
 }

@@ -15,6 +15,8 @@ constexpr int kW = 128;         // keys per online-softmax step (= V tile)
 #endif
 constexpr int kStatRows = SAGE_STAT_ROWS;  // tokens per partial column statistic
 
+constexpr int kCUs = 256;  // compute units of the GPU
+
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // Element strides (batch, head, token) of a 4-D tensor whose channels are contiguous.
@@ -83,6 +85,13 @@ hipError_t launch_prefill(const void *q, bool q_raw, Strides q_st, const int8_t 
                           int Hq, int Hkv, int Nq, int Nk, int d, bool causal, float sm_scale, float p_r, bool bf16,
                           hipStream_t stream, const float *q_mean, const float *dsx, int n_splits, int steps_per_split,
                           float *part_acc, float *part_ml);
+
+// The kernel behind launch_attn for more than kSmallRows query rows that make too few query tiles to fill the GPU
+// (sage_spread.hip).
+hipError_t launch_spread(const void *q, bool q_raw, Strides q_st, const int8_t *k_i8, const uint8_t *v_fp8,
+                         const float *q_scale, const float *k_scale, const float *v_scale, void *out, Strides o_st, int B,
+                         int Hq, int Hkv, int Nq, int Nk, int d, bool causal, float sm_scale, float p_r, bool bf16,
+                         hipStream_t stream, int row_groups);
 
 // Decode-shaped attention (sage_decode.hip): (Hq/Hkv)*Nq <= 64 query rows per K/V head in T = ceil(rows/16) row
 // tiles, the keys cut into ranges of `steps_per_split` key steps; one wavefront per (batch, K/V head, range, row
