@@ -307,8 +307,11 @@ __global__ __launch_bounds__(256) void block_mean_kernel(const uint16_t *__restr
 // (Q block, query head) pairs of a K/V head's group the columns, 32 of each per wavefront.  A lane keeps half a K' row (its
 // key's channels D/2 * h ..) and half a mean row in registers.  A workgroup of 4 wavefronts takes one 128-key tile and
 // `tiles` column tiles.  Columns are numbered Q block major, so that what a causal launch does not need (the Q blocks that
-// see no key of the tile) is a prefix that is skipped.  Measured (B 2, 32 / 8 heads, N 3000, d 128, causal): 122 us with one
-// key per thread and the means broadcast from LDS, which one LDS read per four FMAs bound; 27 us now.
+// see no key of the tile) is a prefix that is skipped.  With 64 dependent MFMAs of 64 cycles per wavefront and tile it is the
+// latency in front of them that counts: keys, means and K mean are fetched together.  Measured (B 2, 32 / 8 heads, N 3000,
+// d 128, causal / full): 122 us with one key per thread and the means broadcast from LDS (one LDS read per four FMAs);
+// 23.8 / 35.7 us with the K mean read behind the mask of the last keys, pair by pair, and the means piece by piece; now
+// 16.0 / 20.2 us.
 // ---------------------------------------------------------------------------
 template <bool BF16, int D>
 __global__ __launch_bounds__(256) void delta_s_kernel(const uint16_t *__restrict__ K, Strides k_st, int Hkv,
@@ -320,6 +323,7 @@ __global__ __launch_bounds__(256) void delta_s_kernel(const uint16_t *__restrict
     typedef float v16f __attribute__((ext_vector_type(16)));
     constexpr int HALF = D / 2;
     __shared__ __attribute__((aligned(16))) float qm[32][D + 4];
+    __shared__ __attribute__((aligned(16))) float km[D];
     const int T = blockIdx.x, bhk = blockIdx.y;
     const int group = Hq / Hkv;
     // causal (mask aligned to the end of both sequences): Q block i sees key n iff n <= i*kBQ + kBQ-1 + Nk - Nq
@@ -329,35 +333,65 @@ __global__ __launch_bounds__(256) void delta_s_kernel(const uint16_t *__restrict
     if (col0 >= col_end) return;  // (workgroup-uniform)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lq = lane & 31, h = lane >> 5;
     const int n = T * 128 + wave * 32 + lq;  // this lane's key
-    float kp[HALF];
-    {
-        const uint16_t *Kr = K + (bhk / Hkv) * k_st.b + (bhk % Hkv) * k_st.h + min(n, Nk - 1) * k_st.n + h * HALF;
-        const float *mu = k_mean + (size_t)bhk * D + h * HALF;
-#pragma unroll
-        for (int c8 = 0; c8 < HALF / 8; ++c8) {
-            float f[8];
-            unpack8<BF16>(*reinterpret_cast<const uint4 *>(Kr + c8 * 8), f);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) kp[c8 * 8 + j] = n < Nk ? f[j] - mu[c8 * 8 + j] : 0.0f;
-        }
-    }
     // a column: Q block i of query head bhq (columns past the end repeat the last one and are not stored)
     const auto column = [&](int c, int &i, int &bhq) {
         const int col = min(c, col_end - 1);
         i = col / group;
         bhq = (bhk / Hkv) * Hq + (bhk % Hkv) * group + col % group;
     };
-    for (int ct = 0; ct < tiles && col0 < col_end; ++ct, col0 += 32) {
-        // the tile's 32 mean rows: whole rows from memory, once for the four wavefronts
-        __syncthreads();
+    // every load of the first tile is issued before the first is waited for (a branch around a load makes it wait for itself)
+    const uint16_t *Kr = K + (bhk / Hkv) * k_st.b + (bhk % Hkv) * k_st.h + min(n, Nk - 1) * k_st.n + h * HALF;
+    uint4 raw[HALF / 8];
 #pragma unroll
-        for (int e = threadIdx.x; e < 32 * D / 4; e += 256) {
-            int i, bhq;
-            column(col0 + e / (D / 4), i, bhq);
-            *reinterpret_cast<float4 *>(&qm[e / (D / 4)][4 * (e % (D / 4))]) =
-                *reinterpret_cast<const float4 *>(q_mean + ((size_t)bhq * nQ + i) * D + 4 * (e % (D / 4)));
+    for (int c8 = 0; c8 < HALF / 8; ++c8) raw[c8] = *reinterpret_cast<const uint4 *>(Kr + c8 * 8);
+    // a tile's 32 mean rows: whole rows from memory, once for the four wavefronts
+    constexpr int NM = 32 * D / 4 / 256;
+    const auto load_mean = [&](int x) {
+        const int e = threadIdx.x + 256 * x;
+        int i, bhq;
+        column(col0 + e / (D / 4), i, bhq);
+        return *reinterpret_cast<const float4 *>(q_mean + ((size_t)bhq * nQ + i) * D + 4 * (e % (D / 4)));
+    };
+    const auto stage_mean = [&](int x, const float4 &v) {
+        const int e = threadIdx.x + 256 * x;
+        *reinterpret_cast<float4 *>(&qm[e / (D / 4)][4 * (e % (D / 4))]) = v;
+    };
+    const auto stage_tile = [&]() {
+        const float4 a = load_mean(0), b = load_mean(1);
+        if constexpr (NM == 4) {
+            const float4 c = load_mean(2), d = load_mean(3);
+            stage_mean(2, c);
+            stage_mean(3, d);
         }
-        __syncthreads();
+        stage_mean(0, a);
+        stage_mean(1, b);
+    };
+    static_assert(NM == 2 || NM == 4, "head dimension 64 or 128");
+    const int kc = 4 * (threadIdx.x % (D / 4));  // (several threads write the same value)
+    const float4 kmean4 = *reinterpret_cast<const float4 *>(k_mean + (size_t)bhk * D + kc);
+    stage_tile();
+    *reinterpret_cast<float4 *>(km + kc) = kmean4;
+    __syncthreads();
+    float kp[HALF];  // (of the last key where n is beyond it)
+#pragma unroll
+    for (int c8 = 0; c8 < HALF / 8; ++c8) {
+        float f[8];
+        unpack8<BF16>(raw[c8], f);
+#pragma unroll
+        for (int j4 = 0; j4 < 2; ++j4) {
+            const float4 mu = *reinterpret_cast<const float4 *>(km + h * HALF + c8 * 8 + 4 * j4);
+            kp[c8 * 8 + 4 * j4] = f[4 * j4] - mu.x;
+            kp[c8 * 8 + 4 * j4 + 1] = f[4 * j4 + 1] - mu.y;
+            kp[c8 * 8 + 4 * j4 + 2] = f[4 * j4 + 2] - mu.z;
+            kp[c8 * 8 + 4 * j4 + 3] = f[4 * j4 + 3] - mu.w;
+        }
+    }
+    for (int ct = 0; ct < tiles && col0 < col_end; ++ct, col0 += 32) {
+        if (ct > 0) {
+            __syncthreads();
+            stage_tile();
+            __syncthreads();
+        }
         int i, bhq;
         column(col0 + lq, i, bhq);
         v16f acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -368,6 +402,11 @@ __global__ __launch_bounds__(256) void delta_s_kernel(const uint16_t *__restrict
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 1], v.y, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 2], v.z, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 3], v.w, acc, 0, 0, 0);
+        }
+        if (T * 128 + 127 >= Nk) {  // (workgroup-uniform) keys beyond the last hold zeros
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (T * 128 + 32 * wave + 8 * (e >> 2) + 4 * h + (e & 3) >= Nk) acc[e] = 0.0f;
         }
         // acc[4b + r] is key 32*wave + 8b + 4h + r of the tile: 16-key group t = 2*wave + (b >> 1), quad g = 2*(b & 1) + h
         if (col0 + lq < col_end) {
