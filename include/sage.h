@@ -373,14 +373,14 @@ int sage_diag_mfma_rate(int kind, int iters, int workgroups, float *sink, double
 
 /*
  * Not a step of the method: selects, process-wide, which kernels the K/V quantisers (sage_quant_kv,
- * sage_quant_kv_static, sage_quant_kv4 and the whole-pass entry points) launch.  Both choices compute the same
+ * sage_quant_kv_static, sage_quant_kv4, sage_quant_k, sage_quant_v and the whole-pass entry points) launch.  Both choices compute the same
  * codes, scales and mean (Sec. 2.1, Sec. 3).
  *   path        0 (default): by shape — the single-read kernel (K and V are read once: the workgroups of a head
- *               keep 64 KiB of tokens each in registers, exchange their partial column statistics through the
- *               workspace and then write the codes) when a head is at most 128 such workgroups (32768 tokens at
- *               d = 128, 65536 at d = 64), the three launches (statistics, finalize, codes; K and V read twice)
- *               above that; 1: always the three launches; 2: always the single-read kernel (calls then fail with
- *               SAGE_EHIP above 256 workgroups per head)
+ *               keep 64 or 128 KiB of tokens each in registers, exchange their partial column statistics through
+ *               the workspace and then write the codes) when a head is at most 128 workgroups of 128 KiB (65536
+ *               tokens at d = 128, 131072 at d = 64), the three launches (statistics, finalize, codes; K and V read
+ *               twice) above that; 1: always the three launches; 2: always the single-read kernel (calls for K and V
+ *               together then fail with SAGE_EHIP above 256 workgroups of 64 KiB per head)
  *   wait_ticks  how long a workgroup of the single-read kernel waits for the partials of its partners before it
  *               computes the head's statistic alone from global memory (same result), in ticks of the GPU's
  *               constant 100 MHz clock; negative: it does not wait at all (for tests of that branch); the

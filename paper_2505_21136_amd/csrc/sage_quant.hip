@@ -513,9 +513,9 @@ __global__ __launch_bounds__(256) void quant_kv_kernel(const uint16_t *__restric
 // K and V quantised with ONE read of each tensor (smoothing of Sec. 3, scales of Sec. 2.1; the same binary32
 // steps and the same outputs as the three launches above).  The codes of a token need a statistic of its whole
 // head (the K mean, the V maxima), so a token must wait somewhere between the statistics and the codes: here it
-// waits in registers.  A workgroup of 256 threads loads kResidentBytes of one (head, tensor) — 256 tokens at
-// d = 128, 512 at d = 64 — keeps them as 16 packed uint4 per thread, publishes its partial column statistic,
-// and then waits for the partials of all G = ceil(N / tokens) workgroups of the (head, tensor).  A partial is
+// waits in registers.  A workgroup of NTHR threads loads NTHR * 128 elements of one (head, tensor) — with 256 threads
+// 256 tokens at d = 128, 512 at d = 64 — keeps them as 16 packed uint4 per thread, publishes its partial column statistic,
+// and then (unless the head is its own alone, G = 1) waits for the partials of all G = ceil(N / tokens) workgroups of the (head, tensor).  A partial is
 // its own "there" flag: the partial buffers are zero at launch (the host enqueues zero_words_kernel in front)
 // and a value is stored with a bit pattern that is never all zero (+0.0 goes out as -0.0, which adds and
 // compares like it), each with one write-through store that is atomic for its 4 or 8 bytes.  Thread t first
@@ -530,14 +530,16 @@ __global__ __launch_bounds__(256) void quant_kv_kernel(const uint16_t *__restric
 // tells whether any thread's value is non-zero.)
 // Workgroup ids are group-major, and the hardware dispatches them in id order, so the G partners are resident
 // together as long as G does not exceed the workgroups the chip holds; since every workgroup reads G partials the
-// host takes this path only up to kResidentMaxGroup.  Grid: B*H*2*G; group 2*bh is K of head bh, 2*bh + 1 is V.
+// host takes this path only up to kResidentMaxGroup.  Grid: B*H*2*G, group 2*bh is K of head bh, 2*bh + 1 is V; or, for one
+// tensor alone, B*H*G.
 // ---------------------------------------------------------------------------
-constexpr int kResidentBytes = 65536;
-constexpr int kResidentMaxGroup = 128;       // largest group the shape-based choice takes (every workgroup reads G partials:
-                                             // measured faster than the three launches up to here, 17-26 % slower at 192-256)
+// tokens of a workgroup of n threads: 16 uint4 of 8 elements per thread
+constexpr int resident_tokens(int threads, int d) { return threads * 128 / d; }
+constexpr int kBothTensors = 0, kOnlyK = 1, kOnlyV = 2;  // what a launch quantises (both: K and V groups in turn)
+constexpr int kResidentMaxGroup = 128;       // largest group the shape-based choice takes (resident_threads)
 constexpr int kResidentHardMaxGroup = 256;   // largest group a forced choice may take (thread t polls partner t)
 constexpr long long kResidentWaitTicks = 50000;  // 0.5 ms
-inline int resident_group_size(int N, int d) { return cdiv(N, kResidentBytes / (2 * d)); }
+inline int resident_group_size(int N, int d, int threads) { return cdiv(N, resident_tokens(threads, d)); }
 
 __global__ __launch_bounds__(256) void zero_words_kernel(uint4 *w, int n) {
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -593,24 +595,25 @@ __device__ __forceinline__ bool resident_wait(const W *rows, int d, int G, long 
     }
 }
 
-template <bool BF16, int D, int QMAX>
-__global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
+template <bool BF16, int D, int QMAX, int NTHR>
+__global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
     const uint16_t *__restrict__ K, Strides k_st, const uint16_t *__restrict__ V, Strides v_st, int H, int N, int G,
     double *k_sum_part, float *v_max_part, float *k_mean, float *v_scale, float v_r,
     int8_t *__restrict__ k_codes, float *__restrict__ k_scale, int nK, uint8_t *__restrict__ Vt, int nT,
-    long long wait_ticks) {
-    constexpr int C = kResidentBytes / (2 * D);  // tokens of a workgroup
-    constexpr int LPR = D / 8;                   // lanes per row
-    constexpr int RP = 256 / LPR;                // rows per pass of the workgroup
+    long long wait_ticks, int tensors) {
     constexpr int NU = 16;                       // uint4 per thread
-    static_assert(C * LPR == NU * 256, "a workgroup's chunk is 16 uint4 per thread");
-    __shared__ __attribute__((aligned(16))) unsigned char smem[16384];
-    __shared__ float stat[D];      // the head's mean (K) or V_r / max (V)
-    __shared__ float wmax[4][8];   // per wavefront and K block: max |K'|
+    constexpr int NW = NTHR / 64;                // wavefronts
+    constexpr int LPR = D / 8;                   // lanes per row
+    constexpr int RP = NTHR / LPR;               // rows per pass of the workgroup
+    constexpr int C = NU * RP;                   // tokens of a workgroup
+    static_assert(C == resident_tokens(NTHR, D), "the host counts the same tokens");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[NTHR * 64];
+    __shared__ float stat[D];           // the head's mean (K) or V_r / max (V)
+    __shared__ float wmax[NW][C / kBK];  // per wavefront and K block: max |K'|
 
     const int grp = blockIdx.x / G, part = blockIdx.x % G;
-    const int bh = grp >> 1;
-    const bool is_v = grp & 1;  // (workgroup-uniform)
+    const int bh = tensors == kBothTensors ? grp >> 1 : grp;
+    const bool is_v = tensors == kBothTensors ? grp & 1 : tensors == kOnlyV;  // (workgroup-uniform)
     const int tid = threadIdx.x;
     const int co = tid % LPR, rr = tid / LPR;
     const int row0 = part * C;
@@ -653,15 +656,21 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
         if (tid < D) {
             double a = smd[0][tid];
             for (int i = 1; i < RP; ++i) a += smd[i][tid];
-            put_shared(&k_bits[((size_t)bh * G + part) * D + tid], tag_bits(a));
+            if (G == 1) {  // the head is this workgroup's alone: nobody to meet
+                const float mu = (float)(a / (double)N);
+                k_mean[(size_t)bh * D + tid] = mu;
+                stat[tid] = mu;
+            } else {
+                put_shared(&k_bits[((size_t)bh * G + part) * D + tid], tag_bits(a));
+            }
         }
         const long long t0 = wall_clock64();
-        bool there = resident_wait(k_bits + (size_t)bh * G * D, D, G, wait_ticks, t0);
-        if (there) {
-            // the G partial sums in index order, 256 / D threads per channel (eight loads in flight: each is a
+        bool there = G == 1 || resident_wait(k_bits + (size_t)bh * G * D, D, G, wait_ticks, t0);
+        if (there && G > 1) {
+            // the G partial sums in index order, NTHR / D threads per channel (eight loads in flight: each is a
             // round trip to memory); repeated in the rare case that a word of a partial lags behind its element 0
             const int c = tid % D, share = tid / D;
-            constexpr int SHARES = 256 / D;
+            constexpr int SHARES = NTHR / D;
             double s;
             for (;;) {
                 s = 0.0;
@@ -753,6 +762,8 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
             if ((tid & 63) == 0) wmax[tid >> 6][b] = a;
             __syncthreads();  // (every block has its own column of wmax: one barrier per block)
             a = fmaxf(fmaxf(wmax[0][b], wmax[1][b]), fmaxf(wmax[2][b], wmax[3][b]));
+#pragma unroll
+            for (int w = 4; w < NW; ++w) a = fmaxf(a, wmax[w][b]);
             const float rcp = a > 0.0f ? kRange / a : 0.0f;
             if (tid == 0) k_scale[(size_t)bh * nK + blk] = a / kRange;
 #pragma unroll
@@ -777,12 +788,15 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
             }
         }
     } else {
-        // ---- V: per 128-key tile a thread owns UPT units of 4 consecutive keys x 8 channels (quant_v_body) ----
-        constexpr int UPT = 32 * LPR / 256;
-        constexpr int TILES = C / kW;
-        static_assert(TILES * UPT * 4 == NU, "a workgroup's chunk is 16 uint4 per thread");
+        // ---- V: a thread owns four units of 4 consecutive keys x 8 channels (quant_v_body); the workgroup converts and
+        // transposes TP tiles at a time, UPT units per thread ----
+        constexpr int UNITS = 32 * LPR;  // per 128-key tile
+        constexpr int UPT = UNITS > NTHR ? UNITS / NTHR : 1, TP = UNITS > NTHR ? 1 : NTHR / UNITS;
+        constexpr int ROUNDS = C / kW / TP;
+        static_assert(ROUNDS * UPT * 4 == NU, "a workgroup's chunk is 16 uint4 per thread");
+        static_assert(TP * D * 128 <= NTHR * 64, "the tiles fit in LDS");
         const uint16_t *Vh = V + (bh / H) * v_st.b + (bh % H) * v_st.h;
-        // this thread's rows are row0 + (tid / LPR) * 4 + (kW / UPT) * (q >> 2) + (q & 3), q = 0 .. 15
+        // this thread's rows are row0 + rr * 4 + 4 * RP * (q >> 2) + (q & 3), q = 0 .. 15
         uint32_t exists = 0u;
         {
             const uint16_t *last = Vh + (int64_t)(N - 1) * v_st.n + co * 8;
@@ -790,7 +804,7 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
             const uint16_t *p = Vh + (int64_t)rbase * v_st.n + co * 8;
 #pragma unroll
             for (int q = 0; q < NU; ++q) {
-                const int dr = (kW / UPT) * (q >> 2) + (q & 3);
+                const int dr = 4 * RP * (q >> 2) + (q & 3);
                 const bool ok = rbase + dr < N;
                 exists |= (ok ? 1u : 0u) << q;
                 raw[q] = *reinterpret_cast<const uint4 *>(ok ? p + dr * v_st.n : last);
@@ -818,13 +832,18 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
         if (tid < D) {
             float a = smf[0][tid];
             for (int i = 1; i < RP; ++i) a = fmaxf(a, smf[i][tid]);
-            put_shared(&v_bits[((size_t)bh * G + part) * D + tid], tag_bits(a));
+            if (G == 1) {
+                v_scale[(size_t)bh * D + tid] = a / v_r;
+                stat[tid] = a > 0.0f ? v_r / a : 0.0f;
+            } else {
+                put_shared(&v_bits[((size_t)bh * G + part) * D + tid], tag_bits(a));
+            }
         }
         const long long t0 = wall_clock64();
-        bool there = resident_wait(v_bits + (size_t)bh * G * D, D, G, wait_ticks, t0);
-        if (there) {
+        bool there = G == 1 || resident_wait(v_bits + (size_t)bh * G * D, D, G, wait_ticks, t0);
+        if (there && G > 1) {
             const int c = tid % D, share = tid / D;
-            constexpr int SHARES = 256 / D;
+            constexpr int SHARES = NTHR / D;
             float a;
             for (;;) {
                 a = 0.0f;
@@ -886,23 +905,25 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j) rc[j] = stat[co * 8 + j];
         keep_packed(raw);
-        uint32_t *tile = reinterpret_cast<uint32_t *>(smem);  // D * 32 dwords
+        uint32_t *tile = reinterpret_cast<uint32_t *>(smem);  // TP tiles of D * 32 dwords
 #pragma unroll
-        for (int tl = 0; tl < TILES; ++tl) {
-            const int T = part * TILES + tl;  // (workgroup-uniform)
+        for (int rd = 0; rd < ROUNDS; ++rd) {
+            const int T = (part * ROUNDS + rd) * TP;  // (workgroup-uniform) first tile of the round
             if (T >= nT) break;
 #pragma unroll
             for (int k = 0; k < UPT; ++k) {
-                const int kq = (tid + 256 * k) / LPR;
+                const int u = tid + NTHR * k;
+                const int kq = (u % UNITS) / LPR;
                 const int t = kq >> 2, g = kq & 3;
+                uint32_t *my_tile = tile + (u / UNITS) * D * 32;
                 // two channels (one packed dword of each of the four keys) at a time; rows >= N hold zeros
 #pragma unroll
                 for (int j2 = 0; j2 < 4; ++j2) {
                     float y[4][2];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const uint4 &u = raw[(tl * UPT + k) * 4 + i];
-                        const uint32_t w16 = j2 == 0 ? u.x : j2 == 1 ? u.y : j2 == 2 ? u.z : u.w;
+                        const uint4 &x = raw[(rd * UPT + k) * 4 + i];
+                        const uint32_t w16 = j2 == 0 ? x.x : j2 == 1 ? x.y : j2 == 2 ? x.z : x.w;
                         y[i][0] = to_f32<BF16>(w16 & 0xffffu) * rc[2 * j2];
                         y[i][1] = to_f32<BF16>(w16 >> 16) * rc[2 * j2 + 1];
                     }
@@ -912,7 +933,7 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
                         int w = 0;
                         w = __builtin_amdgcn_cvt_pk_fp8_f32(y[0][e], y[1][e], w, false);
                         w = __builtin_amdgcn_cvt_pk_fp8_f32(y[2][e], y[3][e], w, true);
-                        tile[(co * 8 + j) * 32 + (t >> 2) * 16 + g * 4 + (t & 3)] = (uint32_t)w;
+                        my_tile[(co * 8 + j) * 32 + (t >> 2) * 16 + g * 4 + (t & 3)] = (uint32_t)w;
                     }
                 }
             }
@@ -920,11 +941,19 @@ __global__ __launch_bounds__(256, 4) void quant_kv_resident_kernel(
             uint4 *dst = reinterpret_cast<uint4 *>(Vt + ((size_t)bh * nT + T) * D * 128);
             const uint4 *src = reinterpret_cast<const uint4 *>(tile);
 #pragma unroll
-            for (int k = 0; k < D / 32; ++k) dst[tid + 256 * k] = src[tid + 256 * k];
+            for (int k = 0; k < TP * D * 8 / NTHR; ++k) {
+                const int e = tid + NTHR * k;
+                if (TP == 1 || T + e / (D * 8) < nT) dst[e] = src[e];
+            }
             __syncthreads();
         }
     }
 }
+
+// which path the K/V quantisers take (0: by shape) and how long a workgroup of the single-read kernel waits for its
+// partners (ticks of the 100 MHz clock; negative: not at all)
+std::atomic<int> g_kv_path{0};
+std::atomic<long long> g_kv_wait_ticks{kResidentWaitTicks};
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -936,9 +965,63 @@ hipError_t quant_q_impl(const uint16_t *q, Strides st, int8_t *q_i8, float *q_sc
     return hipGetLastError();
 }
 
+// Threads of the single-read kernel's workgroups; 0: three launches.  Every workgroup reads its group's G partials and is held
+// up by the slowest partner, so a group of many wants large workgroups: with 512 threads (half of G) against 256, K and V, us:
+// H 24, N 32768, d 128 (G 128 with 256 threads) 145 / 166, H 8, N 16000 (63) 27.6 / 28.4, d 64 N 60000, H 16 (118) 97 / 101.
+// With few partners two workgroups of 256 are the better neighbours of a CU: B 2, H 8, N 5000 (20) 25.1 / 23.1; B 4, H 32,
+// N 4096 (16) costs the whole forward 467 / 457.  A head that fits one workgroup of 512 threads has nobody to wait for and no
+// partials to clear: B 16, H 16, N 512 22.6 / 25.9.  Against three launches at 98 partners of 512 threads (H 8, N 50000, inputs
+// not in the last-level cache) 92 / 105.
+inline int resident_threads(int N, int d) {
+    const int path = g_kv_path.load();
+    if (path == 1) return 0;
+    const int G = resident_group_size(N, d, 256);
+    const int n = G > 48 || G == 2 ? 512 : 256;
+    if (path == 0 && resident_group_size(N, d, n) > kResidentMaxGroup) return 0;
+    return n;
+}
+
+// The outputs from one read of the tensors (quant_kv_resident_kernel).
+template <bool BF16, int D, int QMAX, int NTHR>
+hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v, Strides v_st, int8_t *k_i8, float *k_scale,
+                             float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H, int N,
+                             hipStream_t stream, const QuantScratch &ws, int tensors) {
+    const int G = resident_group_size(N, D, NTHR);
+    const int nK = cdiv(N, kBK), nT = cdiv(N, kW);
+    const long long wait_ticks = g_kv_wait_ticks.load();
+    if (G > 1) {
+        // the partial buffers, which lie back to back (each a multiple of 256 bytes)
+        char *from = reinterpret_cast<char *>(tensors == kOnlyV ? (void *)ws.v_max_part : (void *)ws.k_sum_part);
+        char *to = reinterpret_cast<char *>(tensors == kOnlyK ? (void *)ws.v_max_part : (void *)ws.v_rcp);
+        const int words = (int)((to - from) / 16);
+        zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(reinterpret_cast<uint4 *>(from), words);
+    }
+    const int groups = tensors == kBothTensors ? 2 * BH : BH;
+    quant_kv_resident_kernel<BF16, D, QMAX, NTHR><<<groups * G, NTHR, 0, stream>>>(
+        k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT, wait_ticks,
+        tensors);
+    return hipGetLastError();
+}
+
+template <bool BF16, int D, int QMAX>
+hipError_t launch_resident(int threads, const uint16_t *k, Strides k_st, const uint16_t *v, Strides v_st, int8_t *k_i8,
+                           float *k_scale, float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H, int N,
+                           hipStream_t stream, const QuantScratch &ws, int tensors) {
+    if (resident_group_size(N, D, 256) > kResidentHardMaxGroup) return hipErrorInvalidValue;
+    if (threads == 512)
+        return launch_resident_n<BF16, D, QMAX, 512>(k, k_st, v, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N,
+                                                     stream, ws, tensors);
+    return launch_resident_n<BF16, D, QMAX, 256>(k, k_st, v, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, stream,
+                                                 ws, tensors);
+}
+
 template <bool BF16, int D>
 hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_scale, float *k_mean, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws) {
+    const int threads = resident_threads(N, D);
+    if (threads && resident_group_size(N, D, 256) <= kResidentHardMaxGroup)
+        return launch_resident<BF16, D, 127>(threads, k, st, nullptr, st, k_i8, k_scale, k_mean, nullptr, nullptr, 0.0f, BH, H, N,
+                                             stream, ws, kOnlyK);
     const int chunks = cdiv(N, kStatRows);
     const int nK = cdiv(N, kBK);
     colstats_kernel<BF16, D, false><<<dim3(chunks, BH), 256, 0, stream>>>(k, st, H, N, chunks, ws.k_sum_part, nullptr);
@@ -951,6 +1034,10 @@ hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_sc
 template <bool BF16, int D>
 hipError_t quant_v_impl(const uint16_t *v, Strides st, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws) {
+    const int threads = resident_threads(N, D);
+    if (threads && resident_group_size(N, D, 256) <= kResidentHardMaxGroup)
+        return launch_resident<BF16, D, 127>(threads, nullptr, st, v, st, nullptr, nullptr, nullptr, v_fp8, v_scale, v_r, BH, H, N,
+                                             stream, ws, kOnlyV);
     const int chunks = cdiv(N, kStatRows);
     const int nT = cdiv(N, kW);
     colstats_kernel<BF16, D, true><<<dim3(chunks, BH), 256, 0, stream>>>(v, st, H, N, chunks, nullptr, ws.v_max_part);
@@ -975,24 +1062,6 @@ hipError_t quant_kv_impl(const uint16_t *k, Strides k_st, const uint16_t *v, Str
     return hipGetLastError();
 }
 
-// The same outputs from one read of K and V (quant_kv_resident_kernel); the caller has checked that the
-// group size fits.
-template <bool BF16, int D, int QMAX>
-hipError_t quant_kv_resident_impl(const uint16_t *k, Strides k_st, const uint16_t *v, Strides v_st, int8_t *k_i8,
-                                  float *k_scale, float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int BH,
-                                  int H, int N, hipStream_t stream, const QuantScratch &ws, long long wait_ticks) {
-    const int G = resident_group_size(N, D);
-    const int nK = cdiv(N, kBK), nT = cdiv(N, kW);
-    // both partial buffers, which lie back to back (each a multiple of 256 bytes)
-    const size_t span = reinterpret_cast<char *>(ws.v_rcp) - reinterpret_cast<char *>(ws.k_sum_part);
-    const int words = (int)(span / 16);
-    zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(reinterpret_cast<uint4 *>(ws.k_sum_part), words);
-    quant_kv_resident_kernel<BF16, D, QMAX><<<BH * 2 * G, 256, 0, stream>>>(
-        k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, k_mean, v_scale, v_r, k_i8, k_scale,
-        nK, v_fp8, nT, wait_ticks);
-    return hipGetLastError();
-}
-
 // 4+8 variant, Q side: block means, and (stand-alone) the INT4 codes of Q minus its block means
 template <bool BF16, int D>
 hipError_t q4_impl(const uint16_t *q, Strides st, float *q_mean, int8_t *q_i4, float *q_scale, int BH, int H, int N,
@@ -1006,11 +1075,6 @@ hipError_t q4_impl(const uint16_t *q, Strides st, float *q_mean, int8_t *q_i4, f
 
 }  // namespace
 
-// which path launch_quant_kv takes (0: by shape) and how long a workgroup of the single-read kernel waits for its
-// partners (ticks of the 100 MHz clock; negative: not at all)
-std::atomic<int> g_kv_path{0};
-std::atomic<long long> g_kv_wait_ticks{kResidentWaitTicks};
-
 void set_quant_kv_path(int path, long long wait_ticks) {
     g_kv_path.store(path);
     g_kv_wait_ticks.store(wait_ticks);
@@ -1019,7 +1083,7 @@ void set_quant_kv_path(int path, long long wait_ticks) {
 QuantScratch quant_scratch_layout(void *base, int B, int H, int N, int d) {
     const size_t BH = (size_t)B * H;
     // partial statistics: one per kStatRows tokens (three-launch path) or per resident chunk (single-read path)
-    const size_t chunks = (size_t)std::max(cdiv(N, kStatRows), resident_group_size(N, d));
+    const size_t chunks = (size_t)std::max(cdiv(N, kStatRows), resident_group_size(N, d, 256));
     char *p = static_cast<char *>(base);
     QuantScratch ws;
     size_t off = 0;
@@ -1072,14 +1136,11 @@ hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v
                            bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4) {
     const uint16_t *k16 = static_cast<const uint16_t *>(k), *v16 = static_cast<const uint16_t *>(v);
     const int BH = B * H;
-    const int path = g_kv_path.load();
-    const bool resident = path == 2 || (path == 0 && resident_group_size(N, d) <= kResidentMaxGroup);
-    if (resident && resident_group_size(N, d) > kResidentHardMaxGroup) return hipErrorInvalidValue;
-    const long long wait_ticks = g_kv_wait_ticks.load();
+    const int threads = resident_threads(N, d);
 #define SAGE_KV(BF, DD, QM)                                                                                           \
-    (resident ? quant_kv_resident_impl<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, \
-                                                   BH, H, N, stream, ws, wait_ticks)                                 \
-              : quant_kv_impl<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, \
+    (threads ? launch_resident<BF, DD, QM>(threads, k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, \
+                                           BH, H, N, stream, ws, kBothTensors)                                       \
+             : quant_kv_impl<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, \
                                           stream, ws))
     if (int4) {
         if (d == 128) return bf16 ? SAGE_KV(true, 128, 7) : SAGE_KV(false, 128, 7);

@@ -1,0 +1,36 @@
+"""The single-read quantiser at the token counts where its launch changes form: a head that fits one workgroup (of 256 or 512
+threads: nothing is exchanged), groups of 256-thread workgroups, and from 48 of those on groups of 512 threads; K and V together
+and each alone.  Every form writes the bits of the three launches, also where a workgroup does not wait for its partners."""
+import pytest
+import torch
+
+import paper_2505_21136_amd as sage
+from gpu_util import say
+from test_gpu_quant_paths import SINGLE_READ, THREE_LAUNCHES, _inputs, _quant, _restore_default_path, _same_bits  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _alone(k, v, path, wait_ticks=50_000):
+    sage.diag_quant_kv_path(path, wait_ticks)
+    out = sage.sage_quant_k(k) + sage.sage_quant_v(v, 4.5)
+    torch.cuda.synchronize()
+    return out
+
+
+# tokens of a 256-thread workgroup: 256 at d = 128, 512 at d = 64
+SHAPES = [(1, (1, 2, 256, 128)), (1, (2, 2, 257, 128)), (2, (1, 2, 512, 128)), (2, (1, 2, 513, 128)), (1, (1, 1, 12288, 128)),
+          (5, (1, 2, 12289, 128)), (5, (1, 1, 13001, 128)), (4, (1, 2, 512, 64)), (3, (2, 3, 777, 64)), (3, (1, 2, 1024, 64)),
+          (4, (1, 2, 1025, 64)), (4, (1, 1, 24576, 64)), (3, (1, 2, 24577, 64)), (4, (1, 1, 25601, 64))]
+
+
+@pytest.mark.parametrize("wait_ticks", [50_000, -1])
+@pytest.mark.parametrize("idx,shape", SHAPES)
+def test_every_width_writes_the_bits_of_the_three_launches(idx, shape, wait_ticks):
+    say(f"[quant widths] cfg{idx} distributions, shape {shape}, wait {wait_ticks}")
+    k, v = _inputs(idx, shape)
+    want = _quant(k, v, 4.5, THREE_LAUNCHES)
+    _same_bits(want, _quant(k, v, 4.5, SINGLE_READ, wait_ticks), "K and V together")
+    _same_bits(want, _alone(k, v, THREE_LAUNCHES), "each alone, three launches")
+    _same_bits(want, _alone(k, v, SINGLE_READ, wait_ticks), "each alone, single read")
+    _same_bits(want, _quant(k, v, 4.5, 0, wait_ticks), "by shape")
