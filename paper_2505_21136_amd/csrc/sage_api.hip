@@ -226,9 +226,11 @@ int sage_quant_qk(const void *q, const void *k, int8_t *q_i8, int8_t *k_i8, floa
     if (!aligned16(q) || !aligned16(k) || !aligned16(q_i8) || !aligned16(k_i8)) return SAGE_EINVAL;
     if (!workspace || !aligned256(workspace) || workspace_bytes < sage_quant_workspace_bytes(B, H, N, d))
         return SAGE_EWORKSPACE;
-    const int rc = sage_quant_k(k, k_i8, k_scale, k_mean, B, H, N, d, dt, stream, workspace, workspace_bytes);
-    if (rc != SAGE_OK) return rc;
-    return sage_quant_q(q, q_i8, q_scale, B, H, N, d, dt, stream);
+    const sage::QuantScratch ws = sage::quant_scratch_layout(workspace, B, H, N, d);
+    const sage::Strides st = sage::contiguous_bhnd(H, N, d);
+    discard_pending_hip_error();
+    return from_hip(sage::launch_quant_k(k, st, k_i8, k_scale, k_mean, B, H, N, d, dt == SAGE_BF16,
+                                         static_cast<hipStream_t>(stream), ws, q, st, q_i8, q_scale));
 }
 
 int sage_quant_v(const void *v, uint8_t *v_fp8, float *v_scale, float v_r, int B, int H, int N, int d,

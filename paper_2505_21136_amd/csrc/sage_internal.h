@@ -35,21 +35,22 @@ struct QuantScratch {
 QuantScratch quant_scratch_layout(void *base, int B, int H, int N, int d);
 
 // stage 1 launches (sage_quant.hip)
-// (the inputs are read through their strides; every output is contiguous [B,H,...])
+// (the inputs are read through their strides; every output is contiguous [B,H,...]; launch_quant_k takes Q of K's shape along)
 hipError_t launch_quant_q(const void *q, Strides q_st, int8_t *q_i8, float *q_scale, int B, int H, int N, int d,
                           bool bf16, hipStream_t stream);
 hipError_t launch_quant_k(const void *k, Strides k_st, int8_t *k_i8, float *k_scale, float *k_mean, int B, int H,
-                          int N, int d, bool bf16, hipStream_t stream, const QuantScratch &ws);
+                          int N, int d, bool bf16, hipStream_t stream, const QuantScratch &ws, const void *q = nullptr,
+                          Strides q_st = Strides{}, int8_t *q_i8 = nullptr, float *q_scale = nullptr);
 hipError_t launch_quant_v(const void *v, Strides v_st, uint8_t *v_fp8, float *v_scale, float v_r, int B, int H, int N,
                           int d, bool bf16, hipStream_t stream, const QuantScratch &ws);
 
-// K and V of the same shape together: three launches instead of six, identical results
+// K and V of the same shape together, identical results
 // (int4: the K codes of the 4+8 variant, range [-7, 7], one per byte)
 hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v_st, int8_t *k_i8, float *k_scale,
                            float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int B, int H, int N, int d,
                            bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4 = false);
 
-// Which kernels launch_quant_kv uses: 0 = by shape (the single-read kernel up to 128 workgroups per head),
+// Which kernels the K/V quantisers use: 0 = by shape (the single-read kernel up to 128 workgroups per head),
 // 1 = always the three launches (statistics, finalize, codes), 2 = always the single-read kernel (error above 256
 // workgroups per head).  wait_ticks: how long a workgroup of the single-read kernel waits for its partners before
 // it computes the head's statistic alone (100 MHz ticks; negative: no wait).  Process-wide.

@@ -199,20 +199,20 @@ __global__ __launch_bounds__(1024) void finalize_kv_kernel(const double *__restr
 // QMAX = 127: INT8 codes; QMAX = 7: the INT4 codes of the 4+8 variant (one per
 // byte).  SMOOTH = 0: no mean is subtracted; 1: `mean` holds one vector per
 // head (K smoothing, Sec. 3); 2: one vector per head and block (Q smoothing of
-// the 4+8 variant).  256 threads; wmax: four floats of LDS.
+// the 4+8 variant).  256 threads, numbered by tid, each workgroup's teams in step; wmax: four floats of LDS per team.
 // ---------------------------------------------------------------------------
 template <bool BF16, int D, int BLOCK, int SMOOTH, int QMAX>
 __device__ __forceinline__ void quant_int8_body(const uint16_t *__restrict__ X, Strides st, int H,
                                                 const float *__restrict__ mean, int8_t *__restrict__ codes,
                                                 float *__restrict__ scale, int N, int nblk, float *wmax, int bh,
-                                                int blk) {
+                                                int blk, int tid) {
     constexpr int LPR = D / 8;
     constexpr int RP = 256 / LPR;
     constexpr int ITER = BLOCK / RP;
     constexpr float kRange = (float)QMAX;
     static_assert(BLOCK % RP == 0, "block must be a multiple of the rows covered per pass");
 
-    const int co = threadIdx.x % LPR, rr = threadIdx.x / LPR;
+    const int co = tid % LPR, rr = tid / LPR;
     const uint16_t *Xh = X + (bh / H) * st.b + (bh % H) * st.h;
 
     float mu[8];
@@ -240,11 +240,11 @@ __device__ __forceinline__ void quant_int8_body(const uint16_t *__restrict__ X, 
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = amax;
+    if ((tid & 63) == 0) wmax[tid >> 6] = amax;
     __syncthreads();
     const float a = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
     const float rcp = a > 0.0f ? kRange / a : 0.0f;
-    if (threadIdx.x == 0) scale[(size_t)bh * nblk + blk] = a / kRange;
+    if (tid == 0 && blk < nblk) scale[(size_t)bh * nblk + blk] = a / kRange;
 
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
@@ -480,7 +480,8 @@ __global__ __launch_bounds__(256) void quant_int8_kernel(const uint16_t *__restr
                                                          const float *__restrict__ mean, int8_t *__restrict__ codes,
                                                          float *__restrict__ scale, int N, int nblk) {
     __shared__ float wmax[4];
-    quant_int8_body<BF16, D, BLOCK, SMOOTH, QMAX>(X, st, H, mean, codes, scale, N, nblk, wmax, blockIdx.y, blockIdx.x);
+    quant_int8_body<BF16, D, BLOCK, SMOOTH, QMAX>(X, st, H, mean, codes, scale, N, nblk, wmax, blockIdx.y, blockIdx.x,
+                                                threadIdx.x);
 }
 
 // grid (tiles, B*H)
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(256) void quant_kv_kernel(const uint16_t *__restric
     const int x = blockIdx.x;  // (workgroup-uniform branch)
     if (x < nK)
         quant_int8_body<BF16, D, kBK, 1, QMAX>(K, k_st, H, mean, k_codes, k_scale, N, nK,
-                                               reinterpret_cast<float *>(tile), blockIdx.y, x);
+                                               reinterpret_cast<float *>(tile), blockIdx.y, x, threadIdx.x);
     else
         quant_v_body<BF16, D>(V, v_st, H, v_rcp, Vt, N, nT, tile, blockIdx.y, x - nK);
 }
@@ -535,6 +536,14 @@ __global__ __launch_bounds__(256) void quant_kv_kernel(const uint16_t *__restric
 // ---------------------------------------------------------------------------
 // tokens of a workgroup of n threads: 16 uint4 of 8 elements per thread
 constexpr int resident_tokens(int threads, int d) { return threads * 128 / d; }
+// Q side of a launch that also quantises Q (quant_kv_resident_kernel<..., WITH_Q>): first = workgroups of the K side
+struct QuantQ {
+    const uint16_t *x;
+    Strides st;
+    int8_t *codes;
+    float *scale;
+    int n_blocks, first;
+};
 constexpr int kBothTensors = 0, kOnlyK = 1, kOnlyV = 2;  // what a launch quantises (both: K and V groups in turn)
 constexpr int kResidentMaxGroup = 128;       // largest group the shape-based choice takes (resident_threads)
 constexpr int kResidentHardMaxGroup = 256;   // largest group a forced choice may take (thread t polls partner t)
@@ -595,12 +604,14 @@ __device__ __forceinline__ bool resident_wait(const W *rows, int d, int G, long 
     }
 }
 
-template <bool BF16, int D, int QMAX, int NTHR>
+// WITH_Q (K alone): workgroups beyond the groups' quantise NTHR / 256 Q blocks each (no smoothing), which need nobody and fill the
+// time the others wait (the separate stages at B 16, H 16, N 777, d 64: 89.8 -> 87.9 us against a launch of their own).
+template <bool BF16, int D, int QMAX, int NTHR, bool WITH_Q>
 __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
     const uint16_t *__restrict__ K, Strides k_st, const uint16_t *__restrict__ V, Strides v_st, int H, int N, int G,
     double *k_sum_part, float *v_max_part, float *k_mean, float *v_scale, float v_r,
     int8_t *__restrict__ k_codes, float *__restrict__ k_scale, int nK, uint8_t *__restrict__ Vt, int nT,
-    long long wait_ticks, int tensors) {
+    long long wait_ticks, int tensors, QuantQ q) {
     constexpr int NU = 16;                       // uint4 per thread
     constexpr int NW = NTHR / 64;                // wavefronts
     constexpr int LPR = D / 8;                   // lanes per row
@@ -611,6 +622,16 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
     __shared__ float stat[D];           // the head's mean (K) or V_r / max (V)
     __shared__ float wmax[NW][C / kBK];  // per wavefront and K block: max |K'|
 
+    if constexpr (WITH_Q) {
+        if ((int)blockIdx.x >= q.first) {
+            constexpr int TEAMS = NTHR / 256;
+            const int team = threadIdx.x >> 8, wgs = (q.n_blocks + TEAMS - 1) / TEAMS;
+            const int x = blockIdx.x - q.first;
+            quant_int8_body<BF16, D, kBQ, 0, 127>(q.x, q.st, H, nullptr, q.codes, q.scale, N, q.n_blocks, &wmax[0][0] + 4 * team,
+                                                  x / wgs, x % wgs * TEAMS + team, threadIdx.x & 255);
+            return;
+        }
+    }
     const int grp = blockIdx.x / G, part = blockIdx.x % G;
     const int bh = tensors == kBothTensors ? grp >> 1 : grp;
     const bool is_v = tensors == kBothTensors ? grp & 1 : tensors == kOnlyV;  // (workgroup-uniform)
@@ -985,7 +1006,7 @@ inline int resident_threads(int N, int d) {
 template <bool BF16, int D, int QMAX, int NTHR>
 hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v, Strides v_st, int8_t *k_i8, float *k_scale,
                              float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H, int N,
-                             hipStream_t stream, const QuantScratch &ws, int tensors) {
+                             hipStream_t stream, const QuantScratch &ws, int tensors, QuantQ q) {
     const int G = resident_group_size(N, D, NTHR);
     const int nK = cdiv(N, kBK), nT = cdiv(N, kW);
     const long long wait_ticks = g_kv_wait_ticks.load();
@@ -996,39 +1017,50 @@ hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v,
         const int words = (int)((to - from) / 16);
         zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(reinterpret_cast<uint4 *>(from), words);
     }
-    const int groups = tensors == kBothTensors ? 2 * BH : BH;
-    quant_kv_resident_kernel<BF16, D, QMAX, NTHR><<<groups * G, NTHR, 0, stream>>>(
-        k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT, wait_ticks,
-        tensors);
+    q.first = (tensors == kBothTensors ? 2 * BH : BH) * G;
+#define SAGE_RESIDENT(Q, GRID)                                                                                          \
+    quant_kv_resident_kernel<BF16, D, QMAX, NTHR, Q><<<GRID, NTHR, 0, stream>>>(                                        \
+        k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT,     \
+        wait_ticks, tensors, q)
+    if constexpr (QMAX == 127) {
+        if (q.x) {
+            SAGE_RESIDENT(true, q.first + BH * cdiv(q.n_blocks, NTHR / 256));
+            return hipGetLastError();
+        }
+    }
+    SAGE_RESIDENT(false, q.first);
+#undef SAGE_RESIDENT
     return hipGetLastError();
 }
 
 template <bool BF16, int D, int QMAX>
 hipError_t launch_resident(int threads, const uint16_t *k, Strides k_st, const uint16_t *v, Strides v_st, int8_t *k_i8,
                            float *k_scale, float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H, int N,
-                           hipStream_t stream, const QuantScratch &ws, int tensors) {
+                           hipStream_t stream, const QuantScratch &ws, int tensors, const QuantQ &q = QuantQ{}) {
     if (resident_group_size(N, D, 256) > kResidentHardMaxGroup) return hipErrorInvalidValue;
     if (threads == 512)
         return launch_resident_n<BF16, D, QMAX, 512>(k, k_st, v, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N,
-                                                     stream, ws, tensors);
+                                                     stream, ws, tensors, q);
     return launch_resident_n<BF16, D, QMAX, 256>(k, k_st, v, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, stream,
-                                                 ws, tensors);
+                                                 ws, tensors, q);
 }
 
+// K and, with `q`, Q of the same shape: their codes in K's launch or, where K takes the three launches, in one of their own.
 template <bool BF16, int D>
 hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_scale, float *k_mean, int BH, int H,
-                        int N, hipStream_t stream, const QuantScratch &ws) {
+                        int N, hipStream_t stream, const QuantScratch &ws, const QuantQ &q) {
     const int threads = resident_threads(N, D);
     if (threads && resident_group_size(N, D, 256) <= kResidentHardMaxGroup)
         return launch_resident<BF16, D, 127>(threads, k, st, nullptr, st, k_i8, k_scale, k_mean, nullptr, nullptr, 0.0f, BH, H, N,
-                                             stream, ws, kOnlyK);
+                                             stream, ws, kOnlyK, q);
     const int chunks = cdiv(N, kStatRows);
     const int nK = cdiv(N, kBK);
     colstats_kernel<BF16, D, false><<<dim3(chunks, BH), 256, 0, stream>>>(k, st, H, N, chunks, ws.k_sum_part, nullptr);
     finalize_mean_kernel<<<BH, 1024, 0, stream>>>(ws.k_sum_part, chunks, N, D, k_mean);
     // K right after its statistics pass: its second read can still be served by the last-level cache
     quant_int8_kernel<BF16, D, kBK, 1, 127><<<dim3(nK, BH), 256, 0, stream>>>(k, st, H, k_mean, k_i8, k_scale, N, nK);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || !q.x ? e : quant_q_impl<BF16, D>(q.x, q.st, q.codes, q.scale, BH, H, N, stream);
 }
 
 template <bool BF16, int D>
@@ -1109,14 +1141,16 @@ hipError_t launch_quant_q(const void *q, Strides st, int8_t *q_i8, float *q_scal
 }
 
 hipError_t launch_quant_k(const void *k, Strides st, int8_t *k_i8, float *k_scale, float *k_mean, int B, int H,
-                          int N, int d, bool bf16, hipStream_t stream, const QuantScratch &ws) {
+                          int N, int d, bool bf16, hipStream_t stream, const QuantScratch &ws, const void *q, Strides q_st,
+                          int8_t *q_i8, float *q_scale) {
     const uint16_t *k16 = static_cast<const uint16_t *>(k);
     const int BH = B * H;
+    const QuantQ qq{static_cast<const uint16_t *>(q), q_st, q_i8, q_scale, cdiv(N, kBQ), 0};
     if (d == 128)
-        return bf16 ? quant_k_impl<true, 128>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws)
-                    : quant_k_impl<false, 128>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws);
-    return bf16 ? quant_k_impl<true, 64>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws)
-                : quant_k_impl<false, 64>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws);
+        return bf16 ? quant_k_impl<true, 128>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws, qq)
+                    : quant_k_impl<false, 128>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws, qq);
+    return bf16 ? quant_k_impl<true, 64>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws, qq)
+                : quant_k_impl<false, 64>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws, qq);
 }
 
 hipError_t launch_quant_v(const void *v, Strides st, uint8_t *v_fp8, float *v_scale, float v_r, int B, int H, int N,
