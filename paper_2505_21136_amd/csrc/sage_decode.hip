@@ -1,9 +1,9 @@
 // Decode-shaped attention on gfx950: a few query rows per head over a long key sequence (not treated in the
 // paper; the arithmetic of a key step is the 8+8 path's, Sec. 2.1 / Sec. 3.1, through the same softmax_step).
 //
-// The prefill kernel gives a workgroup 128 query rows of one head and shares every K^/V^ tile among its eight
-// wavefronts through LDS.  Here a head has at most a handful of rows, so that shape leaves 7 of 8 wavefronts
-// and 15 of 16 MFMA columns idle and B*Hq workgroups cannot fill 256 CUs.  Instead:
+// The kernels for many rows give a workgroup up to 128 query rows of one head and share every K^/V^ tile among its
+// wavefronts through LDS.  Here a head has at most a handful of rows, so that shape leaves most wavefronts
+// and MFMA columns idle and B*Hq workgroups cannot fill 256 CUs.  Instead:
 //   * the R = (Hq/Hkv) * Nq <= 64 query rows of all query heads that share one K/V head are packed into the 16
 //     columns of T = ceil(R/16) <= 4 MFMA tiles (exact: every row keeps its own scale, running maximum and sum), so
 //     K^ and V^ of a head leave HBM once for all of them (the T wavefronts of a range sit in one workgroup and
