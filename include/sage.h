@@ -378,7 +378,7 @@ int sage_diag_mfma_rate(int kind, int iters, int workgroups, float *sink, double
  *   path        0 (default): by shape — the single-read kernel (K and V are read once: the workgroups of a head
  *               keep 64 or 128 KiB of tokens each in registers, exchange their partial column statistics through
  *               the workspace and then write the codes) when a head is at most 128 workgroups of 128 KiB (65536
- *               tokens at d = 128, 131072 at d = 64), the three launches (statistics, finalize, codes; K and V read
+ *               tokens at d = 128, 131072 at d = 64, there with enough heads), the three launches (statistics, finalize, codes; K and V read
  *               twice) above that; 1: always the three launches; 2: always the single-read kernel (calls for K and V
  *               together then fail with SAGE_EHIP above 256 workgroups of 64 KiB per head)
  *   wait_ticks  how long a workgroup of the single-read kernel waits for the partials of its partners before it

@@ -993,13 +993,15 @@ hipError_t quant_q_impl(const uint16_t *q, Strides st, int8_t *q_i8, float *q_sc
 // N 4096 (16) costs the whole forward 467 / 457.  A head that fits one workgroup of 512 threads has nobody to wait for and no
 // partials to clear: B 16, H 16, N 512 22.6 / 25.9.  Against three launches at 98 partners of 512 threads (H 8, N 50000, inputs
 // not in the last-level cache) 92 / 105.
-inline int resident_threads(int N, int d) {
+// Where workgroups of 256 threads do not even fill the CUs once, fewer and larger ones lose: H 2, N 16000, d 128 14.8 /
+// 13.2 (the kernel alone), H 1, N 60000, d 64 18.9 / 15.2.  And at d = 64 the launch needs its two workgroups per CU to beat the three launches beyond the reach of 256 threads: H 2, N 70000 (276
+// workgroups) 25.3 / 22.5, N 100000 31.1 / 29.0, N 131072 (512) 33.5 / 36.1; H 8, N 70000 59.9 / 72.4.
+inline int resident_threads(int groups, int N, int d) {
     const int path = g_kv_path.load();
     if (path == 1) return 0;
-    const int G = resident_group_size(N, d, 256);
-    const int n = G > 48 || G == 2 ? 512 : 256;
-    if (path == 0 && resident_group_size(N, d, n) > kResidentMaxGroup) return 0;
-    return n;
+    const int G = resident_group_size(N, d, 256), G512 = resident_group_size(N, d, 512);
+    if (path == 0 && G > kResidentMaxGroup && (G512 > kResidentMaxGroup || (d == 64 && (long)groups * G512 < 2 * kCUs))) return 0;
+    return G == 2 || G > kResidentMaxGroup || (G > 48 && (long)groups * G > kCUs) ? 512 : 256;
 }
 
 // The outputs from one read of the tensors (quant_kv_resident_kernel).
@@ -1049,7 +1051,7 @@ hipError_t launch_resident(int threads, const uint16_t *k, Strides k_st, const u
 template <bool BF16, int D>
 hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_scale, float *k_mean, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws, const QuantQ &q) {
-    const int threads = resident_threads(N, D);
+    const int threads = resident_threads(BH, N, D);
     if (threads && resident_group_size(N, D, 256) <= kResidentHardMaxGroup)
         return launch_resident<BF16, D, 127>(threads, k, st, nullptr, st, k_i8, k_scale, k_mean, nullptr, nullptr, 0.0f, BH, H, N,
                                              stream, ws, kOnlyK, q);
@@ -1066,7 +1068,7 @@ hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_sc
 template <bool BF16, int D>
 hipError_t quant_v_impl(const uint16_t *v, Strides st, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws) {
-    const int threads = resident_threads(N, D);
+    const int threads = resident_threads(BH, N, D);
     if (threads && resident_group_size(N, D, 256) <= kResidentHardMaxGroup)
         return launch_resident<BF16, D, 127>(threads, nullptr, st, v, st, nullptr, nullptr, nullptr, v_fp8, v_scale, v_r, BH, H, N,
                                              stream, ws, kOnlyV);
@@ -1170,7 +1172,7 @@ hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v
                            bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4) {
     const uint16_t *k16 = static_cast<const uint16_t *>(k), *v16 = static_cast<const uint16_t *>(v);
     const int BH = B * H;
-    const int threads = resident_threads(N, d);
+    const int threads = resident_threads(2 * BH, N, d);
 #define SAGE_KV(BF, DD, QM)                                                                                           \
     (threads ? launch_resident<BF, DD, QM>(threads, k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, \
                                            BH, H, N, stream, ws, kBothTensors)                                       \

@@ -21,7 +21,9 @@ def _alone(k, v, path, wait_ticks=50_000):
 # tokens of a 256-thread workgroup: 256 at d = 128, 512 at d = 64
 SHAPES = [(1, (1, 2, 256, 128)), (1, (2, 2, 257, 128)), (2, (1, 2, 512, 128)), (2, (1, 2, 513, 128)), (1, (1, 1, 12288, 128)),
           (5, (1, 2, 12289, 128)), (5, (1, 1, 13001, 128)), (4, (1, 2, 512, 64)), (3, (2, 3, 777, 64)), (3, (1, 2, 1024, 64)),
-          (4, (1, 2, 1025, 64)), (4, (1, 1, 24576, 64)), (3, (1, 2, 24577, 64)), (4, (1, 1, 25601, 64))]
+          (4, (1, 2, 1025, 64)), (4, (1, 1, 24576, 64)), (3, (1, 2, 24577, 64)), (4, (1, 1, 25601, 64)),
+          # enough heads for the wide workgroups, K alone too
+          (5, (2, 3, 12289, 128)), (3, (1, 6, 24577, 64))]
 
 
 @pytest.mark.parametrize("wait_ticks", [50_000, -1])
