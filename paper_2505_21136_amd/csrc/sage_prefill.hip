@@ -253,7 +253,9 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
     cst_lds[wave][lane] = (float)((double)delta_q * (double)sm_scale * 1.4426950408889634 * (double)dk_first);
 
     // ---- state of the recurrence ----
-    float m = -INFINITY, l = 0.0f, alpha = 1.0f;
+    // (l is kept per key tile of a step, as the wavefronts of spread_kernel hold it, and every addition here has that kernel's
+    // order: a row's bits must not depend on which of the two the number of heads selects)
+    float m = -INFINITY, l[4] = {0.0f, 0.0f, 0.0f, 0.0f}, alpha = 1.0f;
     v16f o[CT];
     v16i s[4];
     v8i pb[2];
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
         alpha = __builtin_amdgcn_exp2f(m - m_new);
         return m_new;
     };
-    // P^ of the four keys 32t + 8b + 4h .. + 3, and their share of the row sum.  mo = log2 P_r - m.
+    // P^ of the four keys 32t + 8b + 4h .. + 3, and their share of the key tile's sum.  mo = log2 P_r - m.
     const auto exp_quad = [&](auto masked, int t, int b, float cb, float mo, float &lsum0, float &lsum1)
                               __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked)::value;
@@ -423,6 +425,10 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
             // P^V^ of the last 64 keys of step j-1 in the slots of the first two tiles (their registers are rewritten by the
             // last two)
             constexpr int EVERY = 8 / CT;
+            if ((sl & 3) == 3) {
+                l[sl >> 2] = __builtin_fmaf(l[sl >> 2], alpha, lsum0 + lsum1);
+                lsum0 = lsum1 = -0.0f;
+            }
             if (sl < 8 && sl % EVERY == EVERY - 1) {
                 const int r = CT + sl / EVERY;
                 mfma_pv(vf[r % VA], r);
@@ -441,7 +447,6 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
 #pragma unroll
         for (int n = NQK - KC; n < NQK; ++n) mfma_qk(kf[n % KA], n);
         static_assert(KA <= KC, "the last tile's operands are all read ahead");
-        l = l * alpha + (lsum0 + lsum1);
         m = m_new;
         if (((j + 1) & 31) == 0) park_constants(j + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -475,9 +480,12 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
             if (t < t_hi) max_tile(mask, t, lim, t < 2 ? cc.x : cc.y, ds_lds[j & 1], im, fm);
         const float m_new = new_max(mask, cc.x, cc.y, im, fm);
         const float mo = log2_pr - m_new;
-        float lsum0 = -0.0f, lsum1 = -0.0f;
+        // a row that has seen no key of this range yet and sees none in this step keeps its empty state (the step's arithmetic on
+        // (-inf) - (-inf) is undefined; its P^ is zero either way); without ranges every row sees key 0
+        if constexpr (SPLIT) alpha = blind && m == -INFINITY ? 1.0f : alpha;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
+            float lsum0 = -0.0f, lsum1 = -0.0f;
             if (t < t_hi) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) exp_quad(mask, t, b, t < 2 ? cc.x : cc.y, mo, lsum0, lsum1);
@@ -485,21 +493,12 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
 #pragma unroll
                 for (int b = 0; b < 4; ++b) pb[t >> 1][4 * (b & 1) + 2 * (t & 1) + (b >> 1)] = 0;
             }
+            l[t] = __builtin_fmaf(l[t], alpha, lsum0 + lsum1);
         }
         if (j + 1 < my_steps) {
 #pragma unroll
             for (int n = 0; n < 4 * KC; ++n) mfma_qk(read_k(par, n), n);
         }
-        float l_new = l * alpha + (lsum0 + lsum1);
-        if constexpr (SPLIT) {
-            // a row that has seen no key of this range yet and sees none in this step keeps its empty state (the step's
-            // arithmetic on (-inf) - (-inf) is undefined; its P^ is zero either way); without ranges every row sees key 0
-            if (blind && m == -INFINITY) {
-                alpha = 1.0f;
-                l_new = l;
-            }
-        }
-        l = l_new;
         m = m_new;
         if (((j + 1) & 31) == 0) park_constants(j + 1);
     };
@@ -539,7 +538,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
         arrive();
     }
 
-    const float lsum = halves_sum(l);
+    const float lsum = halves_sum((l[0] + l[1]) + (l[2] + l[3]));
     const int eln = lane_now(), eh = eln >> 5, erow = row0 + (eln & 31);
     if constexpr (SPLIT) {
         // ---- the range's (m, l, acc) of every valid row ----

@@ -5,8 +5,10 @@
 // 32x32 tile of S^T), so the chain that a row's recurrence is -- scores, maximum, exponentials, P^, the same again -- is a
 // quarter as long as where a wavefront scores all 128, and there are 4 / RG times as many workgroups.  The wavefronts of a row
 // group meet twice per step in what one barrier separates: the tile maxima of step j+1 and the P^ of step j go through LDS
-// together.  P^V^ is split by channels (d = 128: wavefront w makes channels 32w .. +31) or by channels and keys (d = 64: 32
-// channels, 64 keys each, added at the end).
+// together.  P^V^ is split by channels: d = 128: wavefront w makes channels 32w .. +31; at d = 64 there are only two such tiles,
+// made by two of the four wavefronts.  (Splitting the keys between all four instead, one MFMA each, is 4 % faster with 64 rows and
+// 1 % slower with 32, but adds up in another order.)  Every addition has the order of prefill_kernel: the result of a row does not
+// depend on which of the two kernels the number of heads selects.
 //
 // Two more wavefronts do nothing but copy: K^ and V^ tiles global -> LDS (ring of four steps), three steps ahead, so that
 // neither the latency of the memory nor the texture path's 16 cycles per 1 KB piece stands in the chain of the others.  (The
@@ -41,7 +43,7 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
     int group, float sm_scale, float log2_pr, int n_tiles) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int KC = D / 32;             // 32-wide contraction chunks of Q.K^T
-    constexpr int NPV = D == 128 ? 2 : 1;  // P^V^ MFMAs of a wavefront per step
+    constexpr int NPV = 2;                 // P^V^ MFMAs of a wavefront per step, one per 64 keys
     constexpr int TILE = 128 * D;          // bytes of one K^ (or V^) tile
     constexpr int ROWS = 32 * RG, NC = 4 * RG;  // query rows and scoring wavefronts of a workgroup
     __shared__ __attribute__((aligned(1024))) uint8_t lds[8 * TILE];  // K^ of steps j & 3, then V^
@@ -49,7 +51,7 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
     __shared__ __attribute__((aligned(16))) float max_lds[2][ROWS][4];     // per query and wavefront: maximum of the key tile
     __shared__ float cst_lds[2][64];  // de-quantisation constants of 64 consecutive K blocks (32 steps), even and odd strips
     __shared__ __attribute__((aligned(16))) float q_wave_max[NC];
-    __shared__ float l_lds[RG][4][32];
+    __shared__ float l_lds[RG][4][64];
     __shared__ __attribute__((aligned(16))) float dv_lds[D];  // delta_V of this head, for the epilogue
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -131,7 +133,6 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
             copy_v(j + 3);
         }
         lds_barrier();
-        if constexpr (D == 64) lds_barrier();
         return;
     }
 
@@ -141,7 +142,9 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
     // ---- Q: the wavefront's operand (those of a row group hold the same 32 rows) and, unquantised, the maximum of the block ----
     v4i qreg[KC];
     const int ct = D == 128 ? w4 : w4 & 1;
-    const auto chunk = [&](int n) { return D == 128 ? n : w4 >> 1; };  // 64-key chunk of the n-th P^V^ MFMA
+    // (d = 64: two wavefronts of a row group make one; the others multiply what is in their registers, which costs less than a
+    // branch inside the exponentials, and store nothing.  On different SIMDs for the two row groups, and not those of the copies.)
+    const bool pv = D == 128 || (w4 >> 1) != rg;
     if (tid < D / 4)
         *reinterpret_cast<float4 *>(dv_lds + 4 * tid) = *reinterpret_cast<const float4 *>(dv + (size_t)bhk * D + 4 * tid);
     const float dk0 = dkh[min(w4 >> 1, nKblk - 1)], dk1 = dkh[min(2 + (w4 >> 1), nKblk - 1)];
@@ -260,7 +263,8 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
     const double cq = (double)delta_q * (double)sm_scale * 1.4426950408889634;
     float c0 = (float)(cq * (double)dk0), c1 = (float)(cq * (double)dk1);  // constants of even and odd steps
     v16i s0 = scores(k0), s1 = scores(k1);                                 // scores of even and odd steps
-    v8i vf[NPV];  // V^ of the step before
+    const v8i none = {0, 0, 0, 0, 0, 0, 0, 0};
+    v8i vf[NPV] = {none, none}, pf[NPV] = {none, none};  // V^ and P^ of the step before
     {
         const float mx = tile_max(s0, 0, c0);
         if (h == 0) max_lds[0][rg * 32 + lq][w4] = mx;
@@ -271,10 +275,9 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
         constexpr int PAR = decltype(parity)::value;
         lds_barrier();
         const float4 mx = *reinterpret_cast<const float4 *>(max_lds[PAR][rg * 32 + lq]);
-        v8i pf[NPV];
-        if (j > 0) {
+        if (pv && j > 0) {
 #pragma unroll
-            for (int n = 0; n < NPV; ++n) pf[n] = operand(p_lds[PAR ^ 1], pof, chunk(n));
+            for (int n = 0; n < NPV; ++n) pf[n] = operand(p_lds[PAR ^ 1], pof, n);
         }
         const float c_after = cst_lds[((j + 2) >> 5) & 1][(2 * (j + 2) + (w4 >> 1)) & 63];
         const float mx_next = tile_max(s_next, j + 1, c_next);
@@ -307,8 +310,10 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
             if (b == 1) read_k(kf, j + 3);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (pv) {
 #pragma unroll
-        for (int n = 0; n < NPV; ++n) vf[n] = operand(lds + (j & 3) * TILE, vof, chunk(n));
+            for (int n = 0; n < NPV; ++n) vf[n] = operand(lds + (j & 3) * TILE, vof, n);
+        }
         if (needs_mask(j)) {
             const int lim = limit(j);
 #pragma unroll
@@ -327,10 +332,13 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
         if (h == 0) max_lds[PAR ^ 1][rg * 32 + lq][w4] = mx_next;
         __builtin_amdgcn_sched_barrier(0);
         alpha = __builtin_amdgcn_exp2f(m - m_new);
-        float lsum[4];
+        float lsum0 = x[0] + x[1], lsum1 = x[2] + x[3];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) lsum[b] = (x[4 * b] + x[4 * b + 1]) + (x[4 * b + 2] + x[4 * b + 3]);
-        l = l * alpha + ((lsum[0] + lsum[1]) + (lsum[2] + lsum[3]));
+        for (int b = 1; b < 4; ++b) {
+            lsum0 += x[4 * b] + x[4 * b + 1];
+            lsum1 += x[4 * b + 2] + x[4 * b + 3];
+        }
+        l = __builtin_fmaf(l, alpha, lsum0 + lsum1);
         m = m_new;
         c = c_after;
     };
@@ -338,27 +346,16 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
         step(std::integral_constant<int, 0>{}, j, s0, c0, s1, c1);
         if (j + 1 < nsteps) step(std::integral_constant<int, 1>{}, j + 1, s1, c1, s0, c0);
     }
-    const float lw = halves_sum(l);
-    if (h == 0) l_lds[rg][w4][lq] = lw;
+    l_lds[rg][w4][lane] = l;
     lds_barrier();  // P^ of the last step and the row sums
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) o *= alpha;
 #pragma unroll
     for (int n = 0; n < NPV; ++n)
-        o = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[n], operand(p_lds[(nsteps - 1) & 1], pof, chunk(n)), o, 0, 0, 0,
+        o = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[n], operand(p_lds[(nsteps - 1) & 1], pof, n), o, 0, 0, 0,
                                                             0, 0, 0);
-    const float inv = 1.0f / ((l_lds[rg][0][lq] + l_lds[rg][1][lq]) + (l_lds[rg][2][lq] + l_lds[rg][3][lq]));
-    if constexpr (D == 64) {
-        // the two key halves of a channel tile: through the K^ ring, which nobody reads any more (RG * 2 * 4 KB)
-        float *x = reinterpret_cast<float *>(lds) + ((rg * 2 + (w4 & 1)) * 16) * 64 + lane;
-        if (w4 >= 2) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) x[i * 64] = o[i];
-        }
-        lds_barrier();
-        if (w4 >= 2) return;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[i] += x[i * 64];
-    }
+    const float inv =
+        1.0f / halves_sum((l_lds[rg][0][lane] + l_lds[rg][1][lane]) + (l_lds[rg][2][lane] + l_lds[rg][3][lane]));
+    if (!pv) return;
     // ---- epilogue: O = acc * delta_V / (P_r * l); l already carries the factor P_r ----
     uint16_t *orow = out + (bh / Hq) * o_st.b + (bh % Hq) * o_st.h + qrow * o_st.n + 32 * ct;
 #pragma unroll
