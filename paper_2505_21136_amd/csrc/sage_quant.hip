@@ -307,14 +307,16 @@ __global__ __launch_bounds__(256) void block_mean_kernel(const uint16_t *__restr
 // (Q block, query head) pairs of a K/V head's group the columns, 32 of each per wavefront.  A lane keeps half a K' row (its
 // key's channels D/2 * h ..) and half a mean row in registers.  A workgroup of 4 wavefronts takes one 128-key tile and
 // `tiles` column tiles.  Columns are numbered Q block major, so that what a causal launch does not need (the Q blocks that
-// see no key of the tile) is a prefix that is skipped.  With 64 dependent MFMAs of 64 cycles per wavefront and tile it is the
-// latency in front of them that counts: keys, means and K mean are fetched together.  Measured (B 2, 32 / 8 heads, N 3000,
-// d 128, causal / full): 122 us with one key per thread and the means broadcast from LDS (one LDS read per four FMAs);
-// 23.8 / 35.7 us with the K mean read behind the mask of the last keys, pair by pair, and the means piece by piece; now
-// 16.0 / 20.2 us.
+// see no key of the tile) is a prefix that is skipped.  With D / 2 MFMAs of 64 cycles per wavefront and tile it is the
+// latency in front of them that counts, with few workgroups: keys, means and K mean are fetched together.  The 64 accumulators of
+// the four sums leave three wavefronts per SIMD (d = 64: four; one less costs 2 us with few columns, gains 2 us with 32 and more).
+// Measured (B 2, 32 / 8 heads, N 3000, d 128, causal / full): 122 us with one key per thread and the means broadcast from LDS (one
+// LDS read per four FMAs); 23.8 / 35.7 us with the K mean read behind the mask of the last keys, pair by pair, and the means piece
+// by piece; 16.0 / 20.2 us with everything fetched together and one sum; about 1 us more with four.  One key per thread is the
+// faster only with one Q block, ungrouped heads and 1000 to 2000 key tiles (B 2, H 32, Nk 4096, d 64: 11.8 / 14.8 us).
 // ---------------------------------------------------------------------------
 template <bool BF16, int D>
-__global__ __launch_bounds__(256) void delta_s_kernel(const uint16_t *__restrict__ K, Strides k_st, int Hkv,
+__global__ __launch_bounds__(256, D == 128 ? 3 : 4) void delta_s_kernel(const uint16_t *__restrict__ K, Strides k_st, int Hkv,
                                                       const float *__restrict__ k_mean,
                                                       const float *__restrict__ q_mean, float *__restrict__ dsx,
                                                       int Hq, int Nq, int Nk, int nQ, int nT, float sm_log2e,
@@ -394,15 +396,19 @@ __global__ __launch_bounds__(256) void delta_s_kernel(const uint16_t *__restrict
         }
         int i, bhq;
         column(col0 + lq, i, bhq);
-        v16f acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        // four sums over the channels of one residue modulo 4, added at the end: with one chain over all of them the error against
+        // 64 bits is 1.8 times as large (2-norm, d = 128: 2.06e-7 of the result against 1.15e-7)
+        const v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        v16f part[4] = {zero, zero, zero, zero};
 #pragma unroll
         for (int c4 = 0; c4 < HALF / 4; ++c4) {
             const float4 v = *reinterpret_cast<const float4 *>(&qm[lq][h * HALF + 4 * c4]);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4], v.x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 1], v.y, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 2], v.z, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 3], v.w, acc, 0, 0, 0);
+            part[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4], v.x, part[0], 0, 0, 0);
+            part[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 1], v.y, part[1], 0, 0, 0);
+            part[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 2], v.z, part[2], 0, 0, 0);
+            part[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[4 * c4 + 3], v.w, part[3], 0, 0, 0);
         }
+        v16f acc = (part[0] + part[1]) + (part[2] + part[3]);
         if (T * 128 + 127 >= Nk) {  // (workgroup-uniform) keys beyond the last hold zeros
 #pragma unroll
             for (int e = 0; e < 16; ++e)
