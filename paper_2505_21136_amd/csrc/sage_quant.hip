@@ -1213,7 +1213,8 @@ hipError_t launch_delta_s(const void *k, Strides k_st, const float *k_mean, cons
     // a workgroup keeps its keys for up to four column tiles when that leaves enough workgroups (about eight per CU)
     const int col_tiles = cdiv(nQ * (Hq / Hkv), 32);
     const long wgs = (long)nT * B * Hkv * col_tiles;
-    const int tiles = (int)std::min<long>(4, std::max<long>(1, wgs / 2048));
+    // -- and for more where the grid's third dimension would exceed its limit of 65535 otherwise
+    const int tiles = std::max((int)std::min<long>(4, std::max<long>(1, wgs / 2048)), cdiv(col_tiles, 65535));
     const dim3 grid(nT, B * Hkv, cdiv(col_tiles, tiles));
 #define SAGE_DS(BF, DD) \
     delta_s_kernel<BF, DD><<<grid, 256, 0, stream>>>(k16, k_st, Hkv, k_mean, q_mean, dsx, Hq, Nq, Nk, nQ, nT, sm_log2e, \

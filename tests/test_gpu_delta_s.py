@@ -39,3 +39,24 @@ def test_error_against_64_bits(Hq, Hkv, Nq, Nk, d):
     bound = 2.0**-24 * math.sqrt(d / 24 + 1.0)
     say(f"   {err:.3e}, bound {bound:.3e}")
     assert err <= bound
+
+
+def test_more_column_tiles_than_a_grid_dimension_takes():
+    """257 query heads on one K/V head, 2^22 query rows: 263168 tiles of 32 (Q block, head) columns, at most four per workgroup
+    by the ordinary rule, and the grid's third dimension ends at 65535."""
+    Hq, Nq, Nk, d = 257, 1 << 22, 40, 64
+    nQ = Nq // 128
+    say(f"[delta_s] Hq{Hq} Nq{Nq} Nk{Nk} d{d}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    k = torch.randn(1, 1, Nk, d, generator=g, device=DEV).half()
+    k_mean = k.float().mean(2)
+    q_mean = torch.randn(1, Hq, nQ, d, generator=g, device=DEV)
+    dsx = sage.sage_delta_s(k, k_mean, q_mean, Nq, causal=False)
+    torch.cuda.synchronize()
+    for h0 in range(0, Hq, 32):
+        got = sage.delta_s_to_key_order(dsx[:, h0:h0 + 32], Nk)[0].double()
+        want = _exact(k, k_mean, q_mean[:, h0:h0 + 32], d)
+        # (as above; the largest single value within sqrt(d) times the typical error)
+        assert ((got - want).norm() / want.norm()).item() <= 2.0**-24 * math.sqrt(d / 24 + 1.0), h0
+        assert ((got - want).abs().max() / want.square().mean().sqrt()).item() <= 2.0**-24 * 64, h0
