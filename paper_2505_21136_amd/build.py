@@ -96,7 +96,8 @@ def build(verbose: bool = False) -> str:
     if bad:
         raise RuntimeError("kernels spill registers to scratch memory: " + repr(bad))
     slow = {n: u for n, u in usage.items()
-            if ("attn_kernel" in n and u.get("Occupancy", 0) < 4) or ("prefill_kernel" in n and u.get("Occupancy", 0) < 2)}
+            if (("attn_kernel" in n or "prefill_kernel" in n) and u.get("Occupancy", 0) < 2)
+            or ("attn_kernelILi64E" in n and u.get("Occupancy", 0) < 4)}
     if slow:
         raise RuntimeError("attention kernels below the wavefronts per SIMD they are built for: " + repr(slow))
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]

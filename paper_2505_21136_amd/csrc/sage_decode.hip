@@ -464,9 +464,8 @@ hipError_t launch_attn_ranges(const void *q, const int8_t *k_i8, const uint8_t *
                            sm_scale, p_r, bf16, stream);
     }
     const Strides st = contiguous_bhnd(Hq, Nq, d);
-    hipError_t e = launch_prefill(q, true, st, k_i8, v_fp8, nullptr, k_scale, v_scale, nullptr, st, B, Hq, Hkv, Nq, Nk, d,
-                                  causal, sm_scale, p_r, bf16, stream, nullptr, nullptr, S, steps_per_split, ws.part_acc,
-                                  ws.part_ml);
+    hipError_t e = launch_attn(q, true, st, k_i8, v_fp8, nullptr, k_scale, v_scale, nullptr, st, B, Hq, Hkv, Nq, Nk, d, causal,
+                               sm_scale, p_r, bf16, stream, nullptr, nullptr, S, steps_per_split, ws.part_acc, ws.part_ml);
     if (e != hipSuccess) return e;
     return launch_merge(ws, v_scale, out, B, Hq, Hkv, Nq, d, bf16, 0, stream);
 }

@@ -72,14 +72,15 @@ hipError_t launch_delta_s(const void *k, Strides k_st, const float *k_mean, cons
 // through their strides; K^, V^ and the scales are contiguous.
 // dsx != NULL selects the 4+8 variant: q is the unquantised Q, k_i8 holds INT4 codes, q_mean the block means of Q
 // (launch_quant_q4) and dsx the score correction (launch_delta_s).
+// part_acc != NULL (with q_raw, without dsx): the key steps are cut into n_splits ranges of steps_per_split steps on separate
+// workgroups, which write partial results ([B*Hq*tiles][n_splits][128 rows][d] and [...][2] floats) instead of `out`.
 hipError_t launch_attn(const void *q, bool q_raw, Strides q_st, const int8_t *k_i8, const uint8_t *v_fp8, const float *q_scale,
                        const float *k_scale, const float *v_scale, void *out, Strides o_st, int B, int Hq, int Hkv,
-                       int Nq, int Nk, int d, bool causal, float sm_scale, float p_r, bool bf16_out,
-                       hipStream_t stream, const float *q_mean = nullptr, const float *dsx = nullptr);
+                       int Nq, int Nk, int d, bool causal, float sm_scale, float p_r, bool bf16,
+                       hipStream_t stream, const float *q_mean = nullptr, const float *dsx = nullptr, int n_splits = 1,
+                       int steps_per_split = 0, float *part_acc = nullptr, float *part_ml = nullptr);
 
-// The kernel behind launch_attn for more than kSmallRows query rows and for the 4+8 variant (sage_prefill.hip).
-// part_acc != NULL: the key steps are cut into n_splits ranges of steps_per_split steps on separate workgroups, which
-// write partial results ([B*Hq*tiles][n_splits][128 rows][d] and [...][2] floats) instead of `out`.
+// The kernel behind launch_attn for more than kSmallRows query rows per head (sage_prefill.hip); arguments as there.
 constexpr int kSmallRows = 64;
 hipError_t launch_prefill(const void *q, bool q_raw, Strides q_st, const int8_t *k_i8, const uint8_t *v_fp8,
                           const float *q_scale, const float *k_scale, const float *v_scale, void *out, Strides o_st, int B,
@@ -112,7 +113,7 @@ hipError_t launch_decode(const void *q, const int8_t *k_i8, const uint8_t *v_fp8
                          const DecodeScratch &ws);
 
 // The same idea for calls with more than 64 query rows per K/V head but too few (head, query tile) pairs to fill
-// the GPU: launch_prefill with its key steps cut into ranges on separate workgroups, then the combination launch of
+// the GPU: launch_attn with its key steps cut into ranges on separate workgroups, then the combination launch of
 // sage_decode.hip.
 int ranges_auto_steps_per_split(int B, int Hq, int Nq, int Nk);
 DecodeScratch ranges_scratch_layout(void *base, int B, int Hq, int Nq, int Nk, int d, int steps_per_split);
