@@ -95,6 +95,9 @@ size_t sage_workspace_bytes_gqa(int B, int Hq, int Hkv, int Nq, int Nk, int d);
  * mean = float(sum_n K / N) with the sum in double; K' = K - mean;
  * a = max|K'| over the valid rows of a block; delta = a / 127;
  * code = rne(K' * (127 / a)); a == 0 gives delta 0 and codes 0.
+ * Every call that quantises K or V may run a kernel whose workgroups wait for each other inside the launch (by shape; see
+ * sage_diag_quant_kv_path).  Next to another stream's kernel that holds the CUs such a wait can run out, after at most
+ * 0.5 ms; the workgroup then goes on alone: the same result, later.
  */
 int sage_quant_qk(const void *q, const void *k, int8_t *q_i8, int8_t *k_i8,
                   float *q_scale, float *k_scale, float *k_mean,
@@ -132,7 +135,7 @@ int sage_quant_v(const void *v, uint8_t *v_fp8, float *v_scale, float v_r,
 
 /*
  * sage_quant_k and sage_quant_v for K and V of one shape in one call  [same passages]:
- * the two tensors share their launches (three kernels instead of six); every output
+ * the two tensors share their launches; every output
  * is bit-identical to the separate calls.  Arguments as for those two calls.
  */
 int sage_quant_kv(const void *k, const void *v, int8_t *k_i8, float *k_scale, float *k_mean,
@@ -372,15 +375,15 @@ int sage_attn_fwd_decode(const void *q, const int8_t *k_i8, const uint8_t *v_fp8
 int sage_diag_mfma_rate(int kind, int iters, int workgroups, float *sink, double *ops_per_launch, void *stream);
 
 /*
- * Not a step of the method: selects, process-wide, which kernels the K/V quantisers (sage_quant_kv,
- * sage_quant_kv_static, sage_quant_kv4, sage_quant_k, sage_quant_v and the whole-pass entry points) launch.  Both choices compute the same
+ * Not a step of the method: selects, process-wide, which kernels the quantisers of K and V (sage_quant_kv, sage_quant_kv_static,
+ * sage_quant_kv4, sage_quant_k, sage_quant_qk, sage_quant_v and the whole-pass entry points) launch.  Both choices compute the same
  * codes, scales and mean (Sec. 2.1, Sec. 3).
- *   path        0 (default): by shape — the single-read kernel (K and V are read once: the workgroups of a head
+ *   path        0 (default): by shape -- the single-read kernel (K and V are read once: the workgroups of a head
  *               keep 64 or 128 KiB of tokens each in registers, exchange their partial column statistics through
- *               the workspace and then write the codes) when a head is at most 128 workgroups of 128 KiB (65536
- *               tokens at d = 128, 131072 at d = 64, there with enough heads), the three launches (statistics, finalize, codes; K and V read
- *               twice) above that; 1: always the three launches; 2: always the single-read kernel (calls for K and V
- *               together then fail with SAGE_EHIP above 256 workgroups of 64 KiB per head)
+ *               the workspace and then write the codes) up to 256 workgroups of 64 KiB per head (65536 tokens at
+ *               d = 128, 131072 at d = 64) where it measures faster than the three launches (statistics, finalize,
+ *               codes; K and V read twice); 1: always the three launches; 2: always the single-read kernel (beyond its
+ *               reach calls for K and V together then fail with SAGE_EHIP, calls for one of them run the three launches)
  *   wait_ticks  how long a workgroup of the single-read kernel waits for the partials of its partners before it
  *               computes the head's statistic alone from global memory (same result), in ticks of the GPU's
  *               constant 100 MHz clock; negative: it does not wait at all (for tests of that branch); the

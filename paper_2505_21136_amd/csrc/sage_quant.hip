@@ -551,8 +551,7 @@ struct QuantQ {
     int n_blocks, first;
 };
 constexpr int kBothTensors = 0, kOnlyK = 1, kOnlyV = 2;  // what a launch quantises (both: K and V groups in turn)
-constexpr int kResidentMaxGroup = 128;       // largest group the shape-based choice takes (resident_threads)
-constexpr int kResidentHardMaxGroup = 256;   // largest group a forced choice may take (thread t polls partner t)
+constexpr int kResidentMaxGroup = 256;  // largest group, in workgroups of 256 threads (thread t polls partner t)
 constexpr long long kResidentWaitTicks = 50000;  // 0.5 ms
 inline int resident_group_size(int N, int d, int threads) { return cdiv(N, resident_tokens(threads, d)); }
 
@@ -992,22 +991,53 @@ hipError_t quant_q_impl(const uint16_t *q, Strides st, int8_t *q_i8, float *q_sc
     return hipGetLastError();
 }
 
-// Threads of the single-read kernel's workgroups; 0: three launches.  Every workgroup reads its group's G partials and is held
-// up by the slowest partner, so a group of many wants large workgroups: with 512 threads (half of G) against 256, K and V, us:
-// H 24, N 32768, d 128 (G 128 with 256 threads) 145 / 166, H 8, N 16000 (63) 27.6 / 28.4, d 64 N 60000, H 16 (118) 97 / 101.
-// With few partners two workgroups of 256 are the better neighbours of a CU: B 2, H 8, N 5000 (20) 25.1 / 23.1; B 4, H 32,
-// N 4096 (16) costs the whole forward 467 / 457.  A head that fits one workgroup of 512 threads has nobody to wait for and no
-// partials to clear: B 16, H 16, N 512 22.6 / 25.9.  Against three launches at 98 partners of 512 threads (H 8, N 50000, inputs
-// not in the last-level cache) 92 / 105.
-// Where workgroups of 256 threads do not even fill the CUs once, fewer and larger ones lose: H 2, N 16000, d 128 14.8 /
-// 13.2 (the kernel alone), H 1, N 60000, d 64 18.9 / 15.2.  And at d = 64 the launch needs its two workgroups per CU to beat the three launches beyond the reach of 256 threads: H 2, N 70000 (276
-// workgroups) 25.3 / 22.5, N 100000 31.1 / 29.0, N 131072 (512) 33.5 / 36.1; H 8, N 70000 59.9 / 72.4.
-inline int resident_threads(int groups, int N, int d) {
+// Threads of the single-read kernel's workgroups; 0: three launches.  G: workgroups of 256 threads that a head of one tensor takes
+// (256 tokens each at d = 128, 512 at d = 64); `groups`: heads times tensors.  Every figure: three launches / 256 / 512 threads, us.
+//   * With few partners two workgroups of 256 are the better neighbours of a CU.  A group of many wants large ones, half as many
+//     partials to wait for and read: at d = 128 from about 96 on (K and V, H 8, G 64 34 / 29.6 / 28.9, G 80 39 / 38.6 / 40.6, G 128
+//     57 / 56 / 52; H 16, G 128 118 / 120 / 107).  At d = 64 a partial covers twice the tokens and 256 stays ahead up to 128
+//     (H 8, G 96 43.5 / 42.6 / 46.5, G 128 55 / 51 / 55; H 3, N 24578 16.8 with 256, 21.5 with 512).
+//   * Two workgroups of 256 that become one of 512 have nobody to meet and nothing to clear (d = 128, H 8 11.6 / 11.7 / 10.0; d = 64
+//     only where the heads fill the CUs: H 8 10.7 / 13.6 / 13.4, H 128 19.2 / 17.6 / 16.2).
+//   * Beyond 128 workgroups of 256 only those of 512 come into question.  512 of those are resident at once; a second round that is
+//     partly empty costs what the second read of the three launches does (d = 128, K and V, H 4, G 160, 640 workgroups
+//     39.8 / - / 43.3; H 4, G 256, 1024 57.7 / - / 54.2; H 1, G 160, 160 24.1 / - / 19.2;
+//     inputs that are not in the last-level cache: H 4, G 192 50.8 / - / 50.9, H 8, G 192, 1536 102 / - / 90).
+//   * K or V alone: three short launches are independent of each other's workgroups, where the single read has a clear and
+//     a meeting, 3 to 4 us that a small call does not win back (d = 64, K, H 4, N 4000 11.1 / 14.3; V, H 8, G 12 10.9 / 11.7,
+//     G 24 13.4 / 12.0; d = 128, K, H 1, G 128 16.3 / 17.2 / 17.5).  With Q in the same launch the workgroups of Q fill that time.
+enum class Quantise { kBoth, kOnlyK, kOnlyV, kKWithQ };
+inline int resident_threads(Quantise what, int groups, int N, int d) {
     const int path = g_kv_path.load();
+    const int G = resident_group_size(N, d, 256);
+    const long wgs = (long)groups * G, wgs512 = (long)groups * resident_group_size(N, d, 512);
     if (path == 1) return 0;
-    const int G = resident_group_size(N, d, 256), G512 = resident_group_size(N, d, 512);
-    if (path == 0 && G > kResidentMaxGroup && (G512 > kResidentMaxGroup || (d == 64 && (long)groups * G512 < 2 * kCUs))) return 0;
-    return G == 2 || G > kResidentMaxGroup || (G > 48 && (long)groups * G > kCUs) ? 512 : 256;
+    if (path == 2) return G == 2 || G > (d == 128 ? 96 : 128) ? 512 : 256;
+    if (G == 1) return 256;
+    if (G > kResidentMaxGroup) return 0;
+    if (d == 128) {
+        if (G == 2) return 512;
+        if (G <= 96) return 256;
+        if (what == Quantise::kKWithQ) return 512;
+        if (wgs512 < kCUs / 2) return G <= 128 && what != Quantise::kOnlyK ? 256 : 0;
+        return G > 128 && wgs512 > 2 * kCUs && wgs512 < 4 * kCUs ? 0 : 512;
+    }
+    switch (what) {
+        case Quantise::kOnlyK:
+            if (G == 2) return groups >= kCUs / 2 ? 512 : 0;
+            return G <= 128 && ((wgs >= kCUs && G <= 48) || wgs >= 2 * kCUs) ? 256 : 0;
+        case Quantise::kOnlyV:
+            if (G == 2) return 512;
+            if (G <= 128) return wgs >= 3 * kCUs / 4 ? 256 : 0;
+            return wgs512 >= kCUs / 2 ? 512 : 0;
+        case Quantise::kKWithQ:
+            if (G == 2) return 512;
+            return G <= 128 && wgs >= 3 * kCUs / 8 ? 256 : 0;
+        default:
+            if (G == 2) return groups >= kCUs / 4 ? 512 : 256;
+            if (G <= 128) return 256;
+            return wgs512 >= 4 * kCUs ? 512 : 0;
+    }
 }
 
 // The outputs from one read of the tensors (quant_kv_resident_kernel).
@@ -1045,7 +1075,7 @@ template <bool BF16, int D, int QMAX>
 hipError_t launch_resident(int threads, const uint16_t *k, Strides k_st, const uint16_t *v, Strides v_st, int8_t *k_i8,
                            float *k_scale, float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H, int N,
                            hipStream_t stream, const QuantScratch &ws, int tensors, const QuantQ &q = QuantQ{}) {
-    if (resident_group_size(N, D, 256) > kResidentHardMaxGroup) return hipErrorInvalidValue;
+    if (resident_group_size(N, D, 256) > kResidentMaxGroup) return hipErrorInvalidValue;
     if (threads == 512)
         return launch_resident_n<BF16, D, QMAX, 512>(k, k_st, v, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N,
                                                      stream, ws, tensors, q);
@@ -1057,8 +1087,8 @@ hipError_t launch_resident(int threads, const uint16_t *k, Strides k_st, const u
 template <bool BF16, int D>
 hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_scale, float *k_mean, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws, const QuantQ &q) {
-    const int threads = resident_threads(BH, N, D);
-    if (threads && resident_group_size(N, D, 256) <= kResidentHardMaxGroup)
+    const int threads = resident_threads(q.x ? Quantise::kKWithQ : Quantise::kOnlyK, BH, N, D);
+    if (threads && resident_group_size(N, D, 256) <= kResidentMaxGroup)
         return launch_resident<BF16, D, 127>(threads, k, st, nullptr, st, k_i8, k_scale, k_mean, nullptr, nullptr, 0.0f, BH, H, N,
                                              stream, ws, kOnlyK, q);
     const int chunks = cdiv(N, kStatRows);
@@ -1074,8 +1104,8 @@ hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_sc
 template <bool BF16, int D>
 hipError_t quant_v_impl(const uint16_t *v, Strides st, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws) {
-    const int threads = resident_threads(BH, N, D);
-    if (threads && resident_group_size(N, D, 256) <= kResidentHardMaxGroup)
+    const int threads = resident_threads(Quantise::kOnlyV, BH, N, D);
+    if (threads && resident_group_size(N, D, 256) <= kResidentMaxGroup)
         return launch_resident<BF16, D, 127>(threads, nullptr, st, v, st, nullptr, nullptr, nullptr, v_fp8, v_scale, v_r, BH, H, N,
                                              stream, ws, kOnlyV);
     const int chunks = cdiv(N, kStatRows);
@@ -1178,7 +1208,7 @@ hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v
                            bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4) {
     const uint16_t *k16 = static_cast<const uint16_t *>(k), *v16 = static_cast<const uint16_t *>(v);
     const int BH = B * H;
-    const int threads = resident_threads(2 * BH, N, d);
+    const int threads = resident_threads(Quantise::kBoth, 2 * BH, N, d);
 #define SAGE_KV(BF, DD, QM)                                                                                           \
     (threads ? launch_resident<BF, DD, QM>(threads, k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, \
                                            BH, H, N, stream, ws, kBothTensors)                                       \
