@@ -493,13 +493,17 @@ hipError_t launch_attn(const void *q, bool q_raw, Strides q_st, const int8_t *k_
 #undef SAGE_SMALL
     }
     // Which kernel above kSmallRows rows: by how many workgroups the query rows make.  Up to one workgroup of 32 rows per CU, a key
-    // step is spread over a workgroup's wavefronts (sage_spread.hip); then with 64 rows per workgroup; beyond one of those per CU the
-    // CUs are filled better by whole steps per wavefront and two workgroups of 128 rows each (sage_prefill.hip).  Measured, us, at
-    // 1024 x 1024 and 1024 x 16384 (rows x keys, d 128, full), spread 32 / spread 64 / prefill: 128 tiles of 32 rows
-    // 10.6 / 13.7 / 16.5 and 76 / 104 / 172; 512 tiles 20.3 / 14.5 / 16.8 and 152 / 111 / 173; 1024 tiles 38.5 / 27.8 / 17.8
-    // and 301 / 220 / 181.  The 4+8 variant and key ranges exist in the prefill kernel only.
+    // step is spread over a workgroup's wavefronts (sage_spread.hip); then with 64 rows per workgroup, where there are more than two
+    // key steps to shorten; beyond one of those per CU the CUs are filled better by whole steps per wavefront and two
+    // workgroups of 128 rows each (sage_prefill.hip).  The bits of a row are the same.  Measured, us, spread 32 / spread 64 / prefill,
+    // full attention, 1024 x 1024 rows x keys: 256 tiles of 32 rows, d 128 11.9 / 15.2 / 17.5, d 64 9.7 / 12.3 / 14.3; 512 tiles
+    // 21.1 / 15.9 / 18.0 and 16.3 / 12.5 / 14.4; 1024 tiles 38.8 / 28.7 / 19.2 and 29.1 / 22.7 / 15.1.  1024 x 8192: 256 tiles
+    // 45 / 60 / 92 and 39 / 54 / 79; 512 tiles 85 / 64 / 95 and 72 / 55 / 79; 1024 tiles 162 / 119 / 100 and 138 / 103 / 82.  512 tiles
+    // over 128 keys 12.7 / 9.4 / 8.2 and 9.3 / 7.2 / 6.3, 256 keys 13.6 / 10.4 / 9.5 and 10.1 / 7.8 / 7.4, 512 keys 16.3 / 12.3 / 12.2
+    // and 12.2 / 9.4 / 9.7.  Causal calls keep the order up to 2048 x 2048 (above, their short tiles would let the spread kernels go
+    // on a little further).  The 4+8 variant and key ranges exist in the prefill kernel only.
     const long heads = (long)B * Hq;
-    const int row_groups = dsx || part_acc ? 0 : heads * cdiv(Nq, 32) <= kCUs ? 1 : heads * cdiv(Nq, 64) <= kCUs ? 2 : 0;
+    const int row_groups = dsx || part_acc ? 0 : heads * cdiv(Nq, 32) <= kCUs ? 1 : heads * cdiv(Nq, 64) <= kCUs && Nk > 2 * kW ? 2 : 0;
     if (row_groups)
         return launch_spread(q, q_raw, q_st, k_i8, v_fp8, q_scale, k_scale, v_scale, out, o_st, B, Hq, Hkv, Nq, Nk, d,
                              causal, sm_scale, p_r, bf16, stream, row_groups);

@@ -1,8 +1,8 @@
 """The kernels behind calls with more than 64 query rows at the edges of their tiles, whole outputs against the oracle:
 wavefronts with one, 31, 32 and no valid rows, key tiles of 32 cut at every kind of place, one key step and the first and last
 of several, masks whose diagonal falls anywhere in a tile.  Which kernel runs depends on how many workgroups the query rows
-make, so every shape runs with few heads (a key step spread over a workgroup of 32 rows), with more (64 rows) and with many
-(whole steps per wavefront)."""
+make, so every shape runs with few heads (a key step spread over a workgroup of 32 rows), with more (64 rows, where there are more
+than two key steps) and with many (whole steps per wavefront)."""
 import numpy as np
 import pytest
 import torch
@@ -21,6 +21,7 @@ CASES = [  # idx, Hkv, Nq, Nk, d, causal
     (2, 1, 128, 129, 128, True), (4, 2, 160, 191, 64, True), (1, 1, 129, 255, 128, True),
     (5, 2, 65, 384, 64, True), (2, 2, 257, 385, 128, True), (3, 1, 320, 320, 64, False), (4, 1, 193, 640, 128, True),
 ]
+CASES += [(2, 2, 65, 257, 128, True), (3, 1, 97, 300, 64, False), (5, 1, 129, 383, 128, False)]  # three key steps
 LONG = [  # de-quantisation constants are re-made every 32 steps
     (5, 1, 130, 4225, 128, False), (4, 1, 100, 8321, 64, True),
 ]
@@ -60,7 +61,7 @@ def test_tile_edges_against_the_oracle(idx, Hkv, Nq, Nk, d, causal, kernel):
     _run(idx, _heads(kernel, Hkv, Nq), Hkv, Nq, Nk, d, causal, kernel)
 
 
-@pytest.mark.parametrize("kernel", ["32 rows", "whole steps"])
+@pytest.mark.parametrize("kernel", ["32 rows", "64 rows", "whole steps"])
 @pytest.mark.parametrize("idx,Hkv,Nq,Nk,d,causal", LONG)
 def test_many_steps_against_the_oracle(idx, Hkv, Nq, Nk, d, causal, kernel):
     _run(idx, _heads(kernel, Hkv, Nq), Hkv, Nq, Nk, d, causal, kernel)
