@@ -27,37 +27,36 @@ if ROOT not in sys.path:
 PEAK_MFMA_8BIT = 5.0e15      # INT8 and FP8 dense, op/s
 PEAK_HBM = 8.0e12            # B/s
 
-# What rocprofv3 measured for the attention kernel on a workload (summaries under profiles/): HBM traffic of one
-# launch (FETCH_SIZE / WRITE_SIZE scaled by a copy kernel of known size) and, per wavefront and 128-key step,
-# the vector instructions issued, how many of them are MFMA, and how many run at half rate (exp, FP8 pack).
-# Only workloads that were profiled have an entry; everything derived from a missing entry is null in the
+# What rocprofv3 measured for the attention kernel (prefill_kernel) on a workload (summary under profiles/): HBM traffic of one
+# launch (FETCH_SIZE / WRITE_SIZE scaled by a copy kernel of known size) and, per wavefront and key step (32 query rows x
+# 128 keys: 64 scores per lane), the vector instructions issued, how many of them are MFMA, and how many run at half rate (exp,
+# FP8 pack).  Only workloads that were profiled have an entry; everything derived from a missing entry is null in the
 # JSON line.  `valu_busy` / `mfma_busy` are SQ_ACTIVE_INST_VALU and SQ_VALU_MFMA_BUSY_CYCLES as fractions of
 # the kernel's SIMD time.
+SOURCE = "profiles/prefill_kernel_counters.md"
 PROFILED = {
-    "cfg5": dict(source="profiles/attn_kernel_cfg5_counters.md",
-                 traffic=int(885132 * 1024 * 2.0 + 196608 * 1024 * 1.0),
-                 valu_per_step=222.2, mfma_i8=16, mfma_f8=8, half_rate=49.2, valu_busy=0.88, mfma_busy=0.41),
-    "cfg3": dict(source="profiles/attn_kernel_cfg5_counters.md (section cfg3)", traffic=None,
-                 valu_per_step=211.7, mfma_i8=8, mfma_f8=4, half_rate=49.2, valu_busy=0.98, mfma_busy=0.24),
+    "cfg5": dict(source=SOURCE, traffic=int(885070 * 1024 * 2.0 + 196608 * 1024 * 1.0),
+                 valu_per_step=389.1, mfma_i8=16, mfma_f8=8, half_rate=97.0, valu_busy=0.87, mfma_busy=0.46),
+    "cfg3": dict(source=SOURCE, traffic=int(65635 * 1024 * 2.0 + 65536 * 1024 * 1.0),
+                 valu_per_step=386.0, mfma_i8=8, mfma_f8=4, half_rate=97.1, valu_busy=1.0, mfma_busy=0.27),
     # causal: per executed wavefront-step, prologue and epilogue of the short workgroups included
-    "cfg2": dict(source="profiles/attn_kernel_cfg5_counters.md (section cfg2)",
-                 traffic=int(174437 * 1024 * 2.0 + 131182 * 1024 * 1.0),
-                 valu_per_step=266.9, mfma_i8=16, mfma_f8=8, half_rate=49.0, valu_busy=0.80, mfma_busy=0.32),
+    "cfg2": dict(source=SOURCE, traffic=int(187390 * 1024 * 2.0 + 131091 * 1024 * 1.0),
+                 valu_per_step=476.6, mfma_i8=16, mfma_f8=8, half_rate=96.0, valu_busy=0.81, mfma_busy=0.37),
 }
 
 
 def alu_bound(prof):
     """The co-limit of the MFMA roofline: the vector-ALU issue port, which MFMA and ordinary vector
     instructions share.  Port cycles per wavefront-step from the measured instruction mix -- 4 cycles per
-    full-rate instruction and per 4-pass MFMA (INT8 16x16x64), 8 per half-rate instruction and per 8-pass MFMA
-    (FP8 16x16x128) -- against the MFMA pipe's own cycles for the same step (16 and 32 per instruction): their
+    full-rate instruction and per MFMA, 8 per half-rate instruction (which adds up to the measured SQ_ACTIVE_INST_VALU within
+    1 %) -- against the MFMA pipe's own cycles for the same step (32 per INT8 32x32x32, 64 per FP8 32x32x64): their
     ratio is the fraction of the MFMA peak this instruction mix can reach at equal clock."""
     if not prof:
         return None
     n_mfma = prof["mfma_i8"] + prof["mfma_f8"]
     other = prof["valu_per_step"] - n_mfma
-    port = 4.0 * (other - prof["half_rate"]) + 8.0 * prof["half_rate"] + 4.0 * prof["mfma_i8"] + 8.0 * prof["mfma_f8"]
-    pipe = 16.0 * prof["mfma_i8"] + 32.0 * prof["mfma_f8"]
+    port = 4.0 * (other - prof["half_rate"]) + 8.0 * prof["half_rate"] + 4.0 * n_mfma
+    pipe = 32.0 * prof["mfma_i8"] + 64.0 * prof["mfma_f8"]
     return {"port_cycles_per_wavefront_step": round(port, 1), "mfma_cycles_per_wavefront_step": pipe,
             "frac_of_peak_allowed": round(pipe / port, 4), "peak_allowed": round(PEAK_MFMA_8BIT / 1e12 * pipe / port, 1),
             "unit": "TFLOP/s", "instruction_mix_from": prof["source"]}
@@ -189,8 +188,9 @@ def main():
     quant_gbs = (9.0 if args.staged_q else 6.0) * E / (quant_ms * 1e-3) / 1e9 if quant_ms > 0 else None
 
     prof = PROFILED.get(cfg.name)
-    # the matrix-pipe rate this GPU sustains on the kernel's own instruction mix (two INT8 16x16x64 per FP8
-    # 16x16x128), measured now, on the warm GPU, with the library's MFMA-only kernel
+    # the matrix-pipe rate this GPU sustains on the kernel's own mix of INT8 and FP8 operations, measured now, on the warm GPU,
+    # with the library's MFMA-only kernel (two INT8 16x16x64 per FP8 16x16x128; the 32x32 forms that the attention kernel
+    # issues do the same 2048 operations per cycle)
     peak_measured = None if args.no_mfma_peak else sage.diag_mfma_rate(3) / 1e12
 
     result = {
@@ -211,7 +211,7 @@ def main():
                                + (f", {cfg.k_outlier_channels} K outlier channels x20" if cfg.k_outlier_channels else ""),
                    "p_r": 224.0, "v_r": 4.5, "bq": 128, "bk": 64, "w": 128},
         "roofline": {
-            "kernel": "attn_kernel (" + ("" if args.staged_q else "Q quantisation + ")
+            "kernel": ("spread_kernel" if cfg.name == "cfg1" else "prefill_kernel") + " (" + ("" if args.staged_q else "Q quantisation + ")
                       + "fused INT8 QK^T + softmax + FP8 PV)",
             "bound": "mfma",
             "achieved": round(attn_tops, 2),
