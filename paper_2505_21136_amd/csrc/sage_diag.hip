@@ -16,7 +16,8 @@ constexpr int kAcc = 8;  // independent accumulators per wavefront (no instructi
 // kind 0: v_mfma_i32_16x16x64_i8            (S = Q^ K^T)
 // kind 1: v_mfma_f32_16x16x128_f8f6f4, FP8  (O += P^ V^)
 // kind 2: v_mfma_f32_16x16x32_fp8_fp8       (the older FP8 form, for comparison)
-// kind 3: two of kind 0 per one of kind 1   (the attention kernel's own mix: equal operation counts)
+// kind 3: two of kind 0 per one of kind 1   (the attention kernels' mix: equal operation counts; the 32x32 forms that serve more
+//         than 64 query rows do the same operations per cycle)
 template <int KIND>
 __global__ __launch_bounds__(256, 4) void mfma_rate_kernel(int iters, float *sink) {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -50,9 +50,9 @@ hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v
                            float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int B, int H, int N, int d,
                            bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4 = false);
 
-// Which kernels the K/V quantisers use: 0 = by shape (the single-read kernel up to 128 workgroups per head),
-// 1 = always the three launches (statistics, finalize, codes), 2 = always the single-read kernel (error above 256
-// workgroups per head).  wait_ticks: how long a workgroup of the single-read kernel waits for its partners before
+// Which kernels the K/V quantisers use: 0 = by shape (resident_threads in sage_quant.hip),
+// 1 = always the three launches (statistics, finalize, codes), 2 = always the single-read kernel (above 256 workgroups of 256 threads
+// per head: an error for K and V together, the three launches for one of them).  wait_ticks: how long a workgroup of the single-read kernel waits for its partners before
 // it computes the head's statistic alone (100 MHz ticks; negative: no wait).  Process-wide.
 void set_quant_kv_path(int path, long long wait_ticks);
 

@@ -1048,17 +1048,19 @@ hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v,
     const int G = resident_group_size(N, D, NTHR);
     const int nK = cdiv(N, kBK), nT = cdiv(N, kW);
     const long long wait_ticks = g_kv_wait_ticks.load();
+    // the partials of K and V together lie back to back, as many as this launch has (the buffers are laid out for groups of 256 threads,
+    // twice as many); K alone and V alone keep to their own buffers
+    const size_t n = (size_t)BH * G * D;
+    float *v_part = tensors == kBothTensors ? reinterpret_cast<float *>(ws.k_sum_part + n) : ws.v_max_part;
     if (G > 1) {
-        // the partial buffers, which lie back to back (each a multiple of 256 bytes)
-        char *from = reinterpret_cast<char *>(tensors == kOnlyV ? (void *)ws.v_max_part : (void *)ws.k_sum_part);
-        char *to = reinterpret_cast<char *>(tensors == kOnlyK ? (void *)ws.v_max_part : (void *)ws.v_rcp);
-        const int words = (int)((to - from) / 16);
-        zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(reinterpret_cast<uint4 *>(from), words);
+        void *from = tensors == kOnlyV ? (void *)v_part : (void *)ws.k_sum_part;
+        const int words = (int)(n * (tensors == kBothTensors ? 12 : tensors == kOnlyK ? 8 : 4) / 16);
+        zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(static_cast<uint4 *>(from), words);
     }
     q.first = (tensors == kBothTensors ? 2 * BH : BH) * G;
 #define SAGE_RESIDENT(Q, GRID)                                                                                          \
     quant_kv_resident_kernel<BF16, D, QMAX, NTHR, Q><<<GRID, NTHR, 0, stream>>>(                                        \
-        k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT,     \
+        k, k_st, v, v_st, H, N, G, ws.k_sum_part, v_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT,     \
         wait_ticks, tensors, q)
     if constexpr (QMAX == 127) {
         if (q.x) {

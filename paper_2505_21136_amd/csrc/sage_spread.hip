@@ -16,10 +16,10 @@
 // load, and the texture path takes one line per cycle: 0.95 us per step against 0.55 us.)
 //
 // What bounds it is the chain: about 120 vector instructions of one wavefront, matrix results and LDS round trips waited for
-// by it, and a barrier per step: 0.55 us per step with 32 rows, 0.8 us with 64, where a wavefront of the other kernel, alone
-// on its SIMD, takes 1.3 us.  (Tried: operands loaded straight into registers; scores made one step instead of two ahead of
-// their use: 0.64 us.)  The per-step work that does not shrink with the tile weighs more than in the other kernel and a CU
-// holds one workgroup, so with enough query tiles that one is faster; launch_attn has the lines and both sides.
+// by it, and a barrier per step: 0.57 us per step with 32 rows, 0.79 us with 64 (d = 64: 0.48 and 0.71), where a wavefront of the
+// other kernel, alone on its SIMD, takes 1.33 us (1.15).  (Tried: operands loaded straight into registers; scores made one step instead of two ahead of
+// their use: 0.64 us.)  The per-step work that does not shrink with the tile weighs more than in the other kernel and LDS
+// holds one workgroup per CU (two of 32 rows at d = 64), so with enough query tiles that one is faster; launch_attn has the lines and both sides.
 #include "sage_attn_device.h"
 #include "sage_internal.h"
 
