@@ -174,7 +174,8 @@ int sage_quant_kv_static(const void *k, const void *v, int8_t *k_i8, float *k_sc
  *            NaN, infinity) selects 1/sqrt(d)
  *   p_r      FP8 range of P~ (224 by default), must lie in (0, 448]
  * The running maximum is updated once per SAGE_W keys to the exact step
- * maximum; l accumulates the unquantised P~.
+ * maximum; l accumulates the unquantised P~.  The result of a (batch, head) depends on its
+ * own operands and sizes alone, bit for bit, not on how many others the call has.
  */
 int sage_attn_fwd_quantized(const int8_t *q_i8, const int8_t *k_i8, const uint8_t *v_fp8,
                             const float *q_scale, const float *k_scale, const float *v_scale,
@@ -198,8 +199,8 @@ int sage_attn_fwd_quantized_gqa(const int8_t *q_i8, const int8_t *k_i8, const ui
 /*
  * Fused attention on quantised K^, V^ and UNQUANTISED Q  [Sec. 2.1; Sec. 3.1]: the
  * per-block INT8 quantisation of Q (blocks of SAGE_BQ rows, delta = max|Q|/127,
- * round to nearest even) runs in the prologue of the attention kernel, whose
- * workgroups own exactly one Q block each; Q^ and delta_Q are the same bits
+ * round to nearest even) runs in the prologue of the attention kernel, each of whose
+ * workgroups has its rows in one Q block; Q^ and delta_Q are the same bits
  * sage_quant_q would produce, but are never written to memory.  Output and every
  * other argument as for sage_attn_fwd_quantized_gqa;
  *   q        device, [B,Hq,Nq,d] of `dt`, 16-byte aligned                 (in)
@@ -295,7 +296,7 @@ int sage_quant_kv4(const void *k, const void *v, int8_t *k_i4, float *k_scale, f
  * The score correction in the units of the softmax exponent:
  *   dsx[b,hq,i,T,pos] = (sum_c q_mean[b,hq,i,c] * (K[b,hkv,n,c] - k_mean[b,hkv,c])) * sm_scale * log2(e)
  * for Q block i and key n = 128*T + 16*t + 4*g + j stored at pos = 32*g + 4*t + j (the order in which a lane
- * of the attention kernel holds its scores); keys >= Nk hold 0.  FP32 arithmetic.
+ * of the attention kernel for few rows holds its scores); keys >= Nk hold 0.  FP32 arithmetic.
  *   k       device, [B,Hkv,Nk,d] of `dt` (the unquantised keys)       (in)
  *   k_mean  device, [B,Hkv,d] float, from sage_quant_kv4              (in)
  *   q_mean  device, [B,Hq,ceil(Nq/SAGE_BQ),d] float                   (in)
@@ -337,8 +338,8 @@ int sage_attn_fwd_4bit(const void *q, const void *k, const void *v, void *out,
  * from it by FP8 rounding decisions only.
  * Up to (Hq/Hkv) * Nq = 64 query rows per K/V head, the rows of all query heads that share a K/V head are packed
  * into MFMA tiles of 16 and one wavefront takes one (K/V head, range, row tile), reading K^ and V^ straight from
- * global memory; above that the prefill kernel runs with its key steps cut into ranges, one workgroup per
- * (head, query tile, range).
+ * global memory; above that the kernel that sage_attn_fwd_kvquantized_gqa would run for that many rows runs with its key steps
+ * cut into ranges, one workgroup per (head, query tile, range).
  *   q, out      device, [B,Hq,Nq,d] contiguous, 16-bit type `dt`; Q is quantised inside (per head and block of 128
  *               rows, as everywhere)
  *   k_i8 .. v_scale   device, as produced by sage_quant_k / sage_quant_v (or sage_quant_kv) for [B,Hkv,Nk,d]
@@ -367,7 +368,8 @@ int sage_attn_fwd_decode(const void *q, const int8_t *k_i8, const uint8_t *v_fp8
  * `iters` rounds), so that a benchmark can time it (events on `stream`) and state throughput against the
  * matrix-pipe rate the GPU at hand sustains, next to the published peak.
  *   kind   0: INT8 16x16x64 (the Q^ K^T product), 1: FP8 16x16x128 (the P^ V^ product),
- *          2: the older FP8 16x16x32 form, 3: the attention kernel's mix (two of kind 0 per one of kind 1)
+ *          2: the older FP8 16x16x32 form, 3: the attention kernels' mix (two of kind 0 per one of kind 1: equal operation
+ *          counts; the 32x32 forms used above 64 query rows do the same operations per cycle)
  *   sink   device, one float (never written in practice; keeps the arithmetic alive)
  *   ops_per_launch  host, receives the operation count (2 per multiply-add) of the launch
  * Returns SAGE_EINVAL for a bad argument, SAGE_EHIP if the launch failed.
