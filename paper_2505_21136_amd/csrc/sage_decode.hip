@@ -6,15 +6,20 @@
 // and MFMA columns idle and B*Hq workgroups cannot fill 256 CUs.  Instead:
 //   * the R = (Hq/Hkv) * Nq <= 64 query rows of all query heads that share one K/V head are packed into the 16
 //     columns of T = ceil(R/16) <= 4 MFMA tiles (exact: every row keeps its own scale, running maximum and sum), so
-//     K^ and V^ of a head leave HBM once for all of them (the T wavefronts of a range sit in one workgroup and
-//     read the same tiles at the same time: all but the first hit L2);
-//   * the keys are cut into ranges of `steps_per_split` key steps and ONE WAVEFRONT owns one (batch, K/V head,
-//     range, row tile): it runs the step recurrence on its range from m = -inf, l = 0, acc = 0 and writes (m, l, acc) per
-//     row; merge_kernel then combines the ranges as partial softmax sums (m = max m_s, weights 2^(m_s - m));
-//   * a wavefront uses each tile exactly once, so the operands go global -> registers directly (16 bytes per
-//     lane and load, in the lane order the MFMA wants), K^ of step j+1 and V^ of step j in flight under the
-//     arithmetic of step j; no LDS, no barrier.
-// The stage is bound by HBM: K^ + V^ are read once, (2 * Nk * d bytes per K/V head).
+//     K^ and V^ of a head leave HBM once for all of them;
+//   * the keys are cut into ranges of `steps_per_split` key steps and ONE WAVEFRONT owns one (batch, K/V head, range) and one or two
+//     row tiles: it runs the step recurrence on its range from m = -inf, l = 0, acc = 0; the ranges are combined as partial softmax
+//     sums (m = max m_s, weights 2^(m_s - m)), by the same workgroup through LDS where it holds all of them, otherwise by a second
+//     launch over the (m, l, acc) per row that the wavefronts write;
+//   * tiles are copied global -> LDS in halves (64 keys of K^, half the channels of V^: contiguous bytes) into two slots of the
+//     wavefront's own, each refilled as soon as its operands are in registers; no barrier.  (Operands loaded straight into registers
+//     cost the texture path four times as much: neighbouring lanes want neighbouring rows, so a load of 1 KB takes 64 cycles instead
+//     of 16, 2048 per key step and wavefront at d = 128, which is what bounded short calls.  Four or eight slots are no faster than
+//     two: 64 heads x 32768 keys, d 128, 97.4 with four, 98.4 us with two; 192 x 4096 41.4 / 36.5.)
+// What bounds it: with a large cache HBM, K^ + V^ read once (2 * Nk * d bytes per K/V head); with a small one the chain launch -- Q --
+// first tiles -- two steps -- combination.  Measured, us per call in a graph, operands in registers and always two launches / now:
+// 16 heads x 1500 keys, d 128, one row of 4 query heads 12.5 / 8.6; 8 x 8192 13.8 / 8.4; 64 x 32768 103 / 98; 128 x 2048 15.9 / 13.1;
+// 64 rows per head, 256 x 2048 64 / 32.5, 64 x 16384 95 / 71 (d 64: 56 / 38.5).
 #include "sage_attn_device.h"
 #include "sage_internal.h"
 
@@ -23,81 +28,170 @@
 namespace sage {
 namespace {
 
-// D: head dimension; CAUSAL: end-aligned mask (key n visible to row r iff n <= r + Nk - Nq); BF16: type of Q / O.
-// Grid: ceil(B*Hkv*S*T / 4) workgroups of 4 wavefronts; wavefront w = ((b*Hkv + kvh)*S + split)*T + row tile.
-// NT: row tiles per wavefront (1: up to 16 rows per K/V head, 2 wavefronts per SIMD; 2: up to 32 rows per
-// wavefront -- the operands of a key step are fetched once for both tiles --, 1 wavefront per SIMD).
-template <int D, bool CAUSAL, bool BF16, int NT>
-__global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void decode_kernel(const uint16_t *__restrict__ Q, const int8_t *__restrict__ Kc,
-                                                        const uint8_t *__restrict__ Vt, const float *__restrict__ dk,
-                                                        float *__restrict__ part_acc, float *__restrict__ part_ml,
-                                                        int n_waves, int Hq, int Hkv, int group, int Nq, int Nk, int nT,
-                                                        int nKblk, int S, int T, int steps_per_split, float sm_scale,
-                                                        float log2_pr) {
+// Epilogue of the prefill kernel on four channels: O = acc * (delta_V / l) (l carries the factor P_r), rounded to the output
+// type.
+template <int D, bool BF16>
+__device__ __forceinline__ void store_quad(const float4 &acc, float l, const float *__restrict__ dv, int bhk,
+                                           uint16_t *__restrict__ out, int row, int cq) {
+    const float inv = 1.0f / l;
+    const float4 sc = *reinterpret_cast<const float4 *>(dv + (size_t)bhk * D + 4 * cq);
+    const float y0 = acc.x * (sc.x * inv), y1 = acc.y * (sc.y * inv);
+    const float y2 = acc.z * (sc.z * inv), y3 = acc.w * (sc.w * inv);
+    *reinterpret_cast<uint2 *>(out + (size_t)row * D + 4 * cq) = make_uint2(pack2<BF16>(y0, y1), pack2<BF16>(y2, y3));
+}
+
+// One range's (m, l, acc) of a row on top of the sums l, acc, which are relative to the row's maximum mx over all ranges.  (Each
+// product is rounded before it is added.)
+__device__ __forceinline__ void add_range(const float2 &ml, const float4 &a, float mx, float &l, float4 &acc) {
+    const float wgt = __builtin_amdgcn_exp2f(ml.x - mx);
+    l += __builtin_fmaf(wgt, ml.y, 0.0f);
+    acc.x += __builtin_fmaf(wgt, a.x, 0.0f);
+    acc.y += __builtin_fmaf(wgt, a.y, 0.0f);
+    acc.z += __builtin_fmaf(wgt, a.z, 0.0f);
+    acc.w += __builtin_fmaf(wgt, a.w, 0.0f);
+}
+
+// D: head dimension; causal: end-aligned mask (key n visible to row r iff n <= r + Nk - Nq); BF16: type of Q / O.
+// NT: row tiles per wavefront (1: up to 16 rows per K/V head; 2: up to 32 -- the operands of a key step are read once for both).
+// TW = ceil(T / NT) wavefronts share a range.  TOGETHER: a workgroup is the TW * S <= 8 wavefronts of a K/V head, which combine their
+// ranges and write the output (the additions of merge_few_kernel: same bits).  Otherwise blockDim / 64 wavefronts,
+// w = ((b*Hkv + kvh)*S + split)*TW + group.  Dynamic LDS: two half tiles per wavefront; TOGETHER the partial results take their place.
+template <int D, bool BF16, int NT, bool TOGETHER>
+__global__ __launch_bounds__(TOGETHER ? 512 : 256, 2) void decode_kernel(
+    const uint16_t *__restrict__ Q, const int8_t *__restrict__ Kc, const uint8_t *__restrict__ Vt, const float *__restrict__ dk,
+    const float *__restrict__ dv, uint16_t *__restrict__ out, float *__restrict__ part_acc, float *__restrict__ part_ml,
+    int n_waves, int Hq, int Hkv, int group, int Nq, int Nk, int nT, int nKblk, int S, int T, int steps_per_split, int causal,
+    float sm_scale, float log2_pr) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int KC = D / 64;  // 64-wide contraction chunks of Q.K^T
-    constexpr int CT = D / 16;  // 16-channel tiles of the output
+    constexpr int KC = D / 64;      // 64-wide contraction chunks of Q.K^T
+    constexpr int CT = D / 16;      // 16-channel tiles of the output
+    constexpr int HALF = 64 * D;    // bytes of half a tile
+    constexpr int NL = HALF / 1024; // copies of 1 KB per half tile
+    constexpr int ROWS = 16 * NT, LD = D + 4;  // combination: rows and floats per row (4 more: sixteen rows fall on different banks)
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    __shared__ float row_max[TOGETHER ? 8 : 4][64];  // max |Q| of the K/V head's rows
+    __shared__ __attribute__((aligned(8))) float2 ml_lds[TOGETHER ? 8 : 1][TOGETHER ? ROWS : 1];
     const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
-    if (w >= n_waves) return;  // (whole wavefronts leave; the kernel has no barrier)
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lq = lane & 15, g = lane >> 4;
-    // T row tiles in groups of NT per wavefront: TW = ceil(T / NT) wavefronts per (K/V head, range)
     const int TW = (T + NT - 1) / NT;
-    const int rt0 = (w % TW) * NT, split = (w / TW) % S, bhk = w / (TW * S);
+    int rt0, split, bhk;
+    if constexpr (TOGETHER) {
+        rt0 = wave % TW * NT, split = wave / TW, bhk = blockIdx.x;
+    } else {
+        const int w = (int)blockIdx.x * ((int)blockDim.x >> 6) + wave;
+        if (w >= n_waves) return;  // (whole wavefronts leave; there is no barrier)
+        rt0 = (w % TW) * NT, split = (w / TW) % S, bhk = w / (TW * S);
+    }
     const int b = bhk / Hkv, kvh = bhk % Hkv;
     const int R = group * Nq;  // rows in use (<= 16 * T)
     const int shift = Nk - Nq;
 
-    const int8_t *Kh = Kc + (size_t)bhk * Nk * D;
+    const uint8_t *Kh = reinterpret_cast<const uint8_t *>(Kc) + (size_t)bhk * Nk * D;
     const uint8_t *Vh = Vt + (size_t)bhk * nT * D * 128;
+    const int k_bytes = Nk * D, v_bytes = nT * D * 128;
     const int j0 = split * steps_per_split, j1 = min(nT, j0 + steps_per_split);
 
-    // per row tile: row 16*(rt0 + qt) + lq of the K/V head = query row r of query head hq (rows past R repeat row 0
-    // of head 0 and are never stored)
-    bool row_ok[NT];
-    int lim[NT];
-    v4i qreg[NT][KC];
-    double cq[NT];
+    // ---- Q: row 16*(rt0 + qt) + lq of the K/V head = query row r of query head hq (rows past R repeat row 0 of head 0 and are
+    // never stored) ----
+    const auto q_row = [&](int ri) {
+        const int i = ri < R ? ri : 0;
+        return Q + (((size_t)b * Hq + kvh * group + i / Nq) * Nq + i % Nq) * D + g * 16;
+    };
+    const auto load_q = [&](uint4 (&x)[KC][2], int ri) {
+        const uint16_t *p = q_row(ri);
 #pragma unroll
-    for (int qt = 0; qt < NT; ++qt) {
-        const int ri = 16 * (rt0 + qt) + lq;
-        row_ok[qt] = ri < R;
-        const int hq = kvh * group + (row_ok[qt] ? ri / Nq : 0);
-        const int r = row_ok[qt] ? ri % Nq : 0;
-        lim[qt] = CAUSAL ? min(Nk - 1, r + shift) : Nk - 1;  // last visible key of this lane's row
-        // ---- Q: load 16-bit, quantise per head over its Nq rows (the stand-alone quantiser's binary32 steps on
-        // one block of Nq <= 64 rows: a head's rows are one Q quantisation block), straight into the B operand
-        // layout of the INT8 MFMA ----
-        const uint16_t *Qr = Q + (((size_t)b * Hq + hq) * Nq + r) * D;
-        uint4 qraw[KC][2];
+        for (int ch = 0; ch < KC; ++ch)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) x[ch][h] = *reinterpret_cast<const uint4 *>(p + ch * 64 + h * 8);
+    };
+    const auto max_q = [&](const uint4 (&x)[KC][2]) {
         float amax = 0.0f;
 #pragma unroll
         for (int ch = 0; ch < KC; ++ch)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                qraw[ch][h] = *reinterpret_cast<const uint4 *>(Qr + ch * 64 + g * 16 + h * 8);
-                const uint32_t u[4] = {qraw[ch][h].x, qraw[ch][h].y, qraw[ch][h].z, qraw[ch][h].w};
+                float f[8];
+                unpack8<BF16>(x[ch][h], f);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    amax = fmaxf(amax, fmaxf(fabsf(to_f32<BF16>(u[i] & 0xffffu)), fabsf(to_f32<BF16>(u[i] >> 16))));
+                for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(f[i]));
             }
-        // the head's maximum: this lane's channels of all Nq rows of its head (they may sit in another row tile),
-        // then over the four lanes that share the row
-        const uint16_t *Qhd = Q + ((size_t)b * Hq + hq) * Nq * D;
-        for (int rr = 0; rr < Nq; ++rr) {
-            if (rr == r) continue;
+        return rowgroup_max(amax);
+    };
+    uint4 qraw[NT][KC][2];
 #pragma unroll
-            for (int ch = 0; ch < KC; ++ch)
+    for (int qt = 0; qt < NT; ++qt) load_q(qraw[qt], 16 * (rt0 + qt) + lq);
+
+    // ---- copies global -> LDS: a half tile is 64 * D contiguous bytes of K^ or V^; 16-byte chunks swizzled for the operand reads.
+    // Half tile i of the range (i & 3: the two of K^, the two of V^ of a step) goes to slot i & 1.  The descriptor ends with the
+    // head's buffer: chunks beyond the last key are not fetched and read as zero.  Q is waited for first: behind the copies it would
+    // arrive with the last of them (1024 wavefronts x 2 steps, d 128: 18.5 -> 17.6 us). ----
+    int koff[NL], voff_[NL];
+    {
+        constexpr int CPR = D / 16;  // 16-byte chunks per K row
+        const int kr = lane / CPR, kc = lane % CPR, vr = lane >> 3, vc = lane & 7;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint4 x = *reinterpret_cast<const uint4 *>(Qhd + (size_t)rr * D + ch * 64 + g * 16 + h * 8);
-                    const uint32_t u[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        amax = fmaxf(amax, fmaxf(fabsf(to_f32<BF16>(u[i] & 0xffffu)), fabsf(to_f32<BF16>(u[i] >> 16))));
-                }
+        for (int p = 0; p < NL; ++p) {
+            koff[p] = kr * D + ((kc ^ k_swz<D>(kr)) << 4) + p * 1024;
+            voff_[p] = D == 128 ? koff[p] : vr * 128 + ((vc ^ (vr & 7)) << 4) + p * 1024;
         }
-        float a = rowgroup_max(amax);
+    }
+    const int ring = wave * (2 * HALF), ring_lds = lds_address(lds) + ring;
+    const int halves = 4 * (j1 - j0);
+    const auto copy_half = [&](int j, auto part_c, int i) {
+        constexpr int PART = decltype(part_c)::value;
+        if (i < halves) {
+            const int first = (j * 2 + (PART & 1)) * HALF;
+            const v4i r = PART < 2 ? lds_copy_rsrc(Kh + first, max(k_bytes - first, 0)) : lds_copy_rsrc(Vh + first, v_bytes - first);
+#pragma unroll
+            for (int p = 0; p < NL; ++p) lds_copy16(r, PART < 2 ? koff[p] : voff_[p], ring_lds + (PART & 1) * HALF + p * 1024);
+        }
+    };
+    constexpr std::integral_constant<int, 0> P0{};
+    constexpr std::integral_constant<int, 1> P1{};
+    constexpr std::integral_constant<int, 2> P2{};
+    constexpr std::integral_constant<int, 3> P3{};
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt)
+#pragma unroll
+        for (int ch = 0; ch < KC; ++ch)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(qraw[qt][ch][h].x), "+v"(qraw[qt][ch][h].y), "+v"(qraw[qt][ch][h].z), "+v"(qraw[qt][ch][h].w));
+    copy_half(j0, P0, 0);
+    copy_half(j0, P1, 1);
+    // half tile i has landed when at most the one behind it is outstanding
+    const auto landed = [&](int i) {
+        if (i + 1 < halves) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    const auto was_read = []() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+
+    // the maximum of every row of the K/V head (a head's rows may sit in another group's tiles), then quantisation per head over its
+    // Nq rows (the stand-alone quantiser's binary32 steps on one block of Nq <= 64 rows: a head's rows are one Q quantisation
+    // block), straight into the B operand layout of the INT8 MFMA
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt)
+        if (rt0 + qt < 4) row_max[wave][16 * (rt0 + qt) + lq] = max_q(qraw[qt]);
+    if (Nq > 1) {
+        for (int t = 0; t < T; ++t) {
+            if (t >= rt0 && t < rt0 + NT) continue;
+            uint4 x[KC][2];
+            load_q(x, 16 * t + lq);
+            row_max[wave][16 * t + lq] = max_q(x);
+        }
+    }
+    was_read();  // (a wavefront's own strip: no barrier)
+    v4i qreg[NT][KC];
+    double cq[NT];
+    int lim[NT];
+    bool row_ok[NT];
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) {
+        const int ri = 16 * (rt0 + qt) + lq, i0 = ri < R ? ri / Nq * Nq : 0;
+        row_ok[qt] = ri < R;
+        lim[qt] = causal ? min(Nk - 1, (row_ok[qt] ? ri % Nq : 0) + shift) : Nk - 1;  // last visible key of this lane's row
+        float a = 0.0f;
+        for (int r = 0; r < Nq; ++r) a = fmaxf(a, row_max[wave][i0 + r]);
         if (!row_ok[qt]) a = 0.0f;
         const float rcp = a > 0.0f ? 127.0f / a : 0.0f;
         cq[qt] = (double)(a / 127.0f) * (double)sm_scale * 1.4426950408889634;
@@ -105,31 +199,22 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void decode_kernel(const uint
         for (int ch = 0; ch < KC; ++ch)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const uint32_t u[4] = {qraw[ch][h].x, qraw[ch][h].y, qraw[ch][h].z, qraw[ch][h].w};
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) {
-                    uint32_t cb[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint32_t v = u[2 * hh + (i >> 1)];
-                        float y = to_f32<BF16>((i & 1) ? (v >> 16) : (v & 0xffffu)) * rcp;
-                        asm volatile("" : "+v"(y));  // keeps the product a rounded binary32 value (no FMA)
-                        cb[i] = __builtin_bit_cast(uint32_t, y + kMagicF);  // low byte = rne(y), two's complement
-                    }
-                    const uint32_t lo2 = __builtin_amdgcn_perm(cb[1], cb[0], 0x0c0c0400u);
-                    const uint32_t hi2 = __builtin_amdgcn_perm(cb[3], cb[2], 0x0c0c0400u);
-                    qreg[qt][ch][2 * h + hh] = (int)__builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
-                }
+                float f[8];
+                unpack8<BF16>(qraw[qt][ch][h], f);
+                const uint2 w = int8_codes(f, rcp);
+                qreg[qt][ch][2 * h] = (int)w.x;
+                qreg[qt][ch][2 * h + 1] = (int)w.y;
             }
     }
     const v4i cinit = {kMagic, kMagic, kMagic, kMagic};
 
-    // last visible key of the first / last row in use
-    const int lim_min = CAUSAL ? min(Nk - 1, shift) : Nk - 1;
-    const int lim_max = Nk - 1;
+    // last visible key of the first row in use (of the last one: Nk - 1)
+    const int lim_min = causal ? min(Nk - 1, shift) : Nk - 1;
 
-    float m[NT], l[NT];
+    float m[NT], l[NT], alpha[NT];
     v4f o[NT][CT];
+    v4i s[NT][8];
+    v8i pb[NT];
 #pragma unroll
     for (int qt = 0; qt < NT; ++qt) {
         m[qt] = -INFINITY;
@@ -138,80 +223,119 @@ __global__ __launch_bounds__(256, NT == 1 ? 2 : 1) void decode_kernel(const uint
         for (int ct = 0; ct < CT; ++ct) o[qt][ct] = v4f{0.f, 0.f, 0.f, 0.f};
     }
 
-    // K^ operand of step j: rows 16t + lq, 16-byte chunk 4ch + g (rows past the end are read from the last row
-    // and masked)
-    v4i ka[KC][8];
-    auto load_k = [&](int j) {
+    // operands: row 16t + lq, 16-byte chunk 4x + g, whose swizzled place is that of chunk g xor 64x bytes
+    const int kof = ring + k_off<D>(lq, g), vof = ring + v_off(lq, g);
+    const auto scores_of = [&](auto part_c) {  // S^T of 64 keys
+        constexpr int PART = decltype(part_c)::value;
+        v4i a[KC][4];
 #pragma unroll
         for (int ch = 0; ch < KC; ++ch)
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int row = min(j * kW + 16 * t + lq, Nk - 1);
-                ka[ch][t] = *reinterpret_cast<const v4i *>(Kh + (size_t)row * D + (4 * ch + g) * 16);
+            for (int t = 0; t < 4; ++t)
+                a[ch][t] = *reinterpret_cast<const v4i *>(lds + ((kof ^ 64 * ch) + (PART & 1) * HALF + t * 16 * D));
+        was_read();
+#pragma unroll
+        for (int ch = 0; ch < KC; ++ch)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int qt = 0; qt < NT; ++qt)
+                    s[qt][4 * PART + t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                        a[ch][t], qreg[qt][ch], ch == 0 ? cinit : s[qt][4 * PART + t], 0, 0, 0);
+    };
+    const auto output_of = [&](auto part_c) {  // O^T += V^T P^T of half the channels
+        constexpr int PART = decltype(part_c)::value;
+        v8i a[CT / 2];
+#pragma unroll
+        for (int c = 0; c < CT / 2; ++c) {
+            const uint8_t *p = lds + ((PART & 1) * HALF + c * 16 * 128);
+            const v4i lo = *reinterpret_cast<const v4i *>(p + vof), hi = *reinterpret_cast<const v4i *>(p + (vof ^ 64));
+            a[c] = v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        }
+        was_read();
+#pragma unroll
+        for (int c = 0; c < CT / 2; ++c)
+#pragma unroll
+            for (int qt = 0; qt < NT; ++qt) {
+                const int ct = (PART & 1) * (CT / 2) + c;
+                o[qt][ct] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[c], pb[qt], o[qt][ct], 0, 0, 0, 0, 0, 0);
             }
     };
-    if (j0 < j1) load_k(j0);
 
     for (int j = j0; j < j1; ++j) {
-        const int key0 = j * kW;
-        // V^ operand of this step: channel rows 16ct + lq of tile j, chunks g and 4 + g (consumed after the softmax)
-        v4i va[CT][2];
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            const uint8_t *vr = Vh + ((size_t)j * D + 16 * ct + lq) * 128;
-            va[ct][0] = *reinterpret_cast<const v4i *>(vr + g * 16);
-            va[ct][1] = *reinterpret_cast<const v4i *>(vr + (4 + g) * 16);
-        }
+        const int key0 = j * kW, i = 4 * (j - j0);
         const float dk0 = dk[(size_t)bhk * nKblk + min(2 * j, nKblk - 1)];
         const float dk1 = dk[(size_t)bhk * nKblk + min(2 * j + 1, nKblk - 1)];
-        const bool masked_step = (key0 + kW > Nk) || (CAUSAL && key0 + kW - 1 > lim_min);
+        landed(i);
+        scores_of(P0);
+        copy_half(j, P2, i + 2);
+        landed(i + 1);
+        scores_of(P1);
+        copy_half(j, P3, i + 3);
+
+        // ---- softmax step: every lane has the constants of its own row (its head's delta_Q) ----
+        const bool masked_step = (key0 + kW > Nk) || (causal && key0 + kW - 1 > lim_min);
         const int t_lo = min(8, max(0, (lim_min - key0 + 1) >> 4));
-        const int t_hi = min(8, max(0, ((lim_max - key0) >> 4) + 1));
+        const int t_hi = min(8, max(0, ((Nk - 1 - key0) >> 4) + 1));
 #pragma unroll
         for (int qt = 0; qt < NT; ++qt) {
-            // ---- S^T = K^ Q^T ----
-            v4i s[8];
-#pragma unroll
-            for (int ch = 0; ch < KC; ++ch)
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    s[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ka[ch][t], qreg[qt][ch], ch == 0 ? cinit : s[t], 0, 0, 0);
-            if (qt == NT - 1 && j + 1 < j1) load_k(j + 1);
-
-            // ---- softmax step: every lane has the constants of its own row (its head's delta_Q) ----
             const float c0 = (float)(cq[qt] * (double)dk0), c1 = (float)(cq[qt] * (double)dk1);
             const float kh0 = -kMagicF * c0, kh1 = -kMagicF * c1;
             const float kl0 = __builtin_fmaf(-kMagicF, c0, -kh0), kl1 = __builtin_fmaf(-kMagicF, c1, -kh1);
-            v8i pb;
-            float alpha;
             if (masked_step) {
                 const float l_old = l[qt];
-                alpha = softmax_step<true>(s, c0, c1, kh0, kh1, kl0, kl1, log2_pr, m[qt], l[qt], pb, key0 + 4 * g, lim[qt],
-                                           t_lo, t_hi);
+                alpha[qt] = softmax_step<true>(s[qt], c0, c1, kh0, kh1, kl0, kl1, log2_pr, m[qt], l[qt], pb[qt], key0 + 4 * g,
+                                               lim[qt], t_lo, t_hi);
                 // a row that has seen no key yet and sees none in this step keeps its empty state (the step's
                 // arithmetic on (-inf) - (-inf) is undefined; its P^ is zero either way)
                 if (lim[qt] < key0 && m[qt] == -INFINITY) {
-                    alpha = 1.0f;
+                    alpha[qt] = 1.0f;
                     l[qt] = l_old;
                 }
             } else {
-                alpha = softmax_step<false>(s, c0, c1, kh0, kh1, kl0, kl1, log2_pr, m[qt], l[qt], pb, 0, 0, 8, 8);
+                alpha[qt] = softmax_step<false>(s[qt], c0, c1, kh0, kh1, kl0, kl1, log2_pr, m[qt], l[qt], pb[qt], 0, 0, 8, 8);
             }
-
-            // ---- O^T = alpha O^T + V^T P^T ----
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+            if (__builtin_amdgcn_ballot_w64(alpha[qt] != 1.0f) != 0) {
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) o[qt][ct] *= alpha;
-            }
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                const v8i a = {va[ct][0][0], va[ct][0][1], va[ct][0][2], va[ct][0][3],
-                               va[ct][1][0], va[ct][1][1], va[ct][1][2], va[ct][1][3]};
-                o[qt][ct] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, pb, o[qt][ct], 0, 0, 0, 0, 0, 0);
+                for (int ct = 0; ct < CT; ++ct) o[qt][ct] *= alpha[qt];
             }
         }
+        landed(i + 2);
+        output_of(P2);
+        copy_half(j + 1, P0, i + 4);
+        landed(i + 3);
+        output_of(P3);
+        copy_half(j + 1, P1, i + 5);
     }
 
+    if constexpr (TOGETHER) {
+        // ---- the ranges' (m, l, acc) meet in LDS, in the place of the tiles ----
+        float *acc_lds = reinterpret_cast<float *>(lds);
+        __syncthreads();
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt) {
+            const float lsum = rowgroup_sum(l[qt]);
+            if (g == 0) ml_lds[wave][16 * qt + lq] = make_float2(m[qt], lsum);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+                *reinterpret_cast<float4 *>(acc_lds + (wave * ROWS + 16 * qt + lq) * LD + 16 * ct + 4 * g) =
+                    make_float4(o[qt][ct][0], o[qt][ct][1], o[qt][ct][2], o[qt][ct][3]);
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < R * (D / 4); e += blockDim.x) {
+            const int ri = e / (D / 4), quad = e % (D / 4), w0 = ri / ROWS, row = ri % ROWS;  // the row's ranges: wavefronts w0 + TW * p
+            float mx = ml_lds[w0][row].x;
+            for (int p = 1; p < S; ++p) mx = fmaxf(mx, ml_lds[w0 + TW * p][row].x);
+            float lt = 0.0f;
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int p = 0; p < S; ++p) {
+                const int w = w0 + TW * p;
+                add_range(ml_lds[w][row], *reinterpret_cast<const float4 *>(acc_lds + (w * ROWS + row) * LD + 4 * quad), mx, lt, acc);
+            }
+            store_quad<D, BF16>(acc, lt, dv, bhk, out, (b * Hq + kvh * group + ri / Nq) * Nq + ri % Nq, quad);
+        }
+        return;
+    }
     // ---- this range's (m, l, acc) of every row in use; l is the sum over the row's four lanes.  Partial rows are
     // indexed (((b*Hkv + kvh)*S + split)*T + row tile)*16 + lq ----
 #pragma unroll
@@ -251,18 +375,6 @@ __device__ __forceinline__ void partial_rows(int row, int Hq, int Hkv, int group
     }
 }
 
-// Epilogue of the prefill kernel on four channels: O = acc * (delta_V / l) (l carries the factor P_r), rounded to the output
-// type.
-template <int D, bool BF16>
-__device__ __forceinline__ void store_quad(const float4 &acc, float l, const float *__restrict__ dv, int bhk,
-                                           uint16_t *__restrict__ out, int row, int cq) {
-    const float inv = 1.0f / l;
-    const float4 sc = *reinterpret_cast<const float4 *>(dv + (size_t)bhk * D + 4 * cq);
-    const float y0 = acc.x * (sc.x * inv), y1 = acc.y * (sc.y * inv);
-    const float y2 = acc.z * (sc.z * inv), y3 = acc.w * (sc.w * inv);
-    *reinterpret_cast<uint2 *>(out + (size_t)row * D + 4 * cq) = make_uint2(pack2<BF16>(y0, y1), pack2<BF16>(y2, y3));
-}
-
 // Combine the S <= MAXS ranges of a row: m = max_s m_s, l = sum_s 2^(m_s - m) l_s, acc likewise.  Bound by memory (S * (D + 2)
 // floats read per row) or, with few rows, by its latency: a thread owns four channels of a row and fetches all ranges at
 // once; no LDS, no barrier, 256 / (D/4) rows per workgroup.  The additions are those of merge_kernel, whose range lanes hold one
@@ -292,30 +404,21 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float *__restrict_
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int s = 0; s < MAXS; ++s) {
-        if (s < S) {
-            // (each product is rounded before it is added, as where a range lane keeps it)
-            const float wgt = __builtin_amdgcn_exp2f(ml[s].x - mx);
-            l += __builtin_fmaf(wgt, ml[s].y, 0.0f);
-            acc.x += __builtin_fmaf(wgt, a[s].x, 0.0f);
-            acc.y += __builtin_fmaf(wgt, a[s].y, 0.0f);
-            acc.z += __builtin_fmaf(wgt, a[s].z, 0.0f);
-            acc.w += __builtin_fmaf(wgt, a[s].w, 0.0f);
-        }
+        if (s < S) add_range(ml[s], a[s], mx, l, acc);
     }
     store_quad<D, BF16>(acc, l, dv, bhk, out, row, cq);
 }
 
 // The same for any number of ranges.  One workgroup of 256 threads per row (grid B*Hq*Nq): thread t owns channels
 // 4*(t % (D/4)) .. +3 and the ranges t / (D/4), + 256/(D/4), ...; the shares are added in a fixed order through LDS, so the
-// result does not depend on timing.  (A row's ranges are read by many threads at once: with one thread walking them the launch
-// is a chain of S memory latencies.)
+// result does not depend on timing.  Bound by latency with few rows: one round trip to memory and one barrier up to 32 ranges (d = 64:
+// 64); with the maximum found through LDS first, nine barriers and a second round trip, 1.0 us more (8 heads x 4096 keys, 16 ranges).
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ part_acc, const float *__restrict__ part_ml,
                                                     const float *__restrict__ dv, uint16_t *__restrict__ out, int Hq,
                                                     int Hkv, int group, int Nq, int S, int T) {
     constexpr int Q4 = D / 4;      // channel quads
     constexpr int SL = 256 / Q4;   // range lanes
-    __shared__ float red[256];
     __shared__ float4 acc_s[SL][Q4];
     __shared__ float l_s[SL];
     const int row = blockIdx.x;  // (b*Hq + hq)*Nq + r
@@ -323,30 +426,38 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ pa
     size_t p0, ps;
     partial_rows(row, Hq, Hkv, group, Nq, S, T, bhk, p0, ps);
     const int tid = threadIdx.x, cq = tid % Q4, sl = tid / Q4;
-    // the row's maximum over all ranges
-    float mx = -INFINITY;
-    for (int s = tid; s < S; s += 256) mx = fmaxf(mx, part_ml[(p0 + s * ps) * 2]);
-    red[tid] = mx;
-    __syncthreads();
-    for (int k = 128; k >= 1; k >>= 1) {
-        if (tid < k) red[tid] = fmaxf(red[tid], red[tid + k]);
-        __syncthreads();
+    // this thread's first FIRST ranges and, for the row's maximum (every wavefront finds it itself), one m per lane: one round trip to
+    // memory up to FIRST * SL ranges
+    constexpr int FIRST = 4;
+    float2 ml[FIRST];
+    float4 a[FIRST];
+#pragma unroll
+    for (int k = 0; k < FIRST; ++k) {
+        const size_t p = p0 + min(sl + k * SL, S - 1) * ps;
+        ml[k] = *reinterpret_cast<const float2 *>(part_ml + p * 2);
+        a[k] = *reinterpret_cast<const float4 *>(part_acc + p * D + 4 * cq);
     }
-    mx = red[0];
+    float mx = -INFINITY;
+    for (int s = tid & 63; s < S; s += 64) mx = fmaxf(mx, part_ml[(p0 + s * ps) * 2]);
+    mx = wave_max(mx);
     float l = 0.0f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-    for (int s = sl; s < S; s += SL) {
-        const float2 ml = *reinterpret_cast<const float2 *>(part_ml + (p0 + s * ps) * 2);
-        const float4 a = *reinterpret_cast<const float4 *>(part_acc + (p0 + s * ps) * D + 4 * cq);
-        // a range in which the row saw no key has m = -inf, l = 0, acc = 0: its weight 2^(-inf) = 0 is exact
-        const float wgt = __builtin_amdgcn_exp2f(ml.x - mx);
-        l = __builtin_fmaf(wgt, ml.y, l);
-        acc.x = __builtin_fmaf(wgt, a.x, acc.x);
-        acc.y = __builtin_fmaf(wgt, a.y, acc.y);
-        acc.z = __builtin_fmaf(wgt, a.z, acc.z);
-        acc.w = __builtin_fmaf(wgt, a.w, acc.w);
-    }
+    // a range in which the row saw no key has m = -inf, l = 0, acc = 0: its weight 2^(-inf) = 0 is exact
+    const auto add = [&](const float2 &mls, const float4 &as) {
+        const float wgt = __builtin_amdgcn_exp2f(mls.x - mx);
+        l = __builtin_fmaf(wgt, mls.y, l);
+        acc.x = __builtin_fmaf(wgt, as.x, acc.x);
+        acc.y = __builtin_fmaf(wgt, as.y, acc.y);
+        acc.z = __builtin_fmaf(wgt, as.z, acc.z);
+        acc.w = __builtin_fmaf(wgt, as.w, acc.w);
+    };
+#pragma unroll
+    for (int k = 0; k < FIRST; ++k)
+        if (sl + k * SL < S) add(ml[k], a[k]);
+#pragma unroll 8
+    for (int s = sl + FIRST * SL; s < S; s += SL)
+        add(*reinterpret_cast<const float2 *>(part_ml + (p0 + s * ps) * 2),
+            *reinterpret_cast<const float4 *>(part_acc + (p0 + s * ps) * D + 4 * cq));
     acc_s[sl][cq] = acc;
     if (cq == 0) l_s[sl] = l;
     __syncthreads();
@@ -414,6 +525,27 @@ DecodeScratch decode_scratch_layout(void *base, int B, int Hkv, int Nk, int d, i
     return ws;
 }
 
+// Whether the ranges of a K/V head are one workgroup's.  Up to eight wavefronts fit a CU's registers and LDS, and the second launch is
+// saved (one workgroup / one wavefront per workgroup and a second launch, us: 16 heads x 1500 keys d 128 8.6 / 9.0, 64 x 256 6.3 / 8.1,
+// 150 x 4096 25.5 / 30.6; 64 rows per head, 256 x 2048 32.5 / 40.5), but half of the CUs or more have nothing to do with up to 128
+// heads.  That costs where they are needed: to stream a cache from HBM (128 x 32768 d 128 202 / 184, d 64 103 / 97; in the last-level
+// cache still ahead, 128 x 8192 40.3 / 44.0), and where the work of two row tiles adds up on one CU (32 rows, 8 x 2048 keys in 8
+// ranges 15.9 / 12.9, in 4 12.3 / 12.5; 64 rows, 16 x 700 17.4 / 13.5).
+bool decode_together(int groups, int S, int nt, int TW, int Nk, int d) {
+    if (TW * S > 8) return false;
+    if (groups > kCUs / 2) return true;
+    const bool in_cache = 2.0 * groups * Nk * d <= 256.0 * (1 << 20);
+    return nt == 1 ? in_cache : TW == 1 && S <= 4 && in_cache;
+}
+
+// Wavefronts of a workgroup where there is a second launch.  One: they start and end independently (64 heads x 32768 keys, d 128: 98 us
+// against 104 with four).  Four where two of them read the same tiles and there are many (64 rows, 64 x 16384: 71 / 95; 256
+// wavefronts, 16 x 2048: 16.1 / 14.4), and at d = 64 with a chip full of the shortest ranges (64 x 4096, 8 rows: 10.4 / 11.0).
+int decode_waves(int n_waves, int TW, int steps_per_split, int d) {
+    if (TW == 2) return n_waves > 2 * kCUs ? 4 : 1;
+    return d == 64 && steps_per_split <= 2 && n_waves >= 4 * kCUs ? 4 : 1;
+}
+
 hipError_t launch_decode(const void *q, const int8_t *k_i8, const uint8_t *v_fp8, const float *k_scale,
                          const float *v_scale, void *out, int B, int Hq, int Hkv, int Nq, int Nk, int d, bool causal,
                          float sm_scale, float p_r, int steps_per_split, bool bf16, hipStream_t stream,
@@ -426,27 +558,35 @@ hipError_t launch_decode(const void *q, const int8_t *k_i8, const uint8_t *v_fp8
     const int n_waves = B * Hkv * S * cdiv(T, nt);
     const float log2_pr = (float)log2((double)p_r);
     const uint16_t *q16 = static_cast<const uint16_t *>(q);
-#define SAGE_DEC(DD, C, BF)                                                                                       \
-    do {                                                                                                          \
-        if (nt == 1)                                                                                              \
-            decode_kernel<DD, C, BF, 1><<<cdiv(n_waves, 4), 256, 0, stream>>>(                                     \
-                q16, k_i8, v_fp8, k_scale, ws.part_acc, ws.part_ml, n_waves, Hq, Hkv, group, Nq, Nk, nT, nK, S, T, \
-                steps_per_split, sm_scale, log2_pr);                                                              \
-        else                                                                                                      \
-            decode_kernel<DD, C, BF, 2><<<cdiv(n_waves, 4), 256, 0, stream>>>(                                     \
-                q16, k_i8, v_fp8, k_scale, ws.part_acc, ws.part_ml, n_waves, Hq, Hkv, group, Nq, Nk, nT, nK, S, T, \
-                steps_per_split, sm_scale, log2_pr);                                                              \
+    const int groups = B * Hkv, TW = cdiv(T, nt);
+    const bool together = decode_together(groups, S, nt, TW, Nk, d);
+    const int waves = together ? TW * S : decode_waves(n_waves, TW, steps_per_split, d);  // of a workgroup
+    const int grid = together ? groups : cdiv(n_waves, waves);
+    uint16_t *o16 = static_cast<uint16_t *>(out);
+    const int tiles = waves * 128 * d;
+    const int lds_bytes = together ? std::max(tiles, waves * 16 * nt * (d + 4) * (int)sizeof(float)) : tiles;
+#define SAGE_DEC_N(DD, BF, NT, TG)                                                                                             \
+    decode_kernel<DD, BF, NT, TG><<<grid, 64 * waves, lds_bytes, stream>>>(                                                    \
+        q16, k_i8, v_fp8, k_scale, v_scale, o16, ws.part_acc, ws.part_ml, n_waves, Hq, Hkv, group, Nq, Nk, nT, nK, S, T,         \
+        steps_per_split, causal ? 1 : 0, sm_scale, log2_pr)
+#define SAGE_DEC_T(DD, BF, NT)                                                                    \
+    do {                                                                                           \
+        if (together) SAGE_DEC_N(DD, BF, NT, true); else SAGE_DEC_N(DD, BF, NT, false);             \
+    } while (0)
+#define SAGE_DEC(DD, BF)                                             \
+    do {                                                             \
+        if (nt == 1) SAGE_DEC_T(DD, BF, 1); else SAGE_DEC_T(DD, BF, 2); \
     } while (0)
     if (d == 128) {
-        if (causal) { if (bf16) SAGE_DEC(128, true, true); else SAGE_DEC(128, true, false); }
-        else        { if (bf16) SAGE_DEC(128, false, true); else SAGE_DEC(128, false, false); }
+        if (bf16) SAGE_DEC(128, true); else SAGE_DEC(128, false);
     } else {
-        if (causal) { if (bf16) SAGE_DEC(64, true, true); else SAGE_DEC(64, true, false); }
-        else        { if (bf16) SAGE_DEC(64, false, true); else SAGE_DEC(64, false, false); }
+        if (bf16) SAGE_DEC(64, true); else SAGE_DEC(64, false);
     }
 #undef SAGE_DEC
+#undef SAGE_DEC_T
+#undef SAGE_DEC_N
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_merge(ws, v_scale, out, B, Hq, Hkv, Nq, d, bf16, T, stream);
+    return e != hipSuccess || together ? e : launch_merge(ws, v_scale, out, B, Hq, Hkv, Nq, d, bf16, T, stream);
 }
 
 

@@ -96,9 +96,9 @@ hipError_t launch_spread(const void *q, bool q_raw, Strides q_st, const int8_t *
                          hipStream_t stream, int row_groups);
 
 // Decode-shaped attention (sage_decode.hip): (Hq/Hkv)*Nq <= 64 query rows per K/V head in T = ceil(rows/16) row
-// tiles, the keys cut into ranges of `steps_per_split` key steps; one wavefront per (batch, K/V head, range, row
-// tile) writes its (m, l, acc) per row into the scratch, a second launch combines the ranges.  q and out are
-// contiguous [B,Hq,Nq,d].
+// tiles, the keys cut into ranges of `steps_per_split` key steps; one wavefront per (batch, K/V head, range, one or two row
+// tiles).  The ranges of a K/V head are combined in the workgroup that holds them all, or every wavefront writes its (m, l, acc) per
+// row into the scratch and a second launch combines them.  q and out are contiguous [B,Hq,Nq,d].
 struct DecodeScratch {
     float *part_acc;  // [B*Hkv][S][T][16][d]  un-normalised outputs of every range
     float *part_ml;   // [B*Hkv][S][T][16][2]  running maximum and sum of every range

@@ -1,0 +1,63 @@
+"""sage_attn_fwd_decode in each of the shapes its launch can take -- the ranges of a K/V head in one workgroup or in workgroups of one
+or four wavefronts with a second launch, one or two row tiles per wavefront, one or two wavefronts per range, the last tiles ragged --
+against the oracle on the same ranges; and, on the CPU, the addresses of its copies into LDS."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import assert_parity
+from test_gpu_decode import _gpu, _inputs, _oracle
+
+FORMS = [  # B, Hq, Hkv, Nq, Nk, d, split_keys, heads compared
+    (1, 2, 2, 1, 1000, 128, 128, None),       # one workgroup of eight wavefronts (64 KB of LDS and more)
+    (1, 4, 4, 4, 1001, 64, 384, None),        # three
+    (1, 2, 2, 32, 500, 128, 128, None),       # two row tiles, one workgroup of four
+    (1, 2, 2, 32, 640, 128, 128, None),       # five ranges of two row tiles: a second launch
+    (1, 1, 1, 40, 300, 64, 128, None),        # three row tiles, two wavefronts per range, a second launch
+    (2, 260, 65, 16, 129, 64, 128, {(0, 0), (1, 64)}),    # 130 K/V heads of 64 rows: one workgroup of 2 x 2 wavefronts
+    (2, 65, 65, 49, 400, 128, 128, {(0, 0), (1, 64)}),    # 130 of 49 rows, 2 x 4 wavefronts: all of LDS
+    (1, 16, 16, 1, 8197, 64, 128, {(0, 0), (0, 15)}),     # 1040 wavefronts of one step, four to a workgroup, 65 ranges
+    (1, 8, 8, 64, 4700, 128, 128, {(0, 0), (0, 7)}),      # 592 wavefronts in pairs, four to a workgroup
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("B,Hq,Hkv,Nq,Nk,d,split,heads", FORMS)
+def test_decode_forms_against_the_oracle(B, Hq, Hkv, Nq, Nk, d, split, heads, causal):
+    q, k, v, sm = _inputs(5 if d == 128 else 1, B, Hq, Hkv, Nq, Nk, d)
+    out, _ = _gpu(q, k, v, causal, sm, split)
+    want = _oracle(q, k, v, causal, sm, split, heads=heads)
+    got = out.cpu().to(torch.float64).numpy()
+    assert np.isfinite(got).all()
+    g = Hq // Hkv
+    pick = [(b, h) for b in range(B) for h in range(Hq) if heads is None or (b, h // g) in heads]
+    w, x = (np.concatenate([t[b, h] for b, h in pick]) for t in (want, got))
+    assert_parity(w, x, "bf16" if q.dtype == torch.bfloat16 else "fp16", f"decode B{B} Hq{Hq}/{Hkv} Nq{Nq} Nk{Nk} d{d} {split}",
+                  flip_factor=4.0)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Nk", [1, 63, 64, 65, 127, 128, 129, 200, 1000])
+def test_half_tile_copies_stay_inside_the_buffer_and_cover_it(Nk, D):
+    """copy_half of decode_kernel: lane l of piece p fetches 16 bytes at voff[p] of a descriptor that begins with the half tile and ends
+    with the head's buffer (a chunk that does not fit is not fetched), and puts them at 1024 p + 16 l of the slot."""
+    half, lanes = 64 * D, np.arange(64)
+    nT = -(-Nk // 128)
+    for is_v in (False, True):
+        row_bytes = 128 if is_v else D
+        cpr = row_bytes // 16
+        row, c = lanes // cpr, lanes % cpr
+        swizzle = (lambda r: r & 7) if row_bytes == 128 else (lambda r: (r >> 1) & 3)
+        total = nT * D * 128 if is_v else Nk * D
+        for i in range(2 * nT):
+            first, src, dst = i * half, [], []
+            for p in range(half // 1024):
+                voff = row * row_bytes + ((c ^ swizzle(row)) << 4) + 1024 * p
+                ok = voff + 16 <= max(total - first, 0)
+                src.append(voff[ok])
+                dst.append((1024 * p + 16 * lanes)[ok])
+            src, dst = np.concatenate(src), np.concatenate(dst)
+            assert np.array_equal(np.sort(src), np.arange(0, min(half, max(total - first, 0)), 16)), (is_v, i)
+            r = src // row_bytes
+            assert np.array_equal(dst, r * row_bytes + (((src % row_bytes // 16) ^ swizzle(r)) << 4)), (is_v, i)
