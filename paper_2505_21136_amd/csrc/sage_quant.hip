@@ -561,6 +561,70 @@ __global__ __launch_bounds__(256) void zero_words_kernel(uint4 *w, int n) {
 }
 
 
+// Eight codes rint(x * rcp), one per byte: rint(y) for |y| <= 127 as the low byte of fl(y + 1.5 * 2^23) -- the addition rounds y to the
+// nearest integer, ties to even, and the sum's bit pattern is 0x4B400000 + that integer.
+__device__ __forceinline__ uint2 code_bytes(const float (&x)[8], float rcp) {
+    uint32_t cb[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) cb[j] = __builtin_bit_cast(uint32_t, x[j] * rcp + 12582912.0f);
+    uint32_t w[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t lo = __builtin_amdgcn_perm(cb[4 * h + 1], cb[4 * h], 0x0c0c0400u);
+        const uint32_t hi = __builtin_amdgcn_perm(cb[4 * h + 3], cb[4 * h + 2], 0x0c0c0400u);
+        w[h] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    }
+    return make_uint2(w[0], w[1]);
+}
+
+// Maximum over the wavefront of a value >= 0 (not NaN), in every lane: within rows of 16 lanes by DPP, then over the four rows, whose
+// bit patterns order like integers, in scalar registers.
+__device__ __forceinline__ float wave_max_abs(float x) {
+#define SAGE_DPP(CTRL) \
+    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true)))
+    SAGE_DPP(0xb1);   // quad_perm [1,0,3,2]
+    SAGE_DPP(0x4e);   // quad_perm [2,3,0,1]
+    SAGE_DPP(0x141);  // row_half_mirror
+    SAGE_DPP(0x140);  // row_mirror
+#undef SAGE_DPP
+    const int b = __builtin_bit_cast(int, x);
+    const int lo = max(__builtin_amdgcn_readlane(b, 0), __builtin_amdgcn_readlane(b, 16));
+    const int hi = max(__builtin_amdgcn_readlane(b, 32), __builtin_amdgcn_readlane(b, 48));
+    return __builtin_bit_cast(float, max(lo, hi));
+}
+
+// The FP8 codes of 8 channels of the keys 16t + 4g + i (raw[4t + i], t, i < 4) of a half tile: for each channel the 16 bytes at
+// `dst` + 128 * channel, straight from the thread that has the keys: with the key quads of a thread chosen like this
+// no transposition through LDS is needed (dwords written there by lanes of neighbouring channels fall on one bank).
+template <bool BF16>
+__device__ __forceinline__ void v_codes(const uint4 (&raw)[16], const float (&rc)[8], uint8_t *dst) {
+#pragma unroll
+    for (int j2 = 0; j2 < 4; ++j2) {  // two channels (one packed dword of each key) at a time
+        uint32_t w[2][4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            float y[4][2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint4 &x = raw[4 * t + i];
+                const uint32_t w16 = j2 == 0 ? x.x : j2 == 1 ? x.y : j2 == 2 ? x.z : x.w;
+                y[i][0] = to_f32<BF16>(w16 & 0xffffu) * rc[2 * j2];
+                y[i][1] = to_f32<BF16>(w16 >> 16) * rc[2 * j2 + 1];
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                int c = 0;
+                c = __builtin_amdgcn_cvt_pk_fp8_f32(y[0][e], y[1][e], c, false);
+                c = __builtin_amdgcn_cvt_pk_fp8_f32(y[2][e], y[3][e], c, true);
+                w[e][t] = (uint32_t)c;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            *reinterpret_cast<uint4 *>(dst + (2 * j2 + e) * 128) = make_uint4(w[e][0], w[e][1], w[e][2], w[e][3]);
+    }
+}
+
 // The packed rows stay packed between the passes over them: without this the compiler keeps the unpacked
 // floats of one pass alive for the next (twice the registers of the packed rows).
 __device__ __forceinline__ void keep_packed(uint4 (&raw)[16]) {
@@ -625,7 +689,7 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
     static_assert(C == resident_tokens(NTHR, D), "the host counts the same tokens");
     __shared__ __attribute__((aligned(16))) unsigned char smem[NTHR * 64];
     __shared__ float stat[D];           // the head's mean (K) or V_r / max (V)
-    __shared__ float wmax[NW][C / kBK];  // per wavefront and K block: max |K'|
+    __shared__ __attribute__((aligned(16))) float wmax[C / kBK][NW];  // per K block and wavefront: max |K'|
 
     if constexpr (WITH_Q) {
         if ((int)blockIdx.x >= q.first) {
@@ -757,80 +821,81 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
         }
         __syncthreads();
 
-        // ---- codes: the quantiser of quant_int8_body on the resident rows, one K block after the other; the
-        // smoothed values of a block stay in registers between its maximum and its codes ----
+        // ---- codes: the quantiser of quant_int8_body on the resident rows, one K block after the other, the smoothed values of a block in
+        // registers between its maximum and its codes.  With 16 blocks (512 threads, d = 64) the maxima of all of them come first: one
+        // barrier instead of 16, the smoothed values are made twice (128 heads x 1024 tokens 19.4 -> 16.5 us; with 4 or 8 blocks
+        // up to 1.5 % slower) ----
         constexpr int NB = C / kBK;    // K blocks of the chunk
         constexpr int IPB = kBK / RP;  // passes per block
+        constexpr bool ALL_MAXIMA = NB >= 16 && !WITH_Q;
         constexpr float kRange = (float)QMAX;
         float mu[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) mu[j] = stat[co * 8 + j];
         keep_packed(raw);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int blk = part * NB + b;  // (workgroup-uniform)
-            if (blk >= nK) break;
-            float x[IPB][8];
-            float a = 0.0f;
+        float x[IPB][8];
+        const auto smooth = [&](int b) {
 #pragma unroll
             for (int i = 0; i < IPB; ++i) {
-                float f[8];
-                unpack8<BF16>(raw[b * IPB + i], f);
+                unpack8<BF16>(raw[b * IPB + i], x[i]);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[i][j] = f[j] - mu[j];
+                for (int j = 0; j < 8; ++j) x[i][j] = x[i][j] - mu[j];
+            }
+        };
+        const auto block_max = [&](int b) {  // this wavefront's part of it goes to LDS
+            float a = 0.0f;
+#pragma unroll
+            for (int i = 0; i < IPB; ++i)
                 if (b * IPB + i < nrow) {  // rows past the end do not count
 #pragma unroll
                     for (int j = 0; j < 8; ++j) a = fmaxf(a, fabsf(x[i][j]));
                 }
+            a = wave_max_abs(a);
+            if ((tid & 63) == 0) wmax[b][tid >> 6] = a;
+        };
+        if constexpr (ALL_MAXIMA) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                smooth(b);
+                block_max(b);
             }
+            __syncthreads();
+            keep_packed(raw);
+        }
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) a = fmaxf(a, __shfl_xor(a, off));
-            if ((tid & 63) == 0) wmax[tid >> 6][b] = a;
-            __syncthreads();  // (every block has its own column of wmax: one barrier per block)
-            a = fmaxf(fmaxf(wmax[0][b], wmax[1][b]), fmaxf(wmax[2][b], wmax[3][b]));
+        for (int b = 0; b < NB; ++b) {
+            const int blk = part * NB + b;  // (workgroup-uniform)
+            if (blk >= nK) break;
+            smooth(b);
+            if constexpr (!ALL_MAXIMA) {
+                block_max(b);
+                __syncthreads();  // (every block has its own row of wmax: one barrier per block)
+            }
+            float a = wmax[b][0];
 #pragma unroll
-            for (int w = 4; w < NW; ++w) a = fmaxf(a, wmax[w][b]);
+            for (int w = 1; w < NW; ++w) a = fmaxf(a, wmax[b][w]);
             const float rcp = a > 0.0f ? kRange / a : 0.0f;
             if (tid == 0) k_scale[(size_t)bh * nK + blk] = a / kRange;
 #pragma unroll
             for (int i = 0; i < IPB; ++i) {
                 const int it = b * IPB + i;
                 const int r = row0 + it * RP + rr;
-                if (it < nrow) {
-                    // rint(y) for |y| <= 127 as the low byte of fl(y + 1.5 * 2^23): the addition rounds y to the
-                    // nearest integer, ties to even, and the sum's bit pattern is 0x4B400000 + that integer
-                    uint32_t cb[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) cb[j] = __builtin_bit_cast(uint32_t, x[i][j] * rcp + 12582912.0f);
-                    uint32_t w[2];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const uint32_t lo = __builtin_amdgcn_perm(cb[4 * h + 1], cb[4 * h], 0x0c0c0400u);
-                        const uint32_t hi = __builtin_amdgcn_perm(cb[4 * h + 3], cb[4 * h + 2], 0x0c0c0400u);
-                        w[h] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-                    }
-                    *reinterpret_cast<uint2 *>(k_codes + ((size_t)bh * N + r) * D + co * 8) = make_uint2(w[0], w[1]);
-                }
+                if (it < nrow) *reinterpret_cast<uint2 *>(k_codes + ((size_t)bh * N + r) * D + co * 8) = code_bytes(x[i], rcp);
             }
         }
     } else {
-        // ---- V: a thread owns four units of 4 consecutive keys x 8 channels (quant_v_body); the workgroup converts and
-        // transposes TP tiles at a time, UPT units per thread ----
-        constexpr int UNITS = 32 * LPR;  // per 128-key tile
-        constexpr int UPT = UNITS > NTHR ? UNITS / NTHR : 1, TP = UNITS > NTHR ? 1 : NTHR / UNITS;
-        constexpr int ROUNDS = C / kW / TP;
-        static_assert(ROUNDS * UPT * 4 == NU, "a workgroup's chunk is 16 uint4 per thread");
-        static_assert(TP * D * 128 <= NTHR * 64, "the tiles fit in LDS");
+        // ---- V: a thread owns 8 channels of the keys 16t + 4g + i (t, i < 4) of a half tile of 64, whose codes are 16 adjacent bytes
+        // of each channel's row ----
         const uint16_t *Vh = V + (bh / H) * v_st.b + (bh % H) * v_st.h;
-        // this thread's rows are row0 + rr * 4 + 4 * RP * (q >> 2) + (q & 3), q = 0 .. 15
-        uint32_t exists = 0u;
+        const int half = rr >> 2, g = rr & 3;
+        uint32_t exists = 0u;  // bit q = 4t + i
         {
             const uint16_t *last = Vh + (int64_t)(N - 1) * v_st.n + co * 8;
-            const int rbase = row0 + rr * 4;
+            const int rbase = row0 + 64 * half + 4 * g;
             const uint16_t *p = Vh + (int64_t)rbase * v_st.n + co * 8;
 #pragma unroll
             for (int q = 0; q < NU; ++q) {
-                const int dr = 4 * RP * (q >> 2) + (q & 3);
+                const int dr = 16 * (q >> 2) + (q & 3);
                 const bool ok = rbase + dr < N;
                 exists |= (ok ? 1u : 0u) << q;
                 raw[q] = *reinterpret_cast<const uint4 *>(ok ? p + dr * v_st.n : last);
@@ -931,48 +996,204 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j) rc[j] = stat[co * 8 + j];
         keep_packed(raw);
-        uint32_t *tile = reinterpret_cast<uint32_t *>(smem);  // TP tiles of D * 32 dwords
+        const int T = (row0 + 64 * half) >> 7;
+        if (T < nT)
+            v_codes<BF16>(raw, rc, Vt + (((size_t)bh * nT + T) * D + co * 8) * 128 + 64 * (half & 1) + 16 * g);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Two launches for small calls: partial column statistics of the chunks that the single-read kernel's workgroups of 256 threads would
+// hold, then codes in workgroups of one K block or V tile that add the head's partials themselves.  Nothing is cleared, nobody
+// waits for anybody, and there are many times as many workgroups; the tokens are read a second time (from the caches, in a
+// small call) and every workgroup of a head reads its G partials.
+// ---------------------------------------------------------------------------
+constexpr int kChunkThreads = 512;
+template <int D>
+constexpr int chunk_tokens() {
+    return resident_tokens(256, D);
+}
+
+// Grid: B*H*G workgroups per tensor (K and V groups in turn, or one tensor alone), then those of Q: two blocks each.
+template <bool BF16, int D>
+__global__ __launch_bounds__(kChunkThreads) void chunk_stats_kernel(const uint16_t *__restrict__ K, Strides k_st,
+                                                                   const uint16_t *__restrict__ V, Strides v_st, int H, int N, int G,
+                                                                   double *__restrict__ k_sum_part, float *__restrict__ v_max_part,
+                                                                   int tensors, QuantQ q) {
+    constexpr int LPR = D / 8, RP = kChunkThreads / LPR, C = chunk_tokens<D>(), NU = C / RP;
+    constexpr int SHARES = kChunkThreads / D, RS = RP / SHARES;  // threads that share a channel, rows of partial sums each adds
+    __shared__ __attribute__((aligned(16))) double smem[RP * D];
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= q.first) {
+        const int team = tid >> 8, wgs = (q.n_blocks + 1) / 2, x = blockIdx.x - q.first;
+        quant_int8_body<BF16, D, kBQ, 0, 127>(q.x, q.st, H, nullptr, q.codes, q.scale, N, q.n_blocks,
+                                              reinterpret_cast<float *>(smem) + 4 * team, x / wgs, x % wgs * 2 + team, tid & 255);
+        return;
+    }
+    const int grp = blockIdx.x / G, part = blockIdx.x % G;
+    const int bh = tensors == kBothTensors ? grp >> 1 : grp;
+    const bool is_v = tensors == kBothTensors ? grp & 1 : tensors == kOnlyV;  // (workgroup-uniform)
+    const int co = tid % LPR, rr = tid / LPR;
+    const Strides st = is_v ? v_st : k_st;
+    const uint16_t *X = (is_v ? V : K) + (bh / H) * st.b + (bh % H) * st.h + co * 8;
+    uint4 raw[NU];
 #pragma unroll
-        for (int rd = 0; rd < ROUNDS; ++rd) {
-            const int T = (part * ROUNDS + rd) * TP;  // (workgroup-uniform) first tile of the round
-            if (T >= nT) break;
+    for (int it = 0; it < NU; ++it)
+        raw[it] = *reinterpret_cast<const uint4 *>(X + (int64_t)min(part * C + it * RP + rr, N - 1) * st.n);
 #pragma unroll
-            for (int k = 0; k < UPT; ++k) {
-                const int u = tid + NTHR * k;
-                const int kq = (u % UNITS) / LPR;
-                const int t = kq >> 2, g = kq & 3;
-                uint32_t *my_tile = tile + (u / UNITS) * D * 32;
-                // two channels (one packed dword of each of the four keys) at a time; rows >= N hold zeros
+    for (int it = 0; it < NU; ++it)  // (rows past the end change neither a sum nor a maximum of |.|)
+        if (part * C + it * RP + rr >= N) raw[it] = make_uint4(0u, 0u, 0u, 0u);
+    const int c = tid % D, share = tid / D;
+    const size_t o = ((size_t)bh * G + part) * D + c;
+    if (!is_v) {
+        double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int j2 = 0; j2 < 4; ++j2) {
-                    float y[4][2];
+        for (int it = 0; it < NU; ++it) {
+            float f[8];
+            unpack8<BF16>(raw[it], f);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint4 &x = raw[(rd * UPT + k) * 4 + i];
-                        const uint32_t w16 = j2 == 0 ? x.x : j2 == 1 ? x.y : j2 == 2 ? x.z : x.w;
-                        y[i][0] = to_f32<BF16>(w16 & 0xffffu) * rc[2 * j2];
-                        y[i][1] = to_f32<BF16>(w16 >> 16) * rc[2 * j2 + 1];
-                    }
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const int j = 2 * j2 + e;
-                        int w = 0;
-                        w = __builtin_amdgcn_cvt_pk_fp8_f32(y[0][e], y[1][e], w, false);
-                        w = __builtin_amdgcn_cvt_pk_fp8_f32(y[2][e], y[3][e], w, true);
-                        my_tile[(co * 8 + j) * 32 + (t >> 2) * 16 + g * 4 + (t & 3)] = (uint32_t)w;
-                    }
-                }
-            }
-            __syncthreads();
-            uint4 *dst = reinterpret_cast<uint4 *>(Vt + ((size_t)bh * nT + T) * D * 128);
-            const uint4 *src = reinterpret_cast<const uint4 *>(tile);
-#pragma unroll
-            for (int k = 0; k < TP * D * 8 / NTHR; ++k) {
-                const int e = tid + NTHR * k;
-                if (TP == 1 || T + e / (D * 8) < nT) dst[e] = src[e];
-            }
-            __syncthreads();
+            for (int j = 0; j < 8; ++j) acc[j] += (double)f[j];
         }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) smem[rr * D + co * 8 + j] = acc[j];
+        __syncthreads();
+        double a = smem[share * RS * D + c];
+#pragma unroll
+        for (int i = 1; i < RS; ++i) a += smem[(share * RS + i) * D + c];
+        __syncthreads();
+        smem[tid] = a;
+        __syncthreads();
+        if (share == 0) {
+#pragma unroll
+            for (int k = 1; k < SHARES; ++k) a += smem[k * D + c];
+            k_sum_part[o] = a;
+        }
+    } else {
+        float *sm = reinterpret_cast<float *>(smem);
+        float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int it = 0; it < NU; ++it) {
+            float f[8];
+            unpack8<BF16>(raw[it], f);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] = fmaxf(acc[j], fabsf(f[j]));
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sm[rr * D + co * 8 + j] = acc[j];
+        __syncthreads();
+        float a = sm[share * RS * D + c];
+#pragma unroll
+        for (int i = 1; i < RS; ++i) a = fmaxf(a, sm[(share * RS + i) * D + c]);
+        __syncthreads();
+        sm[tid] = a;
+        __syncthreads();
+        if (share == 0) {
+#pragma unroll
+            for (int k = 1; k < SHARES; ++k) a = fmaxf(a, sm[k * D + c]);
+            v_max_part[o] = a;
+        }
+    }
+}
+
+// Grid (nK + chunks of V, B*H): K blocks, then V chunks (either count may be 0).
+template <bool BF16, int D, int QMAX>
+__global__ __launch_bounds__(256) void chunk_codes_kernel(const uint16_t *__restrict__ K, Strides k_st,
+                                                          const uint16_t *__restrict__ V, Strides v_st, int H, int N, int G,
+                                                          const double *__restrict__ k_sum_part,
+                                                          const float *__restrict__ v_max_part, float *__restrict__ k_mean,
+                                                          float *__restrict__ v_scale, float v_r, int8_t *__restrict__ k_codes,
+                                                          float *__restrict__ k_scale, int nK, uint8_t *__restrict__ Vt, int nT) {
+    constexpr int LPR = D / 8, RP = 256 / LPR, SHARES = 256 / D;
+    __shared__ double part_sum[256];
+    __shared__ float stat[D], wmax[4];
+    const int tid = threadIdx.x, bh = blockIdx.y, x = blockIdx.x;  // (workgroup-uniform branch)
+    const int co = tid % LPR, rr = tid / LPR, c = tid % D, share = tid / D;
+    if (x < nK) {
+        constexpr int ITER = kBK / RP;
+        constexpr float kRange = (float)QMAX;
+        const uint16_t *Kh = K + (bh / H) * k_st.b + (bh % H) * k_st.h + co * 8;
+        const int row0 = x * kBK + rr;
+        uint4 raw[ITER];  // (in flight under the partials)
+#pragma unroll
+        for (int it = 0; it < ITER; ++it)
+            raw[it] = *reinterpret_cast<const uint4 *>(Kh + (int64_t)min(row0 + it * RP, N - 1) * k_st.n);
+        double s = 0.0;
+        for (int i0 = share; i0 < G; i0 += 8 * SHARES) {
+            double t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = k_sum_part[((size_t)bh * G + min(i0 + u * SHARES, G - 1)) * D + c];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u * SHARES < G) s += t[u];
+        }
+        part_sum[tid] = s;
+        __syncthreads();
+        if (share == 0) {
+#pragma unroll
+            for (int k = 1; k < SHARES; ++k) s += part_sum[k * D + c];
+            const float mu = (float)(s / (double)N);
+            if (x == 0) k_mean[(size_t)bh * D + c] = mu;
+            stat[c] = mu;
+        }
+        __syncthreads();
+        float y[ITER][8], a = 0.0f;
+#pragma unroll
+        for (int it = 0; it < ITER; ++it) {
+            unpack8<BF16>(raw[it], y[it]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[it][j] = y[it][j] - stat[co * 8 + j];
+            if (row0 + it * RP < N) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a = fmaxf(a, fabsf(y[it][j]));
+            }
+        }
+        a = wave_max_abs(a);
+        if ((tid & 63) == 0) wmax[tid >> 6] = a;
+        __syncthreads();
+        a = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+        const float rcp = a > 0.0f ? kRange / a : 0.0f;
+        if (tid == 0) k_scale[(size_t)bh * nK + x] = a / kRange;
+#pragma unroll
+        for (int it = 0; it < ITER; ++it) {
+            const int r = row0 + it * RP;
+            if (r < N)
+                *reinterpret_cast<uint2 *>(k_codes + ((size_t)bh * N + r) * D + co * 8) = code_bytes(y[it], rcp);
+        }
+    } else {
+        const int row0 = (x - nK) * chunk_tokens<D>(), half = rr >> 2, g = rr & 3;
+        const uint16_t *Vh = V + (bh / H) * v_st.b + (bh % H) * v_st.h + co * 8;
+        uint4 raw[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int r = row0 + 64 * half + 4 * g + 16 * (q >> 2) + (q & 3);
+            raw[q] = *reinterpret_cast<const uint4 *>(Vh + (int64_t)min(r, N - 1) * v_st.n);
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (row0 + 64 * half + 4 * g + 16 * (q >> 2) + (q & 3) >= N) raw[q] = make_uint4(0u, 0u, 0u, 0u);
+        float a = 0.0f;
+        for (int i0 = share; i0 < G; i0 += 8 * SHARES) {
+            float t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = v_max_part[((size_t)bh * G + min(i0 + u * SHARES, G - 1)) * D + c];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a = fmaxf(a, t[u]);  // (a partial taken twice does not change a maximum)
+        }
+        float *part_max = reinterpret_cast<float *>(part_sum);
+        part_max[tid] = a;
+        __syncthreads();
+        if (share == 0) {
+#pragma unroll
+            for (int k = 1; k < SHARES; ++k) a = fmaxf(a, part_max[k * D + c]);
+            if (x == nK) v_scale[(size_t)bh * D + c] = a / v_r;
+            stat[c] = a > 0.0f ? v_r / a : 0.0f;
+        }
+        __syncthreads();
+        float rc[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) rc[j] = stat[co * 8 + j];
+        const int T = (row0 + 64 * half) >> 7;
+        if (T < nT) v_codes<BF16>(raw, rc, Vt + (((size_t)bh * nT + T) * D + co * 8) * 128 + 64 * (half & 1) + 16 * g);
     }
 }
 
@@ -991,21 +1212,21 @@ hipError_t quant_q_impl(const uint16_t *q, Strides st, int8_t *q_i8, float *q_sc
     return hipGetLastError();
 }
 
-// Threads of the single-read kernel's workgroups; 0: three launches.  G: workgroups of 256 threads that a head of one tensor takes
-// (256 tokens each at d = 128, 512 at d = 64); `groups`: heads times tensors.  Every figure: three launches / 256 / 512 threads, us.
+// Threads of the single-read kernel's workgroups; 0: three launches.  (Small calls do not come here: chunks_pay.)  G: workgroups of 256
+// threads that a head of one tensor takes (256 tokens each at d = 128, 512 at d = 64); `groups`: heads times tensors.  Every figure:
+// three launches / 256 / 512 threads, us.
 //   * With few partners two workgroups of 256 are the better neighbours of a CU.  A group of many wants large ones, half as many
 //     partials to wait for and read: at d = 128 from about 96 on (K and V, H 8, G 64 34 / 29.6 / 28.9, G 80 39 / 38.6 / 40.6, G 128
 //     57 / 56 / 52; H 16, G 128 118 / 120 / 107).  At d = 64 a partial covers twice the tokens and 256 stays ahead up to 128
 //     (H 8, G 96 43.5 / 42.6 / 46.5, G 128 55 / 51 / 55; H 3, N 24578 16.8 with 256, 21.5 with 512).
-//   * Two workgroups of 256 that become one of 512 have nobody to meet and nothing to clear (d = 128, H 8 11.6 / 11.7 / 10.0; d = 64
-//     only where the heads fill the CUs: H 8 10.7 / 13.6 / 13.4, H 128 19.2 / 17.6 / 16.2).
+//   * Two workgroups of 256 that become one of 512 have nobody to meet and nothing to clear (d = 128, H 128 15.6 with 512, 20.9 in three
+//     launches; d = 64, H 128 20.2 / 17.6 / 16.2).
 //   * Beyond 128 workgroups of 256 only those of 512 come into question.  512 of those are resident at once; a second round that is
 //     partly empty costs what the second read of the three launches does (d = 128, K and V, H 4, G 160, 640 workgroups
 //     39.8 / - / 43.3; H 4, G 256, 1024 57.7 / - / 54.2; H 1, G 160, 160 24.1 / - / 19.2;
 //     inputs that are not in the last-level cache: H 4, G 192 50.8 / - / 50.9, H 8, G 192, 1536 102 / - / 90).
 //   * K or V alone: three short launches are independent of each other's workgroups, where the single read has a clear and
-//     a meeting, 3 to 4 us that a small call does not win back (d = 64, K, H 4, N 4000 11.1 / 14.3; V, H 8, G 12 10.9 / 11.7,
-//     G 24 13.4 / 12.0; d = 128, K, H 1, G 128 16.3 / 17.2 / 17.5).  With Q in the same launch the workgroups of Q fill that time.
+//     a meeting, 3 to 4 us that fewer workgroups than fill the chip do not win back (d = 128, K, H 1, G 128 16.3 / 17.2 / 17.5).
 enum class Quantise { kBoth, kOnlyK, kOnlyV, kKWithQ };
 inline int resident_threads(Quantise what, int groups, int N, int d) {
     const int path = g_kv_path.load();
@@ -1014,30 +1235,54 @@ inline int resident_threads(Quantise what, int groups, int N, int d) {
     if (path == 1) return 0;
     if (path == 2) return G == 2 || G > (d == 128 ? 96 : 128) ? 512 : 256;
     if (G == 1) return 256;
+    if (G == 2) return 512;
     if (G > kResidentMaxGroup) return 0;
     if (d == 128) {
-        if (G == 2) return 512;
         if (G <= 96) return 256;
-        if (what == Quantise::kKWithQ) return 512;
-        if (wgs512 < kCUs / 2) return G <= 128 && what != Quantise::kOnlyK ? 256 : 0;
-        return G > 128 && wgs512 > 2 * kCUs && wgs512 < 4 * kCUs ? 0 : 512;
+        if (what == Quantise::kOnlyK && wgs512 < kCUs / 2) return 0;
+        return what != Quantise::kKWithQ && G > 128 && wgs512 > 2 * kCUs && wgs512 < 4 * kCUs ? 0 : 512;
     }
     switch (what) {
-        case Quantise::kOnlyK:
-            if (G == 2) return groups >= kCUs / 2 ? 512 : 0;
-            return G <= 128 && ((wgs >= kCUs && G <= 48) || wgs >= 2 * kCUs) ? 256 : 0;
-        case Quantise::kOnlyV:
-            if (G == 2) return 512;
-            if (G <= 128) return wgs >= 3 * kCUs / 4 ? 256 : 0;
-            return wgs512 >= kCUs / 2 ? 512 : 0;
-        case Quantise::kKWithQ:
-            if (G == 2) return 512;
-            return G <= 128 && wgs >= 3 * kCUs / 8 ? 256 : 0;
-        default:
-            if (G == 2) return groups >= kCUs / 4 ? 512 : 256;
-            if (G <= 128) return 256;
-            return wgs512 >= 4 * kCUs ? 512 : 0;
+        case Quantise::kOnlyK: return G <= 128 && (G <= 48 || wgs >= 2 * kCUs) ? 256 : 0;
+        case Quantise::kOnlyV: return G <= 128 ? 256 : wgs512 >= kCUs / 2 ? 512 : 0;
+        case Quantise::kKWithQ: return G <= 128 ? 256 : 0;
+        default: return G <= 128 ? 256 : wgs512 >= 4 * kCUs ? 512 : 0;
     }
+}
+
+// Whether the two launches over chunks are the fastest form.  They are while the workgroups leave CUs idle, where the single read is a
+// clear, a meeting and a chain of K blocks; beyond, the second read costs more.  G as above, wgs: workgroups of 256 threads per
+// tensor.  Single read (or three launches) / two, us: K and V, d = 128, H 2, G 4 12.1 / 8.2, G 63 15.1 / 13.8, H 8, G 16 14.0 / 10.9, G 32
+// (256 workgroups) 18.4 / 20.0; d = 64, H 2, G 4 13.7 / 8.1, H 32, G 4 14.2 / 12.3.  A head that one workgroup holds meets nobody: K and V,
+// G 1 7.4 / 7.8.  K alone d = 128, H 8, G 32 14.3 / 12.5, H 32, G 16 (512) 18.7 / 19.0; d = 64, H 2, G 1 8.5 / 6.7, H 128, G 2 13.4 / 12.5.
+// V alone G 2 7.0 / 7.5, H 32, G 4 10.7 / 8.2, G 16 (512) 16.4 / 13.9, H 32, G 32 (1024) 24.7 / 29.2.  K with Q, d = 128, H 2, G 4
+// 12.0 / 8.6, H 32, G 4 13.4 / 12.1, H 8, G 32 17.1 / 18.3, H 64, G 2 (300 tokens; the single read meets nobody) 9.5 / 10.0; d = 64,
+// H 32, G 1 8.8 / 7.2.  Every workgroup of a head reads the G partials: K alone, d = 64, H 2, G 118 16.4 / 17.6.
+inline bool chunks_pay(Quantise what, int heads, int N, int d) {
+    if (g_kv_path.load() != 0) return false;
+    const int G = resident_group_size(N, d, 256);
+    const long wgs = (long)heads * G;
+    if (G == 1) return d == 64 && (what == Quantise::kOnlyK || what == Quantise::kKWithQ) && heads <= kCUs / 4;
+    switch (what) {
+        case Quantise::kOnlyK: return wgs <= kCUs / 2 || (wgs <= kCUs && G <= 64);
+        case Quantise::kOnlyV: return G > 2 && wgs <= 2 * kCUs;
+        default: return wgs <= (G == 2 ? kCUs / 4 : kCUs / 2);
+    }
+}
+
+// The outputs in two launches (chunk_stats_kernel, chunk_codes_kernel).
+template <bool BF16, int D, int QMAX>
+hipError_t launch_chunks(const uint16_t *k, Strides k_st, const uint16_t *v, Strides v_st, int8_t *k_i8, float *k_scale, float *k_mean,
+                         uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H, int N, hipStream_t stream, const QuantScratch &ws,
+                         int tensors, QuantQ q = QuantQ{}) {
+    const int G = resident_group_size(N, D, 256);
+    const int nK = tensors == kOnlyV ? 0 : cdiv(N, kBK), nV = tensors == kOnlyK ? 0 : G;
+    q.first = (tensors == kBothTensors ? 2 * BH : BH) * G;
+    chunk_stats_kernel<BF16, D><<<q.first + (q.x ? BH * cdiv(q.n_blocks, 2) : 0), kChunkThreads, 0, stream>>>(
+        k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, tensors, q);
+    chunk_codes_kernel<BF16, D, QMAX><<<dim3(nK + nV, BH), 256, 0, stream>>>(
+        k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, cdiv(N, kW));
+    return hipGetLastError();
 }
 
 // The outputs from one read of the tensors (quant_kv_resident_kernel).
@@ -1089,7 +1334,11 @@ hipError_t launch_resident(int threads, const uint16_t *k, Strides k_st, const u
 template <bool BF16, int D>
 hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_scale, float *k_mean, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws, const QuantQ &q) {
-    const int threads = resident_threads(q.x ? Quantise::kKWithQ : Quantise::kOnlyK, BH, N, D);
+    const Quantise what = q.x ? Quantise::kKWithQ : Quantise::kOnlyK;
+    if (chunks_pay(what, BH, N, D))
+        return launch_chunks<BF16, D, 127>(k, st, nullptr, st, k_i8, k_scale, k_mean, nullptr, nullptr, 1.0f, BH, H, N, stream, ws,
+                                           kOnlyK, q);
+    const int threads = resident_threads(what, BH, N, D);
     if (threads && resident_group_size(N, D, 256) <= kResidentMaxGroup)
         return launch_resident<BF16, D, 127>(threads, k, st, nullptr, st, k_i8, k_scale, k_mean, nullptr, nullptr, 0.0f, BH, H, N,
                                              stream, ws, kOnlyK, q);
@@ -1106,6 +1355,9 @@ hipError_t quant_k_impl(const uint16_t *k, Strides st, int8_t *k_i8, float *k_sc
 template <bool BF16, int D>
 hipError_t quant_v_impl(const uint16_t *v, Strides st, uint8_t *v_fp8, float *v_scale, float v_r, int BH, int H,
                         int N, hipStream_t stream, const QuantScratch &ws) {
+    if (chunks_pay(Quantise::kOnlyV, BH, N, D))
+        return launch_chunks<BF16, D, 127>(nullptr, st, v, st, nullptr, nullptr, nullptr, v_fp8, v_scale, v_r, BH, H, N, stream, ws,
+                                           kOnlyV);
     const int threads = resident_threads(Quantise::kOnlyV, BH, N, D);
     if (threads && resident_group_size(N, D, 256) <= kResidentMaxGroup)
         return launch_resident<BF16, D, 127>(threads, nullptr, st, v, st, nullptr, nullptr, nullptr, v_fp8, v_scale, v_r, BH, H, N,
@@ -1211,11 +1463,14 @@ hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v
     const uint16_t *k16 = static_cast<const uint16_t *>(k), *v16 = static_cast<const uint16_t *>(v);
     const int BH = B * H;
     const int threads = resident_threads(Quantise::kBoth, 2 * BH, N, d);
+    const bool chunks = chunks_pay(Quantise::kBoth, BH, N, d);
 #define SAGE_KV(BF, DD, QM)                                                                                           \
-    (threads ? launch_resident<BF, DD, QM>(threads, k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, \
-                                           BH, H, N, stream, ws, kBothTensors)                                       \
-             : quant_kv_impl<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, \
-                                          stream, ws))
+    (chunks    ? launch_chunks<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, \
+                                           stream, ws, kBothTensors)                                                  \
+     : threads ? launch_resident<BF, DD, QM>(threads, k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, \
+                                             BH, H, N, stream, ws, kBothTensors)                                      \
+               : quant_kv_impl<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, \
+                                           stream, ws))
     if (int4) {
         if (d == 128) return bf16 ? SAGE_KV(true, 128, 7) : SAGE_KV(false, 128, 7);
         return bf16 ? SAGE_KV(true, 64, 7) : SAGE_KV(false, 64, 7);

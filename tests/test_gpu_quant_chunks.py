@@ -1,0 +1,38 @@
+"""The quantisers' two launches over chunks (small calls), at the edges of chunks, K blocks and V tiles, up to the largest calls that
+take them: K and V together, each alone, K with Q, the INT4 codes and strided inputs write the bits of the three launches, and the codes
+of Q those of a launch of its own."""
+import pytest
+import torch
+
+import paper_2505_21136_amd as sage
+from gpu_util import say
+from test_gpu_quant_paths import THREE_LAUNCHES, _against_oracle, _inputs, _quant, _restore_default_path, _same_bits  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# a chunk is 256 tokens at d = 128 and 512 at d = 64
+SHAPES = [(1, (1, 2, 257, 128)), (2, (1, 3, 512, 128)), (5, (1, 2, 513, 128)), (1, (2, 2, 1024, 128)), (5, (1, 1, 1089, 128)),
+          (2, (1, 1, 32768, 128)), (5, (1, 2, 16129, 128)), (2, (1, 128, 769, 128)),
+          (4, (1, 2, 200, 64)), (3, (1, 2, 512, 64)), (4, (2, 3, 513, 64)), (3, (1, 2, 1537, 64)), (4, (1, 32, 2048, 64)),
+          (3, (1, 64, 300, 64))]
+
+
+@pytest.mark.parametrize("idx,shape", SHAPES)
+def test_chunks_write_the_bits_of_the_three_launches(idx, shape):
+    say(f"[quant chunks] cfg{idx} distributions, shape {shape}")
+    k, v = _inputs(idx, shape)
+    want = _quant(k, v, 4.5, THREE_LAUNCHES)
+    want4 = sage.sage_quant_kv4(k, v)  # (the three launches still forced)
+    got = _quant(k, v, 4.5, 0)
+    _same_bits(want, got, "K and V together")
+    _same_bits(want4, sage.sage_quant_kv4(k, v), "INT4 codes")
+    _same_bits(want, sage.sage_quant_k(k) + sage.sage_quant_v(v, 4.5), "each alone")
+    q_i8, k_i8, q_scale, k_scale, k_mean = sage.sage_quant_qk(v, k)
+    _same_bits(want[:3] + sage.sage_quant_q(v), (k_i8, k_scale, k_mean, q_i8, q_scale), "K with Q")
+    # token-major views, through the call that quantises strided inputs
+    out = sage.sage_attn_fwd(v, k, v, causal=False)
+    q_t, k_t, v_t = (x.transpose(1, 2).contiguous() for x in (v, k, v))
+    out_t = sage.sage_attn_fwd_strided(q_t, k_t, v_t, causal=False, layout="bnhd")
+    assert torch.equal(out.view(torch.int16), out_t.transpose(1, 2).view(torch.int16))
+    if shape[1] * shape[2] <= 3000:
+        _against_oracle(got, k, v, 4.5, shape[2])
