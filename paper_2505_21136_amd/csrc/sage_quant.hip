@@ -680,7 +680,7 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
     const uint16_t *__restrict__ K, Strides k_st, const uint16_t *__restrict__ V, Strides v_st, int H, int N, int G,
     double *k_sum_part, float *v_max_part, float *k_mean, float *v_scale, float v_r,
     int8_t *__restrict__ k_codes, float *__restrict__ k_scale, int nK, uint8_t *__restrict__ Vt, int nT,
-    long long wait_ticks, int tensors, QuantQ q) {
+    long long wait_ticks, int stagger, int tensors, QuantQ q) {
     constexpr int NU = 16;                       // uint4 per thread
     constexpr int NW = NTHR / 64;                // wavefronts
     constexpr int LPR = D / 8;                   // lanes per row
@@ -700,6 +700,14 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
                                                   x / wgs, x % wgs * TEAMS + team, threadIdx.x & 255);
             return;
         }
+    }
+    // Workgroups of one round load, meet and store together, so that the memory rests while they meet.  In launches of at least two rounds
+    // those that come second, third and fourth to their CU start later, `stagger` ticks of the 100 MHz clock each, and the phases
+    // of a CU's workgroups stay apart.  (us without / with: 128 heads x 4096, d 128 87.6 / 83.6; 48 x 17776, d 64 74.5 / 72.2; with 512
+    // threads, two to a CU, 24 x 32768 136 / 132.  Half and twice the step are worse.)
+    if (stagger && (int)blockIdx.x < kCUs * (1024 / NTHR)) {
+        const long long start = wall_clock64() + (long long)(blockIdx.x / kCUs) * stagger;
+        while (wall_clock64() < start) __builtin_amdgcn_s_sleep(4);
     }
     const int grp = blockIdx.x / G, part = blockIdx.x % G;
     const int bh = tensors == kBothTensors ? grp >> 1 : grp;
@@ -1303,10 +1311,11 @@ hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v,
         zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(static_cast<uint4 *>(from), words);
     }
     q.first = (tensors == kBothTensors ? 2 * BH : BH) * G;
+    const int stagger = q.first < 2 * kCUs * (1024 / NTHR) ? 0 : NTHR == 256 ? 400 : 700;
 #define SAGE_RESIDENT(Q, GRID)                                                                                          \
     quant_kv_resident_kernel<BF16, D, QMAX, NTHR, Q><<<GRID, NTHR, 0, stream>>>(                                        \
         k, k_st, v, v_st, H, N, G, ws.k_sum_part, v_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT,     \
-        wait_ticks, tensors, q)
+        wait_ticks, stagger, tensors, q)
     if constexpr (QMAX == 127) {
         if (q.x) {
             SAGE_RESIDENT(true, q.first + BH * cdiv(q.n_blocks, NTHR / 256));
