@@ -16,15 +16,23 @@
 // 16-byte chunks XOR-swizzled against bank conflicts (with a period of 8 rows, which leaves the 32-row operand reads two-way
 // conflicts: 128 of 388 LDS cycles per step; LDS is 17 % busy and hardly waited for).
 //
-// Schedule.  What bounds the kernel is the issue port of the vector ALU, which softmax arithmetic and MFMA issue
-// share (per score one conversion, one FMA, one addition, one exponential, half an FP8 pack, half a max3).  Counters (64 scores per
-// lane and step): 389 vector instructions, port 87 % busy at d = 128 (1 head x 32768 x 24, 1.95 GHz under this load); 386 and 100 % at
-// d = 64 (2.1 GHz); causal rows of 4096 keys 477 and 81 %, the difference being the rescaling of O.  A wavefront's matrix work
+// Schedule.  What bounds the kernel is the issue of vector instructions and, at d = 128, the power the chip may draw (the clock
+// floats: 2.07 GHz with d = 128, 2.2 to 2.3 with d = 64, of 2.4).  Per score one conversion, one FMA, one addition, one exponential, half an FP8 pack, half a
+// max3; 389 vector instructions per step of 64 scores per lane at d = 128 (1 head x 32768 x 24), 386 at d = 64, causal rows of 4096 keys 477, the
+// difference being the rescaling of O.  Measured with single instructions on every SIMD: two wavefronts issue one instruction each per 4
+// cycles if one of them is an FP32 add, multiply or FMA (or a move or an integer addition); conversions and maxima take 4 alone or beside one of those; an
+// exponential or an FP8 pack takes 8 and nothing issues beside it, nor while the matrix pipe works on an MFMA.  A
+// wavefront's matrix work
 // therefore runs INSIDE its own vector work, software-pipelined over the key steps: while the scores of step j turn
 // into P^, the freed score registers already receive Q K^T of step j+1, and the P^ V^ product of step j-1 runs under
 // the maximum and the first exponentials of step j.  The step is cut into slots of about 18 vector instructions with
 // one or two MFMAs each (sched_barrier keeps the compiler from moving work between slots): a wavefront that
 // issues an MFMA while the matrix pipe is busy waits, and nothing behind it can issue.  One barrier per step.
+// RAISE: left alone the wavefronts of a SIMD take turns, one's exponentials against another's additions, and nothing is issued together
+// (64 scores: 1664 cycles).  With the priority raised around the exponentials and packs, and the MFMAs issued first thing in there, the
+// rest of two wavefronts meets: 1360 cycles without MFMAs, 1480 against 1860 with 16.  In this kernel, d = 64: 1904 -> 1821 cycles per step and
+// SIMD at the same clock with the MFMAs behind the exponentials, and with them in front 24 heads x 16384 1282 -> 1233 us, 9 x 8192 171 -> 158; d = 128, 10 x 4480 rows 7 % less, full
+// chip 1 % (the clock falls with every cycle saved).  raise_pays has the rule.
 // The accumulator is rescaled only in steps after which some row maximum has moved (multiplying by 1 is the identity).
 #include "sage_attn_device.h"
 #include "sage_internal.h"
@@ -58,10 +66,11 @@ constexpr int prefill_waves_per_simd() {
 // Q4 (with QRAW): the 4+8 variant.  K^ holds INT4 codes (one per byte), Q is smoothed by its block means `q_mean`, and the
 // score correction `dsx` ((qbar . K'[n]) * sm_scale * log2(e), one float per key and Q block) is added to the scores: the
 // maximum is taken on the finished exponents x = c * S + ds in FP32.
+// RAISE: see above; masked steps and the 4+8 variant without.
 // SPLIT (with QRAW, without Q4): the key steps are cut into `n_splits` ranges of `steps_per_split` steps and the grid holds
 // one workgroup per (head, query tile, range), which runs the recurrence on its range alone and writes (m, l, acc) per row
 // to `part_ml` / `part_acc` ([item][range][128 rows][2] and [...][D] floats); merge_kernel (sage_decode.hip) combines them.
-template <int D, bool CAUSAL, bool BF16, bool QRAW, bool Q4, bool SPLIT>
+template <int D, bool CAUSAL, bool BF16, bool QRAW, bool Q4, bool SPLIT, bool RAISE>
 __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefill_kernel(
     const void *__restrict__ Qsrc, const int8_t *__restrict__ Kc, const uint8_t *__restrict__ Vt,
     const float *__restrict__ dq, const float *__restrict__ dk, const float *__restrict__ dv,
@@ -368,25 +377,49 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
         return m_new;
     };
     // P^ of the four keys 32t + 8b + 4h .. + 3, and their share of the key tile's sum.  mo = log2 P_r - m.
-    const auto exp_quad = [&](auto masked, int t, int b, float cb, float mo, float &lsum0, float &lsum1)
+    // `matrix` issues what the matrix pipe does meanwhile.
+    const auto exp_quad = [&](auto masked, int t, int b, float cb, float mo, float &lsum0, float &lsum1, auto matrix)
                               __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked)::value;
+        constexpr bool UP = RAISE && !MASKED;
         float p[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int sbits = s[t][4 * b + i];
-            p[i] = __builtin_amdgcn_exp2f(Q4 ? __builtin_bit_cast(float, sbits) + mo : __builtin_fmaf((float)sbits, cb, mo));
-            if constexpr (MASKED && !Q4) p[i] = sbits == INT_MIN ? 0.0f : p[i];
+            p[i] = Q4 ? __builtin_bit_cast(float, sbits) + mo : __builtin_fmaf((float)sbits, cb, mo);
         }
-        lsum0 += p[0] + p[1];
-        lsum1 += p[2] + p[3];
+        if constexpr (UP) {
+            asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+            matrix();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(p[i]);
+            if constexpr (MASKED && !Q4) p[i] = s[t][4 * b + i] == INT_MIN ? 0.0f : p[i];
+        }
+        if constexpr (!UP) {
+            lsum0 += p[0] + p[1];
+            lsum1 += p[2] + p[3];
+        }
         int w;  // both halves are overwritten below: an opaque undefined seed saves the v_mov of a zero
         asm volatile("" : "=v"(w));
         w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], w, false);
         w = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
+        if constexpr (UP) {
+            asm volatile("" : "+v"(w));
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            lsum0 += p[0] + p[1];
+            lsum1 += p[2] + p[3];
+        }
         // (pinned to their place: nothing else keeps the arithmetic from sinking to its use a step later)
         asm volatile("" : "+v"(w), "+v"(lsum0), "+v"(lsum1));
         pb[t >> 1][4 * (b & 1) + 2 * (t & 1) + (b >> 1)] = w;
+        if constexpr (!UP) matrix();
     };
 
     // One key step without a mask: P^ of step j from its scores, with P^V^ of step j-1 and Q.K^T of step j+1 in between.
@@ -426,24 +459,21 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
         constexpr int SPT = 4 / KC;  // slots per Q.K^T MFMA (1 at d = 128, 2 at d = 64)
 #pragma unroll
         for (int sl = 0; sl < 16; ++sl) {
-            exp_quad(no_mask, sl >> 2, sl & 3, sl < 8 ? cc.x : cc.y, mo, lsum0, lsum1);
             // P^V^ of the last 64 keys of step j-1 in the slots of the first two tiles (their registers are rewritten by the
             // last two)
             constexpr int EVERY = 8 / CT;
+            const bool pv = sl < 8 && sl % EVERY == EVERY - 1, qk = sl >= 4 && sl % SPT == 0;
+            const int r = CT + sl / EVERY, n = (sl - 4) / SPT;
+            exp_quad(no_mask, sl >> 2, sl & 3, sl < 8 ? cc.x : cc.y, mo, lsum0, lsum1, [&]() __attribute__((always_inline)) {
+                if (pv) mfma_pv(vf[r % VA], r);
+                if (qk) mfma_qk(kf[n % KA], n);
+            });
             if ((sl & 3) == 3) {
                 l[sl >> 2] = __builtin_fmaf(l[sl >> 2], alpha, lsum0 + lsum1);
                 lsum0 = lsum1 = -0.0f;
             }
-            if (sl < 8 && sl % EVERY == EVERY - 1) {
-                const int r = CT + sl / EVERY;
-                mfma_pv(vf[r % VA], r);
-                if (r + VA < NPV) vf[r % VA] = read_v(par, r + VA);
-            }
-            if (sl >= 4 && sl % SPT == 0) {
-                const int n = (sl - 4) / SPT;
-                mfma_qk(kf[n % KA], n);
-                if (n + KA < NQK) kf[n % KA] = read_k(par, n + KA);
-            }
+            if (pv && r + VA < NPV) vf[r % VA] = read_v(par, r + VA);
+            if (qk && n + KA < NQK) kf[n % KA] = read_k(par, n + KA);
             if (sl < NP) copy_k(j + 2, sl);
             if (sl == NP) copy_ds(j + 1);
             __builtin_amdgcn_sched_barrier(0);
@@ -493,7 +523,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
             float lsum0 = -0.0f, lsum1 = -0.0f;
             if (t < t_hi) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) exp_quad(mask, t, b, t < 2 ? cc.x : cc.y, mo, lsum0, lsum1);
+                for (int b = 0; b < 4; ++b) exp_quad(mask, t, b, t < 2 ? cc.x : cc.y, mo, lsum0, lsum1, []() {});
             } else {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) pb[t >> 1][4 * (b & 1) + 2 * (t & 1) + (b >> 1)] = 0;
@@ -588,6 +618,23 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
+// Whether the exponentials run at raised priority (RAISE).  That pays while a SIMD has two wavefronts or more and costs a lone one 5 to
+// 8 % (32 switches per step), so it depends on the last round of workgroups.  Measured, speed with / without:
+//   * up to one workgroup per CU 0.93 (32 heads x 1024, causal 0.93 to 0.95);
+//   * d = 128, two workgroups per CU, rounds of 512: the last one more than half full or full 1.08 .. 1.02 (257 .. 512 workgroups), 1.04 (808
+//     .. 832), 1.02 (1296 .. 1363), 1.00 (2445 .. 2496, 6144); less than half full 0.94 (544 .. 612), 0.97 (1044 .. 1136), 0.98 (1584 ..
+//     1776), 0.99 (2050 .. 2752);
+//   * d = 64, three per CU: 1.06 .. 1.10 up to 748, 0.98 .. 1.01 in 780 .. 952, 1.02 .. 1.05 from 1178 on (6144: 1.06);
+//   * causal calls end on lone wavefronts: d = 64 0.92 .. 0.96 at 1280 .. 1920 workgroups, 1.00 .. 1.06 from 1980 on, d = 128 0.94 .. 1.006
+//     up to 4096.  Key ranges do not (512 workgroups: d = 128 1.02, d = 64 1.06).
+bool raise_pays(int wgs, int d, bool causal, bool ranges) {
+    if (wgs <= kCUs) return false;
+    if (causal && !ranges) return d == 64 && wgs >= 8 * kCUs;
+    if (d == 64) return wgs <= 3 * kCUs || wgs > 4 * kCUs;
+    const int last = wgs % (2 * kCUs);
+    return wgs <= 8 * kCUs && (last == 0 || last > kCUs);
+}
+
 template <int D>
 hipError_t launch_prefill_d(const void *q, bool q_raw, Strides q_st, const int8_t *k_i8, const uint8_t *v_fp8,
                             const float *q_scale, const float *k_scale, const float *v_scale, void *out, Strides o_st, int B,
@@ -598,16 +645,23 @@ hipError_t launch_prefill_d(const void *q, bool q_raw, Strides q_st, const int8_
     const dim3 grid(B * Hq * nQ * n_splits);  // (at most 65535 * 32768 < 2^31 workgroups; ranges only for small calls)
     uint16_t *o16 = static_cast<uint16_t *>(out);
     const bool q4 = dsx != nullptr, ranges = part_acc != nullptr;
-#define SAGE_LAUNCH(C, BF, QR, F4, SP)                                                                               \
-    prefill_kernel<D, C, BF, QR, F4, SP><<<grid, 256, 0, stream>>>(                                                   \
+    const bool raise = raise_pays((int)grid.x, D, causal, ranges);
+#define SAGE_LAUNCH(C, BF, QR, F4, SP, RS)                                                                           \
+    prefill_kernel<D, C, BF, QR, F4, SP, RS><<<grid, 256, 0, stream>>>(                                               \
         q, k_i8, v_fp8, q_scale, k_scale, v_scale, o16, q_st, o_st, Nq, Nk, nT, nQ, nK, Hq, Hq / Hkv, sm_scale,      \
         log2_pr, q_mean, dsx, n_splits, steps_per_split, part_acc, part_ml)
-#define SAGE_LAUNCH_Q(C, BF)                                          \
-    do {                                                              \
-        if (ranges) SAGE_LAUNCH(C, BF, true, false, true);            \
-        else if (q4) SAGE_LAUNCH(C, BF, true, true, false);           \
-        else if (q_raw) SAGE_LAUNCH(C, BF, true, false, false);       \
-        else SAGE_LAUNCH(C, BF, false, false, false);                 \
+#define SAGE_LAUNCH_R(C, BF, QR, SP, CAN)                          \
+    do {                                                           \
+        if (raise) SAGE_LAUNCH(C, BF, QR, false, SP, CAN);         \
+        else SAGE_LAUNCH(C, BF, QR, false, SP, false);             \
+    } while (0)
+#define SAGE_LAUNCH_Q(C, BF)                                                     \
+    do {                                                                         \
+        constexpr bool CAN = D == 64 || !C;                                      \
+        if (ranges) SAGE_LAUNCH_R(C, BF, true, true, true);                      \
+        else if (q4) SAGE_LAUNCH(C, BF, true, true, false, false);               \
+        else if (q_raw) SAGE_LAUNCH_R(C, BF, true, false, CAN);                  \
+        else SAGE_LAUNCH_R(C, BF, false, false, CAN);                            \
     } while (0)
     if (causal) {
         if (bf16) SAGE_LAUNCH_Q(true, true); else SAGE_LAUNCH_Q(true, false);
@@ -615,6 +669,7 @@ hipError_t launch_prefill_d(const void *q, bool q_raw, Strides q_st, const int8_
         if (bf16) SAGE_LAUNCH_Q(false, true); else SAGE_LAUNCH_Q(false, false);
     }
 #undef SAGE_LAUNCH_Q
+#undef SAGE_LAUNCH_R
 #undef SAGE_LAUNCH
     return hipGetLastError();
 }
