@@ -155,43 +155,58 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
         for (int ch = 0; ch < KC; ++ch) f[ch] = *reinterpret_cast<const v4i *>(lds + (j & 3) * TILE + (kof ^ (32 * ch)));
     };
     v4i k0[KC], k1[KC], kf[KC];  // kf: K^ of the step whose scores are made next
-    const auto first_tiles = [&]() {
+    const auto first_tiles = [&](auto also) {
         lds_barrier();  // P0
         read_k(k0, 0);
         read_k(k1, 1);
         read_k(kf, 2);
+        also();
         lds_barrier();  // P1
     };
     if constexpr (QRAW) {
+        // All loads are of whole rows (a lane of the operand's layout wants a row of its own: 64 cycles of the texture path per
+        // load instead of 16, 4096 of them for the two groups of loads below at d = 128): the workgroup's own rows, which go to the
+        // wavefronts through LDS, and the whole block for its maximum.  2 heads x 1024 x 1024, d = 128 10.5 -> 9.5 us, 64 x 128 x 128 6.8 -> 5.7.
         const uint16_t *Qh = static_cast<const uint16_t *>(Qsrc) + (bh / Hq) * q_st.b + (bh % Hq) * q_st.h;
-        // for the maximum, wavefront w of a row group looks at the w-th 32 rows of the block, all channels or (RG = 2) half
-        constexpr int KO = KC / RG;
-        uint4 qraw[KC][2], other[KO][2];
-        const int orow = qblk * kBQ + w4 * 32 + lq;
-        const uint16_t *Qo = Qh + min(orow, Nq - 1) * q_st.n + rg * KO * 32 + h * 16;
-        const uint16_t *Qr = Qh + min(qrow, Nq - 1) * q_st.n + h * 16;
+        constexpr int RC = D / 8, SW = RC - 1;  // 16-byte chunks per row, and the swizzle's mask
+        constexpr int OWN = ROWS * RC / (64 * NC), ALL = kBQ * RC / (64 * NC);
+        static_assert(ROWS * D * 2 <= (int)sizeof(p_lds), "the rows wait where P^ goes later");
+        uint8_t *q_lds = &p_lds[0][0];
+        uint4 own[OWN], all[ALL];
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
+        for (int x = 0; x < OWN; ++x) {
+            const int e = 64 * NC * x + tid;
+            own[x] = *reinterpret_cast<const uint4 *>(Qh + min(tile * ROWS + e / RC, Nq - 1) * q_st.n + e % RC * 8);
+        }
 #pragma unroll
-            for (int ch = 0; ch < KO; ++ch) other[ch][e] = *reinterpret_cast<const uint4 *>(Qo + ch * 32 + e * 8);
+        for (int x = 0; x < ALL; ++x) {
+            const int e = 64 * NC * x + tid;
+            all[x] = *reinterpret_cast<const uint4 *>(Qh + min(qblk * kBQ + e / RC, Nq - 1) * q_st.n + e % RC * 8);
+        }
 #pragma unroll
-            for (int ch = 0; ch < KC; ++ch) qraw[ch][e] = *reinterpret_cast<const uint4 *>(Qr + ch * 32 + e * 8);
+        for (int x = 0; x < OWN; ++x) {
+            const int e = 64 * NC * x + tid, row = e / RC, c = e % RC;
+            *reinterpret_cast<uint4 *>(q_lds + row * D * 2 + ((c ^ (row & SW)) << 4)) = own[x];
         }
         float amax = 0.0f;
 #pragma unroll
-        for (int ch = 0; ch < KO; ++ch)
+        for (int x = 0; x < ALL; ++x) {  // (rows past the end repeat the last one, which the block has, too)
+            float f[8];
+            unpack8<BF16>(all[x], f);
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                float f[8];
-                unpack8<BF16>(other[ch][e], f);
-                if (orow < Nq) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(f[i]));
-                }
-            }
+            for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(f[i]));
+        }
         amax = wave_max(amax);
         if (lane == 0) q_wave_max[wave] = amax;
-        first_tiles();
+        uint4 qraw[KC][2];
+        first_tiles([&]() {
+            const int row = rg * 32 + lq;
+#pragma unroll
+            for (int ch = 0; ch < KC; ++ch)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    qraw[ch][e] = *reinterpret_cast<const uint4 *>(q_lds + row * D * 2 + (((4 * ch + 2 * h + e) ^ (row & SW)) << 4));
+        });
         float rcp;
         delta_q = block_scale(rcp);
 #pragma unroll
@@ -209,7 +224,7 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
                            min(qrow, Nq - 1) * q_st.n;
 #pragma unroll
         for (int ch = 0; ch < KC; ++ch) qreg[ch] = *reinterpret_cast<const v4i *>(Qr + ch * 32 + h * 16);
-        first_tiles();
+        first_tiles([]() {});
         float rcp;
         delta_q = block_scale(rcp);
     }
