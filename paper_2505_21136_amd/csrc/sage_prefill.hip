@@ -171,24 +171,35 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
         for (int k = 0; k < NP; ++k) copy_k(jb, k);
         copy_ds(jb);
     }
-    // the first step's "P^ V^ of the step before" multiplies zeros: its V^ buffer must hold numbers
-#pragma unroll
-    for (int k = 0; k < TILE / 4096; ++k)
-        *reinterpret_cast<uint4 *>(lds + (2 + ((jb + 1) & 1)) * TILE + k * 4096 + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
-
     // the lane's B operand of S^T = K^ Q^T: 16 consecutive channels (32*ch + 16*h ..) of query row lq
     v4i qreg[KC];
     uint4 qraw[KC][2];  // QRAW: the same 16 channels as 16-bit values
     const int qrow = row0 + lq;
     if constexpr (QRAW) {
-        const uint16_t *Qr = static_cast<const uint16_t *>(Qsrc) + (bh / Hq) * q_st.b + (bh % Hq) * q_st.h + qrow * q_st.n;
+        // The wavefront's 32 rows come as whole rows (a load in the operand's layout, a row per lane, costs the texture path 64 cycles
+        // instead of 16) and change lanes in LDS, in the wavefront's own strip of what will be the V^ buffers.  Rows past the end repeat
+        // the last one, which is in the block, too.
+        const uint16_t *Qh = static_cast<const uint16_t *>(Qsrc) + (bh / Hq) * q_st.b + (bh % Hq) * q_st.h;
+        constexpr int RC = D / 8, SW = RC - 1;  // 16-byte chunks per row, and the swizzle's mask
+        uint8_t *q_lds = lds + 2 * TILE + wave * (64 * D);
+        uint4 rows[RC / 2];
+#pragma unroll
+        for (int x = 0; x < RC / 2; ++x) {
+            const int e = 64 * x + lane;
+            rows[x] = *reinterpret_cast<const uint4 *>(Qh + min(row0 + e / RC, Nq - 1) * q_st.n + e % RC * 8);
+        }
+#pragma unroll
+        for (int x = 0; x < RC / 2; ++x) {
+            const int e = 64 * x + lane, row = e / RC;
+            *reinterpret_cast<uint4 *>(q_lds + row * D * 2 + ((e % RC ^ (row & SW)) << 4)) = rows[x];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         float amax = 0.0f;
 #pragma unroll
         for (int ch = 0; ch < KC; ++ch)
 #pragma unroll
             for (int e = 0; e < 2; ++e)
-                qraw[ch][e] = qrow < Nq ? *reinterpret_cast<const uint4 *>(Qr + ch * 32 + h * 16 + e * 8)
-                                        : make_uint4(0u, 0u, 0u, 0u);
+                qraw[ch][e] = *reinterpret_cast<const uint4 *>(q_lds + lq * D * 2 + (((4 * ch + 2 * h + e) ^ (lq & SW)) << 4));
 #pragma unroll
         for (int ch = 0; ch < KC; ++ch)
 #pragma unroll
@@ -224,6 +235,11 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
     const float dk_first = dkh[min(64 * (jb >> 5) + lane, nKblk - 1)];
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): K^(jb) has landed
     __syncthreads();
+    // the first step's "P^ V^ of the step before" multiplies zeros: its V^ buffer must hold numbers
+#pragma unroll
+    for (int k = 0; k < TILE / 4096; ++k)
+        *reinterpret_cast<uint4 *>(lds + (2 + ((jb + 1) & 1)) * TILE + k * 4096 + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
+
     // (not before: the loads above would be waited for behind it)
 #pragma unroll
     for (int k = 0; k < NP; ++k) copy_k(jb + 1, k);
