@@ -368,8 +368,7 @@ int sage_attn_fwd_4bit(const void *q, const void *k, const void *v, void *out, i
     const sage::Strides qs = sage::contiguous_bhnd(Hq, Nq, d), ks = sage::contiguous_bhnd(Hkv, Nk, d);
     discard_pending_hip_error();
     hipError_t e = sage::launch_quant_kv(k, ks, v, ks, w.base.k_i8, w.base.k_scale, w.base.k_mean, w.base.v_fp8,
-                                         w.base.v_scale, 4.5f, B, Hkv, Nk, d, bf16, s, qws, true);
-    if (e == hipSuccess) e = sage::launch_quant_q4(q, qs, w.q_mean, nullptr, nullptr, B, Hq, Nq, d, bf16, s);
+                                         w.base.v_scale, 4.5f, B, Hkv, Nk, d, bf16, s, qws, true, q, qs, w.q_mean, Hq, Nq);
     if (e == hipSuccess)
         e = sage::launch_delta_s(k, ks, w.base.k_mean, w.q_mean, w.dsx, B, Hq, Hkv, Nq, Nk, d, causal != 0, sm_scale, bf16,
                                  s);

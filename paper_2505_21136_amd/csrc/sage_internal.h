@@ -45,10 +45,12 @@ hipError_t launch_quant_v(const void *v, Strides v_st, uint8_t *v_fp8, float *v_
                           int d, bool bf16, hipStream_t stream, const QuantScratch &ws);
 
 // K and V of the same shape together, identical results
-// (int4: the K codes of the 4+8 variant, range [-7, 7], one per byte)
+// (int4: the K codes of the 4+8 variant, range [-7, 7], one per byte, and with q != NULL the block means of Q, as launch_quant_q4 makes
+// them, in the same launches)
 hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v_st, int8_t *k_i8, float *k_scale,
                            float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int B, int H, int N, int d,
-                           bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4 = false);
+                           bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4 = false, const void *q = nullptr,
+                           Strides q_st = Strides{}, float *q_mean = nullptr, int Hq = 0, int Nq = 0);
 
 // Which kernels the K/V quantisers use: 0 = by shape (resident_threads in sage_quant.hip),
 // 1 = always the three launches (statistics, finalize, codes), 2 = always the single-read kernel (above 256 workgroups of 256 threads

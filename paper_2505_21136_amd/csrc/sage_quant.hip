@@ -267,33 +267,50 @@ __device__ __forceinline__ void quant_int8_body(const uint16_t *__restrict__ X, 
 // double (exact for 16-bit inputs, so the order of the additions does not matter).  One workgroup of 256
 // threads per Q block; sm: RP x D doubles.
 // ---------------------------------------------------------------------------
+// Bound by latency, not by bytes (32 KB per block): all of a thread's loads are in flight at once, and with K and V quantised in the
+// same call the blocks are the last workgroups of that launch.  The quantiser's workgroups of the 4+8 variant rarely fill the chip
+// (24 / 8 heads of 4096 x 128: 384 of 256 threads), so the blocks run beside them and a launch with its gap goes: the whole call
+// 180.5 -> 174.4 us.  Teams of 256 threads, numbered by tid, a workgroup's teams in step.
+template <int D>
+constexpr int block_mean_doubles() {
+    return 256 / (D / 8) * D;
+}
+template <bool BF16, int D>
+__device__ __forceinline__ void block_mean_body(const uint16_t *__restrict__ Q, Strides st, int H, int N, int nblk,
+                                                float *__restrict__ mean, double *sm, int bh, int blk, int tid) {
+    constexpr int LPR = D / 8, RP = 256 / LPR, ITER = kBQ / RP;
+    const int co = tid % LPR, rr = tid / LPR;
+    const uint16_t *Qh = Q + (bh / H) * st.b + (bh % H) * st.h + co * 8;
+    const int r0 = blk * kBQ + rr;
+    uint4 raw[ITER];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) raw[it] = *reinterpret_cast<const uint4 *>(Qh + (int64_t)min(r0 + it * RP, N - 1) * st.n);
+    double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) {
+        float f[8];
+        unpack8<BF16>(raw[it], f);
+        if (r0 + it * RP < N) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += (double)f[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sm[rr * D + co * 8 + j] = acc[j];
+    __syncthreads();
+    if (tid < D && blk < nblk) {
+        double a = sm[tid];
+#pragma unroll
+        for (int i = 1; i < RP; ++i) a += sm[i * D + tid];
+        mean[((size_t)bh * nblk + blk) * D + tid] = (float)(a / (double)(min(kBQ, N - blk * kBQ)));
+    }
+}
+
 template <bool BF16, int D>
 __global__ __launch_bounds__(256) void block_mean_kernel(const uint16_t *__restrict__ Q, Strides st, int H, int N,
                                                          int nblk, float *__restrict__ mean) {
-    constexpr int LPR = D / 8;
-    constexpr int RP = 256 / LPR;
-    __shared__ double sm[RP][D];
-    const int bh = blockIdx.y, blk = blockIdx.x;
-    const int co = threadIdx.x % LPR, rr = threadIdx.x / LPR;
-    const uint16_t *Qh = Q + (bh / H) * st.b + (bh % H) * st.h;
-    const int r0 = blk * kBQ, r1 = min(r0 + kBQ, N);
-    double acc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.0;
-    for (int r = r0 + rr; r < r1; r += RP) {
-        float f[8];
-        unpack8<BF16>(*reinterpret_cast<const uint4 *>(Qh + r * st.n + co * 8), f);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += (double)f[j];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sm[rr][co * 8 + j] = acc[j];
-    __syncthreads();
-    if (threadIdx.x < D) {
-        double a = sm[0][threadIdx.x];
-        for (int i = 1; i < RP; ++i) a += sm[i][threadIdx.x];
-        mean[((size_t)bh * nblk + blk) * D + threadIdx.x] = (float)(a / (double)(r1 - r0));
-    }
+    __shared__ double sm[block_mean_doubles<D>()];
+    block_mean_body<BF16, D>(Q, st, H, N, nblk, mean, sm, blockIdx.y, blockIdx.x, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -542,13 +559,16 @@ __global__ __launch_bounds__(256) void quant_kv_kernel(const uint16_t *__restric
 // ---------------------------------------------------------------------------
 // tokens of a workgroup of n threads: 16 uint4 of 8 elements per thread
 constexpr int resident_tokens(int threads, int d) { return threads * 128 / d; }
-// Q side of a launch that also quantises Q (quant_kv_resident_kernel<..., WITH_Q>): first = workgroups of the K side
+// Q side of a launch that also works on Q (quant_kv_resident_kernel<..., WITH_Q>, chunk_stats_kernel): INT8 codes and scales or, with
+// `mean`, the block means of the 4+8 variant.  BH heads (H per batch) of N rows; first = workgroups of the K and V side.
 struct QuantQ {
     const uint16_t *x;
     Strides st;
     int8_t *codes;
-    float *scale;
-    int n_blocks, first;
+    float *scale, *mean;
+    int BH, H, N, n_blocks, first;
+    // workgroups that the blocks take, `teams` each
+    int workgroups(int teams) const { return x ? BH * cdiv(n_blocks, teams) : 0; }
 };
 constexpr int kBothTensors = 0, kOnlyK = 1, kOnlyV = 2;  // what a launch quantises (both: K and V groups in turn)
 constexpr int kResidentMaxGroup = 256;  // largest group, in workgroups of 256 threads (thread t polls partner t)
@@ -695,9 +715,16 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
         if ((int)blockIdx.x >= q.first) {
             constexpr int TEAMS = NTHR / 256;
             const int team = threadIdx.x >> 8, wgs = (q.n_blocks + TEAMS - 1) / TEAMS;
-            const int x = blockIdx.x - q.first;
-            quant_int8_body<BF16, D, kBQ, 0, 127>(q.x, q.st, H, nullptr, q.codes, q.scale, N, q.n_blocks, &wmax[0][0] + 4 * team,
-                                                  x / wgs, x % wgs * TEAMS + team, threadIdx.x & 255);
+            const int x = blockIdx.x - q.first, bh = x / wgs, blk = x % wgs * TEAMS + team;
+            if constexpr (QMAX == 127) {
+                quant_int8_body<BF16, D, kBQ, 0, 127>(q.x, q.st, q.H, nullptr, q.codes, q.scale, q.N, q.n_blocks,
+                                                      &wmax[0][0] + 4 * team, bh, blk, threadIdx.x & 255);
+            } else {
+                static_assert(TEAMS * block_mean_doubles<D>() * sizeof(double) <= sizeof(smem), "teams of the block means");
+                block_mean_body<BF16, D>(q.x, q.st, q.H, q.N, q.n_blocks, q.mean,
+                                         reinterpret_cast<double *>(smem) + team * block_mean_doubles<D>(), bh, blk,
+                                         threadIdx.x & 255);
+            }
             return;
         }
     }
@@ -835,7 +862,7 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
         // up to 1.5 % slower) ----
         constexpr int NB = C / kBK;    // K blocks of the chunk
         constexpr int IPB = kBK / RP;  // passes per block
-        constexpr bool ALL_MAXIMA = NB >= 16 && !WITH_Q;
+        constexpr bool ALL_MAXIMA = NB >= 16 && !(WITH_Q && QMAX == 127);
         constexpr float kRange = (float)QMAX;
         float mu[8];
 #pragma unroll
@@ -1033,9 +1060,13 @@ __global__ __launch_bounds__(kChunkThreads) void chunk_stats_kernel(const uint16
     __shared__ __attribute__((aligned(16))) double smem[RP * D];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= q.first) {
-        const int team = tid >> 8, wgs = (q.n_blocks + 1) / 2, x = blockIdx.x - q.first;
-        quant_int8_body<BF16, D, kBQ, 0, 127>(q.x, q.st, H, nullptr, q.codes, q.scale, N, q.n_blocks,
-                                              reinterpret_cast<float *>(smem) + 4 * team, x / wgs, x % wgs * 2 + team, tid & 255);
+        const int team = tid >> 8, wgs = (q.n_blocks + 1) / 2, x = blockIdx.x - q.first, bh = x / wgs, blk = x % wgs * 2 + team;
+        if (q.mean)
+            block_mean_body<BF16, D>(q.x, q.st, q.H, q.N, q.n_blocks, q.mean, smem + team * block_mean_doubles<D>(), bh, blk,
+                                     tid & 255);
+        else
+            quant_int8_body<BF16, D, kBQ, 0, 127>(q.x, q.st, q.H, nullptr, q.codes, q.scale, q.N, q.n_blocks,
+                                                  reinterpret_cast<float *>(smem) + 4 * team, bh, blk, tid & 255);
         return;
     }
     const int grp = blockIdx.x / G, part = blockIdx.x % G;
@@ -1286,7 +1317,7 @@ hipError_t launch_chunks(const uint16_t *k, Strides k_st, const uint16_t *v, Str
     const int G = resident_group_size(N, D, 256);
     const int nK = tensors == kOnlyV ? 0 : cdiv(N, kBK), nV = tensors == kOnlyK ? 0 : G;
     q.first = (tensors == kBothTensors ? 2 * BH : BH) * G;
-    chunk_stats_kernel<BF16, D><<<q.first + (q.x ? BH * cdiv(q.n_blocks, 2) : 0), kChunkThreads, 0, stream>>>(
+    chunk_stats_kernel<BF16, D><<<q.first + q.workgroups(2), kChunkThreads, 0, stream>>>(
         k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, tensors, q);
     chunk_codes_kernel<BF16, D, QMAX><<<dim3(nK + nV, BH), 256, 0, stream>>>(
         k, k_st, v, v_st, H, N, G, ws.k_sum_part, ws.v_max_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, cdiv(N, kW));
@@ -1316,13 +1347,8 @@ hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v,
     quant_kv_resident_kernel<BF16, D, QMAX, NTHR, Q><<<GRID, NTHR, 0, stream>>>(                                        \
         k, k_st, v, v_st, H, N, G, ws.k_sum_part, v_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT,     \
         wait_ticks, stagger, tensors, q)
-    if constexpr (QMAX == 127) {
-        if (q.x) {
-            SAGE_RESIDENT(true, q.first + BH * cdiv(q.n_blocks, NTHR / 256));
-            return hipGetLastError();
-        }
-    }
-    SAGE_RESIDENT(false, q.first);
+    if (q.x) SAGE_RESIDENT(true, q.first + q.workgroups(NTHR / 256));
+    else SAGE_RESIDENT(false, q.first);
 #undef SAGE_RESIDENT
     return hipGetLastError();
 }
@@ -1446,7 +1472,7 @@ hipError_t launch_quant_k(const void *k, Strides st, int8_t *k_i8, float *k_scal
                           int8_t *q_i8, float *q_scale) {
     const uint16_t *k16 = static_cast<const uint16_t *>(k);
     const int BH = B * H;
-    const QuantQ qq{static_cast<const uint16_t *>(q), q_st, q_i8, q_scale, cdiv(N, kBQ), 0};
+    const QuantQ qq{static_cast<const uint16_t *>(q), q_st, q_i8, q_scale, nullptr, BH, H, N, cdiv(N, kBQ), 0};
     if (d == 128)
         return bf16 ? quant_k_impl<true, 128>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws, qq)
                     : quant_k_impl<false, 128>(k16, st, k_i8, k_scale, k_mean, BH, H, N, stream, ws, qq);
@@ -1468,21 +1494,26 @@ hipError_t launch_quant_v(const void *v, Strides st, uint8_t *v_fp8, float *v_sc
 
 hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v_st, int8_t *k_i8, float *k_scale,
                            float *k_mean, uint8_t *v_fp8, float *v_scale, float v_r, int B, int H, int N, int d,
-                           bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4) {
+                           bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4, const void *q, Strides q_st,
+                           float *q_mean, int Hq, int Nq) {
     const uint16_t *k16 = static_cast<const uint16_t *>(k), *v16 = static_cast<const uint16_t *>(v);
     const int BH = B * H;
     const int threads = resident_threads(Quantise::kBoth, 2 * BH, N, d);
     const bool chunks = chunks_pay(Quantise::kBoth, BH, N, d);
+    const QuantQ qm{static_cast<const uint16_t *>(q), q_st, nullptr, nullptr, q_mean, B * Hq, Hq, Nq, cdiv(Nq, kBQ), 0};
 #define SAGE_KV(BF, DD, QM)                                                                                           \
     (chunks    ? launch_chunks<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, \
-                                           stream, ws, kBothTensors)                                                  \
+                                           stream, ws, kBothTensors, qm)                                              \
      : threads ? launch_resident<BF, DD, QM>(threads, k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, \
-                                             BH, H, N, stream, ws, kBothTensors)                                      \
+                                             BH, H, N, stream, ws, kBothTensors, qm)                                  \
                : quant_kv_impl<BF, DD, QM>(k16, k_st, v16, v_st, k_i8, k_scale, k_mean, v_fp8, v_scale, v_r, BH, H, N, \
                                            stream, ws))
     if (int4) {
-        if (d == 128) return bf16 ? SAGE_KV(true, 128, 7) : SAGE_KV(false, 128, 7);
-        return bf16 ? SAGE_KV(true, 64, 7) : SAGE_KV(false, 64, 7);
+        const hipError_t e = d == 128 ? (bf16 ? SAGE_KV(true, 128, 7) : SAGE_KV(false, 128, 7))
+                                      : (bf16 ? SAGE_KV(true, 64, 7) : SAGE_KV(false, 64, 7));
+        // (the three launches have no place for the block means of Q)
+        return e != hipSuccess || !q || chunks || threads ? e
+                                                          : launch_quant_q4(q, q_st, q_mean, nullptr, nullptr, B, Hq, Nq, d, bf16, stream);
     }
     if (d == 128) return bf16 ? SAGE_KV(true, 128, 127) : SAGE_KV(false, 128, 127);
     return bf16 ? SAGE_KV(true, 64, 127) : SAGE_KV(false, 64, 127);

@@ -36,3 +36,23 @@ def test_chunks_write_the_bits_of_the_three_launches(idx, shape):
     assert torch.equal(out.view(torch.int16), out_t.transpose(1, 2).view(torch.int16))
     if shape[1] * shape[2] <= 3000:
         _against_oracle(got, k, v, 4.5, shape[2])
+
+
+# (q heads, kv heads, q rows, kv rows, d): the block means of Q as the last workgroups of two launches over chunks (teams of two blocks)
+# and of the single-read kernel at 256 and 512 threads (1 and 2 blocks a workgroup), odd counts and short last blocks
+MEANS = [(4, 2, 1, 300, 128), (2, 2, 385, 513, 128), (6, 2, 1029, 4224, 64), (6, 3, 700, 16200, 128), (4, 4, 513, 32768, 128),
+         (3, 3, 129, 65536, 64), (16, 16, 641, 8192, 128)]
+
+
+@pytest.mark.parametrize("hq,hkv,nq,nk,d", MEANS)
+@pytest.mark.parametrize("path", [0, 2])
+def test_block_means_beside_the_quantiser_equal_those_of_their_own_launch(hq, hkv, nq, nk, d, path):
+    say(f"[block means] {hq}/{hkv} heads, {nq} x {nk} x {d}, quantiser path {path}")
+    k, v = _inputs(2 if d == 128 else 4, (2, hkv, nk, d))
+    q, _ = _inputs(5 if d == 128 else 3, (2, hq, nq, d))
+    q = q.to(k.dtype)
+    sage.diag_quant_kv_path(THREE_LAUNCHES)
+    want = sage.sage_attn_fwd_4bit(q, k, v, causal=False)
+    sage.diag_quant_kv_path(path)
+    got = sage.sage_attn_fwd_4bit(q, k, v, causal=False)
+    assert torch.equal(want.view(torch.int16), got.view(torch.int16))
