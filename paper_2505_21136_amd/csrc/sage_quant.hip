@@ -269,8 +269,8 @@ __device__ __forceinline__ void quant_int8_body(const uint16_t *__restrict__ X, 
 // ---------------------------------------------------------------------------
 // Bound by latency, not by bytes (32 KB per block): all of a thread's loads are in flight at once, and with K and V quantised in the
 // same call the blocks are the last workgroups of that launch.  The quantiser's workgroups of the 4+8 variant rarely fill the chip
-// (24 / 8 heads of 4096 x 128: 384 of 256 threads), so the blocks run beside them and a launch with its gap goes: the whole call
-// 180.5 -> 174.4 us.  Teams of 256 threads, numbered by tid, a workgroup's teams in step.
+// (B 2, 32 / 8 heads of 3000 x 128: 384 of 256 threads), so the blocks run beside them and a launch with its gap goes: the whole
+// call 180.5 -> 174.4 us (B 1, 8 heads of 1024 x 64: two launches over chunks; with them 37.3 -> 29.5 us).  Teams of 256 threads, numbered by tid, a workgroup's teams in step.
 template <int D>
 constexpr int block_mean_doubles() {
     return 256 / (D / 8) * D;
