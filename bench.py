@@ -32,25 +32,26 @@ PEAK_HBM = 8.0e12            # B/s
 # 128 keys: 64 scores per lane), the vector instructions issued, how many of them are MFMA, and how many run at half rate (exp,
 # FP8 pack).  Only workloads that were profiled have an entry; everything derived from a missing entry is null in the
 # JSON line.  `valu_busy` / `mfma_busy` are SQ_ACTIVE_INST_VALU and SQ_VALU_MFMA_BUSY_CYCLES as fractions of
-# the kernel's SIMD time.
+# the kernel's SIMD time (above 1: instructions of two wavefronts issued together).
 SOURCE = "profiles/prefill_kernel_counters.md"
 PROFILED = {
     "cfg5": dict(source=SOURCE, traffic=int(885070 * 1024 * 2.0 + 196608 * 1024 * 1.0),
-                 valu_per_step=389.1, mfma_i8=16, mfma_f8=8, half_rate=97.0, valu_busy=0.87, mfma_busy=0.46),
+                 valu_per_step=389.5, mfma_i8=16, mfma_f8=8, half_rate=97.0, valu_busy=0.87, mfma_busy=0.46),
     "cfg3": dict(source=SOURCE, traffic=int(65635 * 1024 * 2.0 + 65536 * 1024 * 1.0),
-                 valu_per_step=386.0, mfma_i8=8, mfma_f8=4, half_rate=97.1, valu_busy=1.0, mfma_busy=0.27),
+                 valu_per_step=386.6, mfma_i8=8, mfma_f8=4, half_rate=97.1, valu_busy=1.11, mfma_busy=0.30),
     # causal: per executed wavefront-step, prologue and epilogue of the short workgroups included
     "cfg2": dict(source=SOURCE, traffic=int(187390 * 1024 * 2.0 + 131091 * 1024 * 1.0),
-                 valu_per_step=476.6, mfma_i8=16, mfma_f8=8, half_rate=96.0, valu_busy=0.81, mfma_busy=0.37),
+                 valu_per_step=482.1, mfma_i8=16, mfma_f8=8, half_rate=96.0, valu_busy=0.83, mfma_busy=0.37),
 }
 
 
 def alu_bound(prof):
-    """The co-limit of the MFMA roofline: the vector-ALU issue port, which MFMA and ordinary vector
-    instructions share.  Port cycles per wavefront-step from the measured instruction mix -- 4 cycles per
+    """The co-limit of the MFMA roofline: vector instruction issue, with every instruction issued alone.
+    Cycles per wavefront-step from the measured instruction mix -- 4 cycles per
     full-rate instruction and per MFMA, 8 per half-rate instruction (which adds up to the measured SQ_ACTIVE_INST_VALU within
-    1 %) -- against the MFMA pipe's own cycles for the same step (32 per INT8 32x32x32, 64 per FP8 32x32x64): their
-    ratio is the fraction of the MFMA peak this instruction mix can reach at equal clock."""
+    1 %; two wavefronts of a SIMD can issue an FP32 addition, multiplication or FMA together with an instruction of 4 cycles, which
+    they do where the kernel raises their priority around the exponentials) -- against the MFMA pipe's own cycles for the
+    same step (32 per INT8 32x32x32, 64 per FP8 32x32x64): their ratio is the fraction of the MFMA peak this instruction mix can reach at equal clock."""
     if not prof:
         return None
     n_mfma = prof["mfma_i8"] + prof["mfma_f8"]
@@ -225,8 +226,8 @@ def main():
             "frac_of_peak_measured": round(attn_tops / peak_measured, 4) if peak_measured else None,
             # from the rocprofv3 counters of this workload (null for a workload that was not profiled)
             "alu_bound": alu_bound(prof),
-            "limiter": (f"vector-ALU issue port (softmax arithmetic shares it with MFMA issue): "
-                        f"{100 * prof['valu_busy']:.0f} % busy, MFMA pipe {100 * prof['mfma_busy']:.0f} % "
+            "limiter": (f"vector instruction issue (softmax arithmetic and MFMA), at d = 128 also power: "
+                        f"issue cycles one by one {100 * prof['valu_busy']:.0f} % of the time, MFMA pipe {100 * prof['mfma_busy']:.0f} % "
                         f"[{prof['source']}]") if prof else None,
         },
         "quant_stage": {"ms": round(quant_ms, 4), "algorithmic_GBps": round(quant_gbs, 1) if quant_gbs else None,

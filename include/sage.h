@@ -350,7 +350,7 @@ int sage_attn_fwd_4bit(const void *q, const void *k, const void *v, void *out,
  *   workspace   device, 256-byte aligned, >= sage_decode_workspace_bytes(B, Hq, Hkv, Nq, Nk, d, split_keys): the
  *               ranges' partial results; nothing in it has to be initialised
  * Returns SAGE_EINVAL for a split_keys that is negative or no multiple of 128 and for the argument errors of the
- * other entry points; SAGE_EWORKSPACE; SAGE_EHIP.  Two launches (ranges, combination); allocates nothing, does not
+ * other entry points; SAGE_EWORKSPACE; SAGE_EHIP.  One launch, or two (ranges, combination); allocates nothing, does not
  * synchronise.
  */
 int sage_decode_split_keys(int B, int Hq, int Hkv, int Nq, int Nk);
@@ -378,14 +378,15 @@ int sage_diag_mfma_rate(int kind, int iters, int workgroups, float *sink, double
 
 /*
  * Not a step of the method: selects, process-wide, which kernels the quantisers of K and V (sage_quant_kv, sage_quant_kv_static,
- * sage_quant_kv4, sage_quant_k, sage_quant_qk, sage_quant_v and the whole-pass entry points) launch.  Both choices compute the same
+ * sage_quant_kv4, sage_quant_k, sage_quant_qk, sage_quant_v and the whole-pass entry points) launch.  All choices compute the same
  * codes, scales and mean (Sec. 2.1, Sec. 3).
  *   path        0 (default): by shape -- the single-read kernel (K and V are read once: the workgroups of a head
  *               keep 64 or 128 KiB of tokens each in registers, exchange their partial column statistics through
  *               the workspace and then write the codes) up to 256 workgroups of 64 KiB per head (65536 tokens at
  *               d = 128, 131072 at d = 64) where it measures faster than the three launches (statistics, finalize,
- *               codes; K and V read twice); 1: always the three launches; 2: always the single-read kernel (beyond its
- *               reach calls for K and V together then fail with SAGE_EHIP, calls for one of them run the three launches)
+ *               codes; K and V read twice), and two launches over chunks where a call is small; 1: always the three
+ *               launches; 2: always the single-read kernel (beyond its reach calls for K and V
+ *               together then fail with SAGE_EHIP, calls for one of them run the three launches)
  *   wait_ticks  how long a workgroup of the single-read kernel waits for the partials of its partners before it
  *               computes the head's statistic alone from global memory (same result), in ticks of the GPU's
  *               constant 100 MHz clock; negative: it does not wait at all (for tests of that branch); the

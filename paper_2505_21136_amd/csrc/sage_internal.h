@@ -52,7 +52,7 @@ hipError_t launch_quant_kv(const void *k, Strides k_st, const void *v, Strides v
                            bool bf16, hipStream_t stream, const QuantScratch &ws, bool int4 = false, const void *q = nullptr,
                            Strides q_st = Strides{}, float *q_mean = nullptr, int Hq = 0, int Nq = 0);
 
-// Which kernels the K/V quantisers use: 0 = by shape (resident_threads in sage_quant.hip),
+// Which kernels the K/V quantisers use: 0 = by shape (chunks_pay, resident_threads in sage_quant.hip),
 // 1 = always the three launches (statistics, finalize, codes), 2 = always the single-read kernel (above 256 workgroups of 256 threads
 // per head: an error for K and V together, the three launches for one of them).  wait_ticks: how long a workgroup of the single-read kernel waits for its partners before
 // it computes the head's statistic alone (100 MHz ticks; negative: no wait).  Process-wide.
