@@ -500,10 +500,20 @@ hipError_t launch_attn(const void *q, bool q_raw, Strides q_st, const int8_t *k_
     // 21.1 / 15.9 / 18.0 and 16.3 / 12.5 / 14.4; 1024 tiles 38.8 / 28.7 / 19.2 and 29.1 / 22.7 / 15.1.  1024 x 8192: 256 tiles
     // 45 / 60 / 92 and 39 / 54 / 79; 512 tiles 85 / 64 / 95 and 72 / 55 / 79; 1024 tiles 162 / 119 / 100 and 138 / 103 / 82.  512 tiles
     // over 128 keys 12.7 / 9.4 / 8.2 and 9.3 / 7.2 / 6.3, 256 keys 13.6 / 10.4 / 9.5 and 10.1 / 7.8 / 7.4, 512 keys 16.3 / 12.3 / 12.2
-    // and 12.2 / 9.4 / 9.7.  Causal calls keep the order up to 2048 x 2048 (above, their short tiles would let the spread kernels go
-    // on a little further).  The 4+8 variant and key ranges exist in the prefill kernel only.
-    const long heads = (long)B * Hq;
-    const int row_groups = dsx || part_acc ? 0 : heads * cdiv(Nq, 32) <= kCUs ? 1 : heads * cdiv(Nq, 64) <= kCUs && Nk > 2 * kW ? 2 : 0;
+    // and 12.2 / 9.4 / 9.7.  The 4+8 variant and key ranges exist in the prefill kernel only.
+    // Causal: a head's last tiles are its longest and start first, so a second tile of a CU is a short one and the lines move with how
+    // short, Nq against Nk, and with what a tile costs besides its keys.  Rows = keys: 32 rows win up to 512 tiles of 32 from 4096 keys
+    // on (384 tiles 27.2 / 32.5 / 49.5 and, d 64, 21.6 / 28.7 / 42.8; 512 tiles 29.5 / 32.6 / 49.7), with 2048 up to 450 (384 tiles 17.7 /
+    // 20.1 / 28.5, 448 20.6 / 20.6), with 1024 up to 370 (288 tiles 11.4 / 13.9, 384 14.4 / 14.1), with 300 up to 256 (10.3 / 9.8 at 260);
+    // 64 rows up to 512 tiles of 64 from 4096 on (320 tiles 41.0 / 34.4 / 50.3, 512 tiles 54.9 / 40.8 / 50.6, 768 tiles 80 / 62 / 54.5; 2 heads x
+    // 16384 165 / 125 / 174), with 2048 up to 450 (320 tiles 28.2 / 20.6 / 28.8; 512 37.9 / 27.6 / 29.6), with 1024 up to 340 (320 tiles
+    // 20.7 / 17.0 / 18.5, 384 22.7 / 19.4 / 18.8), with 700 not beyond 256 (308 tiles 18.3 / 15.8 / 14.8).  Nk = 4 Nq (1024 x 4096) as
+    // full attention: 144 tiles of 64 40.7 / 32.7, 288 61 / 53.6 / 50.4.
+    const long heads = (long)B * Hq, t32 = heads * cdiv(Nq, 32), t64 = heads * cdiv(Nq, 64);
+    const auto rounds_fit = [&](long tiles, int tile_keys, int thirds) {
+        return tiles <= kCUs || (causal && tiles <= 2 * kCUs && 3 * tiles * ((long)Nk + tile_keys) <= (long)thirds * kCUs * Nq);
+    };
+    const int row_groups = dsx || part_acc ? 0 : rounds_fit(t32, 5 * kW, 7) ? 1 : rounds_fit(t64, 8 * kW, 8) && Nk > 2 * kW ? 2 : 0;
     if (row_groups)
         return launch_spread(q, q_raw, q_st, k_i8, v_fp8, q_scale, k_scale, v_scale, out, o_st, B, Hq, Hkv, Nq, Nk, d,
                              causal, sm_scale, p_r, bf16, stream, row_groups);
