@@ -526,16 +526,26 @@ DecodeScratch decode_scratch_layout(void *base, int B, int Hkv, int Nk, int d, i
 }
 
 // Whether the ranges of a K/V head are one workgroup's.  Up to eight wavefronts fit a CU's registers and LDS, and the second launch is
-// saved (one workgroup / one wavefront per workgroup and a second launch, us: 16 heads x 1500 keys d 128 8.6 / 9.0, 64 x 256 6.3 / 8.1,
-// 150 x 4096 25.5 / 30.6; 64 rows per head, 256 x 2048 32.5 / 40.5), but half of the CUs or more have nothing to do with up to 128
-// heads.  That costs where they are needed: to stream a cache from HBM (128 x 32768 d 128 202 / 184, d 64 103 / 97; in the last-level
-// cache still ahead, 128 x 8192 40.3 / 44.0), and where the work of two row tiles adds up on one CU (32 rows, 8 x 2048 keys in 8
-// ranges 15.9 / 12.9, in 4 12.3 / 12.5; 64 rows, 16 x 700 17.4 / 13.5).
+// saved, 2 to 3 us; but up to 128 heads leave half of the CUs or more idle, and a CU draws 55 to 90 GB/s.  A program that steps through
+// its layers finds the cache of each one cold, so the lines are those of calls that go round caches of 900 MB together (us, one
+// workgroup / one wavefront per workgroup and a second launch; behind the semicolon the same cache again and again):
+//   * one row tile, bytes of K^ and V^ per head: d 128, 8 heads x 512 keys (128 KB) 6.3 / 8.4, x 1000 8.1 / 9.5, x 1500 (375 KB) 10.9 /
+//     9.7; 8.2 / 8.6, x 2048 (512 KB) 12.7 / 9.4; 8.6 / 8.2; 96 x 2048 15.1 / 14.5; 11.6 / 13.4, 128 x 3000 21.4 / 22.6, 128 x 4096
+//     30.3 / 28.7; 22.4 / 25.1; d 64, 128 x 4096 (512 KB) 16.1 / 17.7, x 8192 30.4 / 29.0;
+//   * with at most 32 KB of copies in flight a CU is not the limit: 2 ranges at d 128, 64 x 2048 17.6 / 19.8, 4 at d 64, 8 x 16384 47 / 48;
+//     with 64 KB it is: 4 ranges at d 128, 64 x 8192 45 / 35;
+//   * 129 .. 256 heads leave fewer CUs idle than a fifth wavefront on some of them costs: 136 x 1000 10.4 / 13.2, x 32768 206 / 217, 192 x 4096
+//     38 / 44, 256 x 8192 99.6 / 95.7, x 32768 363 / 370; beyond, the last round counts: 257 x 2048 33 / 31, 300 x 8192 132 / 117 (d 64
+//     71 / 59), 340 x 4096 70.2 / 68.6, 360 x 4096 72.5 / 75.5, 520 x 4096 111 / 107, 1000 x 4096 177 / 185;
+//   * the work of two row tiles adds up on a CU (d 128, 32 rows, 8 x 256 keys in one range 14.4 / 12.6, 8 x 1000 in four 13.3 / 13.5, 64 x 8192
+//     in four 52.8 / 51.3, 8 x 2048 in eight 18.5 / 13.8), that of two wavefronts per range more so (64 rows, 16 x 700 18.1 / 14.4).
 bool decode_together(int groups, int S, int nt, int TW, int Nk, int d) {
     if (TW * S > 8) return false;
+    const long kb = 2L * Nk * d / 1024;
+    if (groups > kCUs) return S < 4 || 2L * cdiv(groups, kCUs) * kCUs <= 3L * groups || kb < 512 * nt;
     if (groups > kCUs / 2) return true;
-    const bool in_cache = 2.0 * groups * Nk * d <= 256.0 * (1 << 20);
-    return nt == 1 ? in_cache : TW == 1 && S <= 4 && in_cache;
+    if (nt == 1) return S * d <= 256 || kb <= std::max(384, 6 * groups);
+    return TW == 1 && (S > 1 || d == 64) && S <= 4;
 }
 
 // Wavefronts of a workgroup where there is a second launch.  One: they start and end independently (64 heads x 32768 keys, d 128: 98 us
