@@ -193,6 +193,22 @@ __global__ __launch_bounds__(1024) void finalize_kv_kernel(const double *__restr
         finalize_vscale_body(max_part, chunks, D, v_r, v_scale, v_rcp, reinterpret_cast<float *>(sm), blockIdx.x);
 }
 
+// Maximum over the wavefront of a value >= 0 (not NaN), in every lane: within rows of 16 lanes by DPP, then over the four rows, whose
+// bit patterns order like integers, in scalar registers.
+__device__ __forceinline__ float wave_max_abs(float x) {
+#define SAGE_DPP(CTRL) \
+    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true)))
+    SAGE_DPP(0xb1);   // quad_perm [1,0,3,2]
+    SAGE_DPP(0x4e);   // quad_perm [2,3,0,1]
+    SAGE_DPP(0x141);  // row_half_mirror
+    SAGE_DPP(0x140);  // row_mirror
+#undef SAGE_DPP
+    const int b = __builtin_bit_cast(int, x);
+    const int lo = max(__builtin_amdgcn_readlane(b, 0), __builtin_amdgcn_readlane(b, 16));
+    const int hi = max(__builtin_amdgcn_readlane(b, 32), __builtin_amdgcn_readlane(b, 48));
+    return __builtin_bit_cast(float, max(lo, hi));
+}
+
 // ---------------------------------------------------------------------------
 // Per-block integer quantisation (Sec. 2.1): one workgroup per block of BLOCK
 // tokens, the block lives in registers between the max pass and the code pass.
@@ -200,6 +216,9 @@ __global__ __launch_bounds__(1024) void finalize_kv_kernel(const double *__restr
 // byte).  SMOOTH = 0: no mean is subtracted; 1: `mean` holds one vector per
 // head (K smoothing, Sec. 3); 2: one vector per head and block (Q smoothing of
 // the 4+8 variant).  256 threads, numbered by tid, each workgroup's teams in step; wmax: four floats of LDS per team.
+// Bound by memory, or by its latency: a thread's loads are all in flight at once (rows past the end load the last one; with a branch
+// around each load, which then waited for itself, and the maximum through LDS: Q of 512 heads x 1024, d 128 40.4 -> 32.2 us, of 64 heads x 777
+// 5.7 -> 4.7; beside K's workgroups in one launch, 256 heads x 777, d 64 21.2 -> 18.2, x 1024 23.2 -> 20.3).
 // ---------------------------------------------------------------------------
 template <bool BF16, int D, int BLOCK, int SMOOTH, int QMAX>
 __device__ __forceinline__ void quant_int8_body(const uint16_t *__restrict__ X, Strides st, int H,
@@ -220,26 +239,25 @@ __device__ __forceinline__ void quant_int8_body(const uint16_t *__restrict__ X, 
 #pragma unroll
     for (int j = 0; j < 8; ++j) mu[j] = SMOOTH ? mean[mrow * D + co * 8 + j] : 0.0f;
 
+    uint4 raw[ITER];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it)
+        raw[it] = *reinterpret_cast<const uint4 *>(Xh + (int64_t)min(blk * BLOCK + it * RP + rr, N - 1) * st.n + co * 8);
     float x[ITER][8];
     float amax = 0.0f;
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
-        const int r = blk * BLOCK + it * RP + rr;
-        if (r < N) {
-            const uint4 u = *reinterpret_cast<const uint4 *>(Xh + r * st.n + co * 8);
-            unpack8<BF16>(u, x[it]);
+        unpack8<BF16>(raw[it], x[it]);
+        if constexpr (SMOOTH != 0) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if constexpr (SMOOTH != 0) x[it][j] = x[it][j] - mu[j];
-                amax = fmaxf(amax, fabsf(x[it][j]));
-            }
-        } else {
+            for (int j = 0; j < 8; ++j) x[it][j] = x[it][j] - mu[j];
+        }
+        if (blk * BLOCK + it * RP + rr < N) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x[it][j] = 0.0f;
+            for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf(x[it][j]));
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+    amax = wave_max_abs(amax);
     if ((tid & 63) == 0) wmax[tid >> 6] = amax;
     __syncthreads();
     const float a = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
@@ -595,22 +613,6 @@ __device__ __forceinline__ uint2 code_bytes(const float (&x)[8], float rcp) {
         w[h] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
     }
     return make_uint2(w[0], w[1]);
-}
-
-// Maximum over the wavefront of a value >= 0 (not NaN), in every lane: within rows of 16 lanes by DPP, then over the four rows, whose
-// bit patterns order like integers, in scalar registers.
-__device__ __forceinline__ float wave_max_abs(float x) {
-#define SAGE_DPP(CTRL) \
-    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true)))
-    SAGE_DPP(0xb1);   // quad_perm [1,0,3,2]
-    SAGE_DPP(0x4e);   // quad_perm [2,3,0,1]
-    SAGE_DPP(0x141);  // row_half_mirror
-    SAGE_DPP(0x140);  // row_mirror
-#undef SAGE_DPP
-    const int b = __builtin_bit_cast(int, x);
-    const int lo = max(__builtin_amdgcn_readlane(b, 0), __builtin_amdgcn_readlane(b, 16));
-    const int hi = max(__builtin_amdgcn_readlane(b, 32), __builtin_amdgcn_readlane(b, 48));
-    return __builtin_bit_cast(float, max(lo, hi));
 }
 
 // The FP8 codes of 8 channels of the keys 16t + 4g + i (raw[4t + i], t, i < 4) of a half tile: for each channel the 16 bytes at

@@ -96,3 +96,24 @@ def test_joint_kv_quantiser_equals_the_separate_calls(idx, shape):
                           joint):
         assert a.shape == b.shape and a.dtype == b.dtype, name
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,N", [(1, 1), (2, 5), (3, 127), (2, 129), (5, 200), (256, 300)])
+def test_what_lies_behind_the_last_row_does_not_count(H, N, d):
+    """Q alone and in K's launch: rows past the end of a block stand for the last row, and nothing behind the tensor is looked at."""
+    say(f"[quant] guard: H{H} N{N} d{d}")
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    n = H * N * d
+    def fenced():
+        x = torch.full((n + 130 * d,), float("inf"), dtype=torch.float16, device=DEV)
+        x[:n] = torch.randn(n, generator=g, device=DEV).to(torch.float16)
+        return x[:n].view(1, H, N, d)
+    q, k = fenced(), fenced()
+    codes, scale = sage.sage_quant_q(q)
+    q_i8, k_i8, q_scale, k_scale, k_mean = sage.sage_quant_qk(q, k)
+    assert torch.equal(codes, q_i8) and torch.equal(scale, q_scale)
+    qf = q.float().cpu().numpy()[0]
+    for h in (0, H - 1):
+        want, delta = oracle.quant_int8(qf[h], None, 128)
+        assert np.array_equal(codes[0, h].cpu().numpy(), want) and np.array_equal(scale[0, h].cpu().numpy(), delta)
