@@ -730,8 +730,8 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
             return;
         }
     }
-    // Workgroups of one round load, meet and store together, so that the memory rests while they meet.  In launches of at least two rounds
-    // those that come second, third and fourth to their CU start later, `stagger` ticks of the 100 MHz clock each, and the phases
+    // Workgroups of one round load, meet and store together, so that the memory rests while they meet.  In launches of two rounds and more
+    // (launch_resident_n has the rule) those that come second, third and fourth to their CU start later, `stagger` ticks of the 100 MHz clock each, and the phases
     // of a CU's workgroups stay apart.  (us without / with: 128 heads x 4096, d 128 87.6 / 83.6; 48 x 17776, d 64 74.5 / 72.2; with 512
     // threads, two to a CU, 24 x 32768 136 / 132.  Half and twice the step are worse.)
     if (stagger && (int)blockIdx.x < kCUs * (1024 / NTHR)) {
@@ -1344,7 +1344,16 @@ hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v,
         zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(static_cast<uint4 *>(from), words);
     }
     q.first = (tensors == kBothTensors ? 2 * BH : BH) * G;
-    const int stagger = q.first < 2 * kCUs * (1024 / NTHR) ? 0 : NTHR == 256 ? 400 : 700;
+    // Where it pays to start the workgroups of a CU apart, from two rounds on (time with / without).  Groups that meet: of 8 and more chunks of
+    // 256 threads 0.95 .. 0.99 (K and V; V alone of 8 to 12 up to 1.02), of 3 to 6 0.97 .. 1.05 below four rounds and 0.96 .. 1.00 from there on.  A
+    // head that one workgroup holds meets nobody, and its start is only late: 256 threads, K and V of 1024 heads x 129 x 128 27.9 / 24.9
+    // us, x 256 39.1 / 36.2, 2048 x 129 45.4 / 42.5; 512 threads, 512 x 257 30.5 / 27.6, x 300 31.4 / 28.9; only from three quarters of
+    // a chunk on, when a CU's two load and store long enough, 512 x 400 36.6 / 36.1, 1024 x 400 66.7 / 67.7, 600 x 512 46.2 / 48.3, d 64 512 x 800
+    // 38.7 / 40.1, x 1024 43.6 / 45.2.
+    constexpr int kSlots = kCUs * (1024 / NTHR);
+    const bool apart = G == 1 ? NTHR == 512 && 4L * N >= 3 * resident_tokens(NTHR, D)
+                              : resident_group_size(N, D, 256) >= 8 || q.first >= 4 * kSlots;
+    const int stagger = !apart || q.first < 2 * kSlots ? 0 : NTHR == 256 ? 400 : 700;
 #define SAGE_RESIDENT(Q, GRID)                                                                                          \
     quant_kv_resident_kernel<BF16, D, QMAX, NTHR, Q><<<GRID, NTHR, 0, stream>>>(                                        \
         k, k_st, v, v_st, H, N, G, ws.k_sum_part, v_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT,     \

@@ -36,3 +36,18 @@ def test_every_width_writes_the_bits_of_the_three_launches(idx, shape, wait_tick
     _same_bits(want, _alone(k, v, THREE_LAUNCHES), "each alone, three launches")
     _same_bits(want, _alone(k, v, SINGLE_READ, wait_ticks), "each alone, single read")
     _same_bits(want, _quant(k, v, 4.5, 0, wait_ticks), "by shape")
+
+
+# two rounds of workgroups and more, on both sides of the lines from which on a CU's workgroups start apart: 256 threads, heads of one
+# chunk (never) and of seven and eight; 512 threads, a chunk less and more than three quarters full; four rounds of small groups
+MANY = [(1, (1, 1030, 129, 128)), (5, (1, 150, 1700, 128)), (2, (1, 128, 2048, 128)), (2, (1, 513, 300, 128)), (5, (1, 513, 384, 128)),
+        (3, (1, 513, 767, 64)), (3, (1, 513, 1010, 64)), (1, (1, 700, 600, 128))]
+
+
+@pytest.mark.parametrize("idx,shape", MANY)
+def test_several_rounds_of_workgroups_write_the_bits_of_the_three_launches(idx, shape):
+    say(f"[quant rounds] cfg{idx} distributions, shape {shape}")
+    k, v = _inputs(idx, shape)
+    want = _quant(k, v, 4.5, THREE_LAUNCHES)
+    _same_bits(want, _quant(k, v, 4.5, 0), "K and V together")
+    _same_bits(want, _alone(k, v, 0), "each alone")
