@@ -615,35 +615,38 @@ __device__ __forceinline__ uint2 code_bytes(const float (&x)[8], float rcp) {
     return make_uint2(w[0], w[1]);
 }
 
+// The FP8 codes of channels 2 j2 and 2 j2 + 1 (one packed dword of each key; of the eight with the reciprocals rc) of four keys.
+template <bool BF16>
+__device__ __forceinline__ uint2 v_pair_codes(const uint4 *keys, const float (&rc)[8], int j2) {
+    float y[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint4 &x = keys[i];
+        const uint32_t w16 = j2 == 0 ? x.x : j2 == 1 ? x.y : j2 == 2 ? x.z : x.w;
+        y[i][0] = to_f32<BF16>(w16 & 0xffffu) * rc[2 * j2];
+        y[i][1] = to_f32<BF16>(w16 >> 16) * rc[2 * j2 + 1];
+    }
+    int c[2] = {0, 0};
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        c[e] = __builtin_amdgcn_cvt_pk_fp8_f32(y[0][e], y[1][e], c[e], false);
+        c[e] = __builtin_amdgcn_cvt_pk_fp8_f32(y[2][e], y[3][e], c[e], true);
+    }
+    return make_uint2((uint32_t)c[0], (uint32_t)c[1]);
+}
+
 // The FP8 codes of 8 channels of the keys 16t + 4g + i (raw[4t + i], t, i < 4) of a half tile: for each channel the 16 bytes at
 // `dst` + 128 * channel, straight from the thread that has the keys: with the key quads of a thread chosen like this
 // no transposition through LDS is needed (dwords written there by lanes of neighbouring channels fall on one bank).
 template <bool BF16>
 __device__ __forceinline__ void v_codes(const uint4 (&raw)[16], const float (&rc)[8], uint8_t *dst) {
 #pragma unroll
-    for (int j2 = 0; j2 < 4; ++j2) {  // two channels (one packed dword of each key) at a time
-        uint32_t w[2][4];
+    for (int j2 = 0; j2 < 4; ++j2) {
+        uint2 w[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            float y[4][2];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint4 &x = raw[4 * t + i];
-                const uint32_t w16 = j2 == 0 ? x.x : j2 == 1 ? x.y : j2 == 2 ? x.z : x.w;
-                y[i][0] = to_f32<BF16>(w16 & 0xffffu) * rc[2 * j2];
-                y[i][1] = to_f32<BF16>(w16 >> 16) * rc[2 * j2 + 1];
-            }
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                int c = 0;
-                c = __builtin_amdgcn_cvt_pk_fp8_f32(y[0][e], y[1][e], c, false);
-                c = __builtin_amdgcn_cvt_pk_fp8_f32(y[2][e], y[3][e], c, true);
-                w[e][t] = (uint32_t)c;
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-            *reinterpret_cast<uint4 *>(dst + (2 * j2 + e) * 128) = make_uint4(w[e][0], w[e][1], w[e][2], w[e][3]);
+        for (int t = 0; t < 4; ++t) w[t] = v_pair_codes<BF16>(&raw[4 * t], rc, j2);
+        *reinterpret_cast<uint4 *>(dst + 2 * j2 * 128) = make_uint4(w[0].x, w[1].x, w[2].x, w[3].x);
+        *reinterpret_cast<uint4 *>(dst + (2 * j2 + 1) * 128) = make_uint4(w[0].y, w[1].y, w[2].y, w[3].y);
     }
 }
 
@@ -702,7 +705,7 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
     const uint16_t *__restrict__ K, Strides k_st, const uint16_t *__restrict__ V, Strides v_st, int H, int N, int G,
     double *k_sum_part, float *v_max_part, float *k_mean, float *v_scale, float v_r,
     int8_t *__restrict__ k_codes, float *__restrict__ k_scale, int nK, uint8_t *__restrict__ Vt, int nT,
-    long long wait_ticks, int stagger, int tensors, QuantQ q) {
+    long long wait_ticks, int stagger, bool v_through_lds, int tensors, QuantQ q) {
     constexpr int NU = 16;                       // uint4 per thread
     constexpr int NW = NTHR / 64;                // wavefronts
     constexpr int LPR = D / 8;                   // lanes per row
@@ -921,21 +924,23 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
             }
         }
     } else {
-        // ---- V: a thread owns 8 channels of the keys 16t + 4g + i (t, i < 4) of a half tile of 64, whose codes are 16 adjacent bytes
-        // of each channel's row ----
+        // ---- V: a thread owns 8 channels of four key quads.  Straight from registers: the keys 16t + 4g + i (t, i < 4) of a half tile of 64,
+        // whose codes are 16 adjacent bytes of each channel's row.  Through LDS: the quads lie 4 RP keys apart, a round transposes
+        // TP tiles and stores them in one piece ----
         const uint16_t *Vh = V + (bh / H) * v_st.b + (bh % H) * v_st.h;
+        constexpr bool CAN_LDS = D == 64 || NTHR == 256;
+        const bool v_lds = CAN_LDS && v_through_lds;
         const int half = rr >> 2, g = rr & 3;
         uint32_t exists = 0u;  // bit q = 4t + i
         {
             const uint16_t *last = Vh + (int64_t)(N - 1) * v_st.n + co * 8;
-            const int rbase = row0 + 64 * half + 4 * g;
+            const int rbase = row0 + (v_lds ? 4 * rr : 64 * half + 4 * g), apart = v_lds ? 4 * RP : 16;
             const uint16_t *p = Vh + (int64_t)rbase * v_st.n + co * 8;
 #pragma unroll
             for (int q = 0; q < NU; ++q) {
-                const int dr = 16 * (q >> 2) + (q & 3);
-                const bool ok = rbase + dr < N;
+                const bool ok = rbase + apart * (q >> 2) + (q & 3) < N;
                 exists |= (ok ? 1u : 0u) << q;
-                raw[q] = *reinterpret_cast<const uint4 *>(ok ? p + dr * v_st.n : last);
+                raw[q] = *reinterpret_cast<const uint4 *>(ok ? p + (q >> 2) * (apart * v_st.n) + (q & 3) * v_st.n : last);
             }
         }
 #pragma unroll
@@ -1033,6 +1038,38 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j) rc[j] = stat[co * 8 + j];
         keep_packed(raw);
+        if (v_lds) {
+            constexpr int UNITS = 32 * LPR;  // quads of keys x 8 channels of a tile
+            constexpr int UPT = UNITS > NTHR ? UNITS / NTHR : 1, TP = UNITS > NTHR ? 1 : NTHR / UNITS, ROUNDS = C / kW / TP;
+            static_assert(ROUNDS * UPT * 4 == NU, "a workgroup's chunk is 16 uint4 per thread");
+            static_assert(TP * D * 128 <= NTHR * 64, "the tiles fit in LDS");
+            uint32_t *tile = reinterpret_cast<uint32_t *>(smem) + tid / UNITS * D * 32;
+#pragma unroll
+            for (int rd = 0; rd < ROUNDS; ++rd) {
+                const int T = (part * ROUNDS + rd) * TP;  // (workgroup-uniform) first tile of the round
+                if (T >= nT) break;
+#pragma unroll
+                for (int k = 0; k < UPT; ++k) {
+                    const int kq = (tid + NTHR * k) % UNITS / LPR;
+                    uint32_t *dst = tile + co * 8 * 32 + (kq >> 4) * 16 + (kq & 3) * 4 + (kq >> 2 & 3);
+#pragma unroll
+                    for (int j2 = 0; j2 < 4; ++j2) {
+                        const uint2 w = v_pair_codes<BF16>(&raw[(rd * UPT + k) * 4], rc, j2);
+                        dst[2 * j2 * 32] = w.x;
+                        dst[(2 * j2 + 1) * 32] = w.y;
+                    }
+                }
+                __syncthreads();
+                uint4 *dst = reinterpret_cast<uint4 *>(Vt + ((size_t)bh * nT + T) * D * 128);
+#pragma unroll
+                for (int k = 0; k < TP * D * 8 / NTHR; ++k) {
+                    const int e = tid + NTHR * k;
+                    if (TP == 1 || T + e / (D * 8) < nT) dst[e] = reinterpret_cast<const uint4 *>(smem)[e];
+                }
+                __syncthreads();
+            }
+            return;
+        }
         const int T = (row0 + 64 * half) >> 7;
         if (T < nT)
             v_codes<BF16>(raw, rc, Vt + (((size_t)bh * nT + T) * D + co * 8) * 128 + 64 * (half & 1) + 16 * g);
@@ -1354,10 +1391,20 @@ hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v,
     const bool apart = G == 1 ? NTHR == 512 && 4L * N >= 3 * resident_tokens(NTHR, D)
                               : resident_group_size(N, D, 256) >= 8 || q.first >= 4 * kSlots;
     const int stagger = !apart || q.first < 2 * kSlots ? 0 : NTHR == 256 ? 400 : 700;
+    // The codes of V through LDS or straight from registers.  LDS costs a workgroup a barrier and bank conflicts, the registers' 16-byte
+    // pieces, 128 bytes apart, cost the memory where it is the limit.  By rounds of V's workgroups (us, LDS / registers): d 128, 256 threads,
+    // V alone 300 heads x 1500 (1.8) 42.7 / 40.0, 200 x 3021 (2.3) 54.0 / 53.8, 300 x 2700 (3.2) 67.8 / 70.0, 700 x 3021 (8.2) 151 / 165, K
+    // and V 128 x 4096 (2.0) 84.5 / 83.8, 300 x 2700 123.0 / 126.6; 512 threads 48 x 32768 (6) 277 / 254.  d 64, 256 threads, V alone 300 x
+    // 1500 (0.9) 25.1 / 24.2, 2048 x 512 (2.0) 34.6 / 36.8, K and V 700 x 6042 (8.2) 292 / 297; a head of up to 256 tokens, whose chunk half
+    // of the threads have, 16 x 100 4.4 / 4.9, x 500 6.1 / 5.6; 512 threads, K and V 4 x 131000 (1.0) 51.2 / 51.0, 8 x 130000 (2.0) 104.7 / 106.4,
+    // 40 x 100000 (7.7) 342 / 377.
+    const long v_wgs = tensors == kOnlyK ? 0 : (long)BH * G;
+    const bool v_lds = D == 128 ? NTHR == 256 && 2 * v_wgs >= 5 * kSlots
+                                : NTHR == 256 ? v_wgs >= kSlots || (G == 1 && N <= 256) : 8 * v_wgs >= 15 * kSlots;
 #define SAGE_RESIDENT(Q, GRID)                                                                                          \
     quant_kv_resident_kernel<BF16, D, QMAX, NTHR, Q><<<GRID, NTHR, 0, stream>>>(                                        \
         k, k_st, v, v_st, H, N, G, ws.k_sum_part, v_part, k_mean, v_scale, v_r, k_i8, k_scale, nK, v_fp8, nT,     \
-        wait_ticks, stagger, tensors, q)
+        wait_ticks, stagger, v_lds, tensors, q)
     if (q.x) SAGE_RESIDENT(true, q.first + q.workgroups(NTHR / 256));
     else SAGE_RESIDENT(false, q.first);
 #undef SAGE_RESIDENT

@@ -38,16 +38,20 @@ def test_every_width_writes_the_bits_of_the_three_launches(idx, shape, wait_tick
     _same_bits(want, _quant(k, v, 4.5, 0, wait_ticks), "by shape")
 
 
-# two rounds of workgroups and more, on both sides of the lines from which on a CU's workgroups start apart: 256 threads, heads of one
-# chunk (never) and of seven and eight; 512 threads, a chunk less and more than three quarters full; four rounds of small groups
-MANY = [(1, (1, 1030, 129, 128)), (5, (1, 150, 1700, 128)), (2, (1, 128, 2048, 128)), (2, (1, 513, 300, 128)), (5, (1, 513, 384, 128)),
-        (3, (1, 513, 767, 64)), (3, (1, 513, 1010, 64)), (1, (1, 700, 600, 128))]
+# Many workgroups, on both sides of the lines from which on those of a CU start apart (from two rounds on; 256 threads, heads of one
+# chunk never and of seven and eight chunks; 512 threads, a chunk less and more than three quarters full) and from which on V's codes go
+# through LDS (by the rounds of V's workgroups: d = 128 2.5; d = 64 one, with 512 threads 1.9 -- there with several workgroups per head, too --
+# and a head of up to 256 tokens)
+MANY = [(1030, 129, 128), (150, 1700, 128), (128, 2048, 128), (513, 300, 128), (513, 384, 128), (700, 600, 128), (860, 601, 128),
+        (513, 767, 64), (513, 1010, 64), (340, 1100, 64), (350, 1100, 64), (7, 256, 64), (7, 257, 64), (1000, 600, 64), (14, 70001, 64)]
 
 
-@pytest.mark.parametrize("idx,shape", MANY)
-def test_several_rounds_of_workgroups_write_the_bits_of_the_three_launches(idx, shape):
-    say(f"[quant rounds] cfg{idx} distributions, shape {shape}")
-    k, v = _inputs(idx, shape)
+@pytest.mark.parametrize("wait_ticks", [50_000, -1])
+@pytest.mark.parametrize("H,N,d", MANY)
+def test_several_rounds_of_workgroups_write_the_bits_of_the_three_launches(H, N, d, wait_ticks):
+    say(f"[quant rounds] {H} heads x {N} x {d}, wait {wait_ticks}")
+    g = torch.Generator(device="cuda").manual_seed(H + N)
+    k, v = (torch.randn(1, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
     want = _quant(k, v, 4.5, THREE_LAUNCHES)
-    _same_bits(want, _quant(k, v, 4.5, 0), "K and V together")
-    _same_bits(want, _alone(k, v, 0), "each alone")
+    _same_bits(want, _quant(k, v, 4.5, 0, wait_ticks), "K and V together")
+    _same_bits(want, _alone(k, v, 0, wait_ticks), "each alone")
