@@ -1381,15 +1381,18 @@ hipError_t launch_resident_n(const uint16_t *k, Strides k_st, const uint16_t *v,
         zero_words_kernel<<<cdiv(words, 256), 256, 0, stream>>>(static_cast<uint4 *>(from), words);
     }
     q.first = (tensors == kBothTensors ? 2 * BH : BH) * G;
-    // Where it pays to start the workgroups of a CU apart, from two rounds on (time with / without).  Groups that meet: of 8 and more chunks of
-    // 256 threads 0.95 .. 0.99 (K and V; V alone of 8 to 12 up to 1.02), of 3 to 6 0.97 .. 1.05 below four rounds and 0.96 .. 1.00 from there on.  A
+    // Where it pays to start the workgroups of a CU apart, from two rounds on (time with / without).  Groups that meet: 512 threads 0.96 .. 1.01;
+    // 256 threads from 8 chunks on 0.95 .. 1.02, but not if there are exactly two rounds, whose end is only later (128 heads x 4096 K alone,
+    // d 128 48.9 / 46.3 us, K and V 64 x 4096 48.2 / 46.0), nor V alone at d 64 below four (2.0 .. 2.3 rounds 1.01 .. 1.07); 3 to 6 chunks
+    // 0.97 .. 1.05 below four rounds and 0.96 .. 1.00 from there on.  A
     // head that one workgroup holds meets nobody, and its start is only late: 256 threads, K and V of 1024 heads x 129 x 128 27.9 / 24.9
     // us, x 256 39.1 / 36.2, 2048 x 129 45.4 / 42.5; 512 threads, 512 x 257 30.5 / 27.6, x 300 31.4 / 28.9; only from three quarters of
     // a chunk on, when a CU's two load and store long enough, 512 x 400 36.6 / 36.1, 1024 x 400 66.7 / 67.7, 600 x 512 46.2 / 48.3, d 64 512 x 800
     // 38.7 / 40.1, x 1024 43.6 / 45.2.
     constexpr int kSlots = kCUs * (1024 / NTHR);
     const bool apart = G == 1 ? NTHR == 512 && 4L * N >= 3 * resident_tokens(NTHR, D)
-                              : resident_group_size(N, D, 256) >= 8 || q.first >= 4 * kSlots;
+                              : NTHR == 512 || q.first >= 4 * kSlots ||
+                                    (q.first > 2 * kSlots && G >= 8 && !(D == 64 && tensors == kOnlyV));
     const int stagger = !apart || q.first < 2 * kSlots ? 0 : NTHR == 256 ? 400 : 700;
     // The codes of V through LDS or straight from registers.  LDS costs a workgroup a barrier and bank conflicts, the registers' 16-byte
     // pieces, 128 bytes apart, cost the memory where it is the limit.  By rounds of V's workgroups (us, LDS / registers): d 128, 256 threads,
