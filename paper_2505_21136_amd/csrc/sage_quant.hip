@@ -1306,25 +1306,27 @@ hipError_t quant_q_impl(const uint16_t *q, Strides st, int8_t *q_i8, float *q_sc
 //   * K or V alone: three short launches are independent of each other's workgroups, where the single read has a clear and
 //     a meeting, 3 to 4 us that fewer workgroups than fill the chip do not win back (d = 128, K, H 1, G 128 16.3 / 17.2 / 17.5).
 enum class Quantise { kBoth, kOnlyK, kOnlyV, kKWithQ };
+constexpr int wide_above(int d) { return d == 128 ? 96 : 128; }  // the largest G that is better off with 256 threads
 inline int resident_threads(Quantise what, int groups, int N, int d) {
     const int path = g_kv_path.load();
     const int G = resident_group_size(N, d, 256);
     const long wgs = (long)groups * G, wgs512 = (long)groups * resident_group_size(N, d, 512);
     if (path == 1) return 0;
-    if (path == 2) return G == 2 || G > (d == 128 ? 96 : 128) ? 512 : 256;
+    const bool wide = G > wide_above(d);
+    if (path == 2) return G == 2 || wide ? 512 : 256;
     if (G == 1) return 256;
     if (G == 2) return 512;
     if (G > kResidentMaxGroup) return 0;
     if (d == 128) {
-        if (G <= 96) return 256;
+        if (!wide) return 256;
         if (what == Quantise::kOnlyK && wgs512 < kCUs / 2) return 0;
         return what != Quantise::kKWithQ && G > 128 && wgs512 > 2 * kCUs && wgs512 < 4 * kCUs ? 0 : 512;
     }
     switch (what) {
-        case Quantise::kOnlyK: return G <= 128 && (G <= 48 || wgs >= 2 * kCUs) ? 256 : 0;
-        case Quantise::kOnlyV: return G <= 128 ? 256 : wgs512 >= kCUs / 2 ? 512 : 0;
-        case Quantise::kKWithQ: return G <= 128 ? 256 : 0;
-        default: return G <= 128 ? 256 : wgs512 >= 4 * kCUs ? 512 : 0;
+        case Quantise::kOnlyK: return !wide && (G <= 48 || wgs >= 2 * kCUs) ? 256 : 0;
+        case Quantise::kOnlyV: return wide ? 512 : 256;
+        case Quantise::kKWithQ: return wide ? 0 : 256;
+        default: return !wide ? 256 : wgs512 >= 4 * kCUs ? 512 : 0;
     }
 }
 
@@ -1335,7 +1337,10 @@ inline int resident_threads(Quantise what, int groups, int N, int d) {
 // G 1 7.4 / 7.8.  K alone d = 128, H 8, G 32 14.3 / 12.5, H 32, G 16 (512) 18.7 / 19.0; d = 64, H 2, G 1 8.5 / 6.7, H 128, G 2 13.4 / 12.5.
 // V alone G 2 7.0 / 7.5, H 32, G 4 10.7 / 8.2, G 16 (512) 16.4 / 13.9, H 32, G 32 (1024) 24.7 / 29.2.  K with Q, d = 128, H 2, G 4
 // 12.0 / 8.6, H 32, G 4 13.4 / 12.1, H 8, G 32 17.1 / 18.3, H 64, G 2 (300 tokens; the single read meets nobody) 9.5 / 10.0; d = 64,
-// H 32, G 1 8.8 / 7.2.  Every workgroup of a head reads the G partials: K alone, d = 64, H 2, G 118 16.4 / 17.6.
+// H 32, G 1 8.8 / 7.2.  Every workgroup of a head reads the G partials: K alone, d = 64, H 2, G 118 16.4 / 17.6; V alone, beyond one
+// workgroup per CU and where the single read has 512 threads, d = 128, H 4, G 96 18.3 / 17.3, G 120 17.5 / 19.9, H 2, G 160 16.5 / 17.3, G 256 18.8 /
+// 22.0, d = 64, H 2, G 256 18.1 / 19.0; with one per CU H 2, G 128 14.8 / 13.8, H 1, G 200 14.9 / 14.8; beyond the single read's reach three
+// launches are no better, H 1, G 320 27.6 / 20.9, G 512 31.2 / 27.2 (tensors that are not in the last-level cache).
 inline bool chunks_pay(Quantise what, int heads, int N, int d) {
     if (g_kv_path.load() != 0) return false;
     const int G = resident_group_size(N, d, 256);
@@ -1343,7 +1348,7 @@ inline bool chunks_pay(Quantise what, int heads, int N, int d) {
     if (G == 1) return d == 64 && (what == Quantise::kOnlyK || what == Quantise::kKWithQ) && heads <= kCUs / 4;
     switch (what) {
         case Quantise::kOnlyK: return wgs <= kCUs / 2 || (wgs <= kCUs && G <= 64);
-        case Quantise::kOnlyV: return G > 2 && wgs <= 2 * kCUs;
+        case Quantise::kOnlyV: return G > 2 && (wgs <= kCUs || (wgs <= 2 * kCUs && (G <= wide_above(d) || G > kResidentMaxGroup)));
         default: return wgs <= (G == 2 ? kCUs / 4 : kCUs / 2);
     }
 }

@@ -1,5 +1,5 @@
-"""The quantisers' two launches over chunks (small calls), at the edges of chunks, K blocks and V tiles, up to the largest calls that
-take them: K and V together, each alone, K with Q, the INT4 codes and strided inputs write the bits of the three launches, and the codes
+"""The quantisers' two launches over chunks (small calls), at the edges of chunks, K blocks and V tiles, and V alone up to the largest calls
+that take them: K and V together, each alone, K with Q, the INT4 codes and strided inputs write the bits of the three launches, and the codes
 of Q those of a launch of its own."""
 import pytest
 import torch
@@ -56,3 +56,26 @@ def test_block_means_beside_the_quantiser_equal_those_of_their_own_launch(hq, hk
     sage.diag_quant_kv_path(path)
     got = sage.sage_attn_fwd_4bit(q, k, v, causal=False)
     assert torch.equal(want.view(torch.int16), got.view(torch.int16))
+
+
+# V alone, heads x tokens on both sides of the lines: one workgroup per CU, the most partials beyond it, the single read's reach
+V_ROUTES = [(2, 32731, 128, True), (2, 32769, 128, False), (4, 24539, 128, True), (4, 24700, 128, False), (2, 65499, 128, False),
+            (1, 65499, 128, True), (1, 131035, 128, True), (4, 65499, 64, True), (3, 70000, 64, False), (2, 65500, 64, True),
+            (2, 131035, 64, False), (1, 262107, 64, True)]
+
+
+@pytest.mark.parametrize("H,N,d,chunks", V_ROUTES)
+def test_v_alone_takes_chunks_where_they_pay_and_writes_the_same_bits(H, N, d, chunks):
+    """A chunk leaves a partial per channel in the scratch; the single read leaves half as many there (its workgroups hold two chunks)."""
+    say(f"[quant chunks] V alone {H} heads x {N} x {d}")
+    g = torch.Generator(device="cuda").manual_seed(H + N)
+    v = torch.randn(1, H, N, d, generator=g, device="cuda").to(torch.float16)
+    sage.diag_quant_kv_path(THREE_LAUNCHES)
+    want = sage.sage_quant_v(v)
+    sage.diag_quant_kv_path(0)
+    ws = torch.full((sage.quant_workspace_bytes(1, H, N, d),), 0x5A, dtype=torch.uint8, device="cuda")
+    got = sage.sage_quant_v(v, workspace=ws)
+    for a, b in zip(want, got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    partials = -(-N // (256 if d == 128 else 512)) * H * d * 4
+    assert (int((ws != 0x5A).sum()) > 0.75 * partials) == chunks
