@@ -1286,7 +1286,11 @@ template <bool BF16, int D>
 hipError_t quant_q_impl(const uint16_t *q, Strides st, int8_t *q_i8, float *q_scale, int BH, int H, int N,
                         hipStream_t stream) {
     const int nQ = cdiv(N, kBQ);
-    quant_int8_kernel<BF16, D, kBQ, 0, 127><<<dim3(nQ, BH), 256, 0, stream>>>(q, st, H, nullptr, q_i8, q_scale, N, nQ);
+    // (a block that is half empty at least: its loads would repeat the last row; 1467 heads x 4, d 128 4.9 -> 4.05 us, 1000 x 40 5.05 -> 4.4)
+    if (N <= kBQ / 2)
+        quant_int8_kernel<BF16, D, kBQ / 2, 0, 127><<<dim3(1, BH), 256, 0, stream>>>(q, st, H, nullptr, q_i8, q_scale, N, 1);
+    else
+        quant_int8_kernel<BF16, D, kBQ, 0, 127><<<dim3(nQ, BH), 256, 0, stream>>>(q, st, H, nullptr, q_i8, q_scale, N, nQ);
     return hipGetLastError();
 }
 
