@@ -1341,7 +1341,8 @@ inline int resident_threads(Quantise what, int groups, int N, int d) {
 // G 1 7.4 / 7.8.  K alone d = 128, H 8, G 32 14.3 / 12.5, H 32, G 16 (512) 18.7 / 19.0; d = 64, H 2, G 1 8.5 / 6.7, H 128, G 2 13.4 / 12.5.
 // V alone G 2 7.0 / 7.5, H 32, G 4 10.7 / 8.2, G 16 (512) 16.4 / 13.9, H 32, G 32 (1024) 24.7 / 29.2.  K with Q, d = 128, H 2, G 4
 // 12.0 / 8.6, H 32, G 4 13.4 / 12.1, H 8, G 32 17.1 / 18.3, H 64, G 2 (300 tokens; the single read meets nobody) 9.5 / 10.0; d = 64,
-// H 32, G 1 8.8 / 7.2.  Every workgroup of a head reads the G partials: K alone, d = 64, H 2, G 118 16.4 / 17.6; V alone, beyond one
+// H 32, G 1 8.8 / 7.2, but with few K blocks in the one workgroup of a head (one launch / two) K alone H 8 x 64 tokens 5.0 / 6.1, x 256
+// 6.2 / 6.5, H 1 x 320 6.4 / 6.3, H 32 x 512 8.0 / 6.8.  Every workgroup of a head reads the G partials: K alone, d = 64, H 2, G 118 16.4 / 17.6; V alone, beyond one
 // workgroup per CU and where the single read has 512 threads, d = 128, H 4, G 96 18.3 / 17.3, G 120 17.5 / 19.9, H 2, G 160 16.5 / 17.3, G 256 18.8 /
 // 22.0, d = 64, H 2, G 256 18.1 / 19.0; with one per CU H 2, G 128 14.8 / 13.8, H 1, G 200 14.9 / 14.8; beyond the single read's reach three
 // launches are no better, H 1, G 320 27.6 / 20.9, G 512 31.2 / 27.2 (tensors that are not in the last-level cache).
@@ -1349,7 +1350,7 @@ inline bool chunks_pay(Quantise what, int heads, int N, int d) {
     if (g_kv_path.load() != 0) return false;
     const int G = resident_group_size(N, d, 256);
     const long wgs = (long)heads * G;
-    if (G == 1) return d == 64 && (what == Quantise::kOnlyK || what == Quantise::kKWithQ) && heads <= kCUs / 4;
+    if (G == 1) return d == 64 && (what == Quantise::kOnlyK || what == Quantise::kKWithQ) && heads <= kCUs / 4 && N > 4 * kBK;
     switch (what) {
         case Quantise::kOnlyK: return wgs <= kCUs / 2 || (wgs <= kCUs && G <= 64);
         case Quantise::kOnlyV: return G > 2 && (wgs <= kCUs || (wgs <= 2 * kCUs && (G <= wide_above(d) || G > kResidentMaxGroup)));

@@ -79,3 +79,20 @@ def test_v_alone_takes_chunks_where_they_pay_and_writes_the_same_bits(H, N, d, c
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     partials = -(-N // (256 if d == 128 else 512)) * H * d * 4
     assert (int((ws != 0x5A).sum()) > 0.75 * partials) == chunks
+
+
+@pytest.mark.parametrize("H,N,chunks", [(8, 64, False), (64, 128, False), (8, 256, False), (8, 257, True), (64, 512, True), (65, 512, False)])
+def test_k_of_heads_that_one_workgroup_holds(H, N, chunks):
+    """K alone and with Q, d = 64: two launches from five K blocks on, before that one, which writes nothing to its scratch."""
+    say(f"[quant chunks] K alone {H} heads x {N} x 64")
+    g = torch.Generator(device="cuda").manual_seed(H + N)
+    q, k = (torch.randn(1, H, N, 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    sage.diag_quant_kv_path(THREE_LAUNCHES)
+    want = sage.sage_quant_k(k)
+    sage.diag_quant_kv_path(0)
+    for with_q in (False, True):
+        ws = torch.full((sage.quant_workspace_bytes(1, H, N, 64),), 0x5A, dtype=torch.uint8, device="cuda")
+        got = sage.sage_quant_qk(q, k, workspace=ws)[1::2] if with_q else sage.sage_quant_k(k, workspace=ws)
+        for a, b in zip((want[0], want[1]), got):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+        assert bool((ws == 0x5A).all()) != chunks
