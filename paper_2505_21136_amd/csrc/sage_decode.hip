@@ -413,6 +413,8 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float *__restrict_
 // 4*(t % (D/4)) .. +3 and the ranges t / (D/4), + 256/(D/4), ...; the shares are added in a fixed order through LDS, so the
 // result does not depend on timing.  Bound by latency with few rows: one round trip to memory and one barrier up to 32 ranges (d = 64:
 // 64); with the maximum found through LDS first, nine barriers and a second round trip, 1.0 us more (8 heads x 4096 keys, 16 ranges).
+// With hundreds of ranges a CU's share of memory is what counts, S * (D + 2) floats on one CU, and every extra read of the maxima shows
+// (one row of 512 ranges, whole call, each wavefront reading all of them / sharing them: d 64 14.4 / 12.6 us, d 128 19.8 / 18.1).
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ part_acc, const float *__restrict__ part_ml,
                                                     const float *__restrict__ dv, uint16_t *__restrict__ out, int Hq,
@@ -420,13 +422,13 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ pa
     constexpr int Q4 = D / 4;      // channel quads
     constexpr int SL = 256 / Q4;   // range lanes
     __shared__ float4 acc_s[SL][Q4];
-    __shared__ float l_s[SL];
+    __shared__ float l_s[SL], m_s[4];
     const int row = blockIdx.x;  // (b*Hq + hq)*Nq + r
     int bhk;
     size_t p0, ps;
     partial_rows(row, Hq, Hkv, group, Nq, S, T, bhk, p0, ps);
     const int tid = threadIdx.x, cq = tid % Q4, sl = tid / Q4;
-    // this thread's first FIRST ranges and, for the row's maximum (every wavefront finds it itself), one m per lane: one round trip to
+    // this thread's first FIRST ranges and, for the row's maximum (up to 64 ranges every wavefront finds it itself), one m per lane: one round trip to
     // memory up to FIRST * SL ranges
     constexpr int FIRST = 4;
     float2 ml[FIRST];
@@ -437,9 +439,18 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ pa
         ml[k] = *reinterpret_cast<const float2 *>(part_ml + p * 2);
         a[k] = *reinterpret_cast<const float4 *>(part_acc + p * D + 4 * cq);
     }
-    float mx = -INFINITY;
-    for (int s = tid & 63; s < S; s += 64) mx = fmaxf(mx, part_ml[(p0 + s * ps) * 2]);
-    mx = wave_max(mx);
+    // (a maximum's neighbours are 128 bytes apart, so that 64 of them cost the texture path 64 cycles: beyond 64 the workgroup shares them)
+    float mx;
+    if (S <= 64) {
+        mx = wave_max(part_ml[(p0 + min(tid & 63, S - 1) * ps) * 2]);
+    } else {
+        mx = -INFINITY;
+        for (int s = tid; s < S; s += 256) mx = fmaxf(mx, part_ml[(p0 + s * ps) * 2]);
+        mx = wave_max(mx);
+        if ((tid & 63) == 0) m_s[tid >> 6] = mx;
+        __syncthreads();
+        mx = fmaxf(fmaxf(m_s[0], m_s[1]), fmaxf(m_s[2], m_s[3]));
+    }
     float l = 0.0f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     // a range in which the row saw no key has m = -inf, l = 0, acc = 0: its weight 2^(-inf) = 0 is exact
@@ -454,7 +465,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const float *__restrict__ pa
 #pragma unroll
     for (int k = 0; k < FIRST; ++k)
         if (sl + k * SL < S) add(ml[k], a[k]);
-#pragma unroll 8
+#pragma unroll 4
     for (int s = sl + FIRST * SL; s < S; s += SL)
         add(*reinterpret_cast<const float2 *>(part_ml + (p0 + s * ps) * 2),
             *reinterpret_cast<const float4 *>(part_acc + (p0 + s * ps) * D + 4 * cq));

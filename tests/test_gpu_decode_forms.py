@@ -19,6 +19,8 @@ FORMS = [  # B, Hq, Hkv, Nq, Nk, d, split_keys, heads compared
     (2, 65, 65, 49, 400, 128, 128, {(0, 0), (1, 64)}),    # 130 of 49 rows, 2 x 4 wavefronts: all of LDS
     (1, 16, 16, 1, 8197, 64, 128, {(0, 0), (0, 15)}),     # 1040 wavefronts of one step, four to a workgroup, 65 ranges
     (1, 8, 8, 64, 4700, 128, 128, {(0, 0), (0, 7)}),      # 592 wavefronts in pairs, four to a workgroup
+    (1, 2, 2, 1, 8193, 128, 128, None),       # 65 ranges of a row to combine, ...
+    (1, 4, 1, 2, 33000, 64, 128, None),       # ... 258: more than a workgroup's threads
 ]
 
 
