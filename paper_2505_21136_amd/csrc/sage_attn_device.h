@@ -1,7 +1,7 @@
 // Device-side building blocks shared by the attention kernels of libsage (gfx950): vector types, the lane
 // exchanges over the four 16-lane rows of a wavefront, 16-bit conversions, and the online-softmax step of the
 // 8+8 path (paper Sec. 2.1 for the online softmax and the scales, Sec. 3.1 for the bounded FP8 range of P~).
-// Included by the attention translation units; every function is inlined.
+// Included by the attention translation units and, for the conversions and codes, by the quantiser; every function is inlined.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <limits.h>

@@ -11,6 +11,7 @@
 // step (x - mean, a / range, range / a, x * r) is one correctly rounded binary32
 // operation, which is what makes codes and scales reproducible bit for bit
 // (paper Sec. 2.1 for the scales, Sec. 3 for the smoothing).
+#include "sage_attn_device.h"
 #include "sage_internal.h"
 
 #include <algorithm>
@@ -18,25 +19,6 @@
 
 namespace sage {
 namespace {
-
-template <bool BF16>
-__device__ __forceinline__ float to_f32(uint32_t h16) {
-    if constexpr (BF16) {
-        return __builtin_bit_cast(float, h16 << 16);
-    } else {
-        return (float)__builtin_bit_cast(_Float16, (uint16_t)h16);
-    }
-}
-
-template <bool BF16>
-__device__ __forceinline__ void unpack8(const uint4 &u, float (&f)[8]) {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f[2 * i] = to_f32<BF16>(w[i] & 0xffffu);
-        f[2 * i + 1] = to_f32<BF16>(w[i] >> 16);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Partial column statistics over chunks of kStatRows tokens.
@@ -194,7 +176,8 @@ __global__ __launch_bounds__(1024) void finalize_kv_kernel(const double *__restr
 }
 
 // Maximum over the wavefront of a value >= 0 (not NaN), in every lane: within rows of 16 lanes by DPP, then over the four rows, whose
-// bit patterns order like integers, in scalar registers.
+// bit patterns order like integers, in scalar registers.  (wave_max of the attention kernels exchanges the rows in vector registers, which
+// with a block's 16 maxima in a row is slower: K and V of 16 heads x 100000, d 64 148.5 / 145.7 us.)
 __device__ __forceinline__ float wave_max_abs(float x) {
 #define SAGE_DPP(CTRL) \
     x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true)))
@@ -599,22 +582,6 @@ __global__ __launch_bounds__(256) void zero_words_kernel(uint4 *w, int n) {
 }
 
 
-// Eight codes rint(x * rcp), one per byte: rint(y) for |y| <= 127 as the low byte of fl(y + 1.5 * 2^23) -- the addition rounds y to the
-// nearest integer, ties to even, and the sum's bit pattern is 0x4B400000 + that integer.
-__device__ __forceinline__ uint2 code_bytes(const float (&x)[8], float rcp) {
-    uint32_t cb[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) cb[j] = __builtin_bit_cast(uint32_t, x[j] * rcp + 12582912.0f);
-    uint32_t w[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const uint32_t lo = __builtin_amdgcn_perm(cb[4 * h + 1], cb[4 * h], 0x0c0c0400u);
-        const uint32_t hi = __builtin_amdgcn_perm(cb[4 * h + 3], cb[4 * h + 2], 0x0c0c0400u);
-        w[h] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    }
-    return make_uint2(w[0], w[1]);
-}
-
 // The FP8 codes of channels 2 j2 and 2 j2 + 1 (one packed dword of each key; of the eight with the reciprocals rc) of four keys.
 template <bool BF16>
 __device__ __forceinline__ uint2 v_pair_codes(const uint4 *keys, const float (&rc)[8], int j2) {
@@ -920,7 +887,7 @@ __global__ __launch_bounds__(NTHR, 4) void quant_kv_resident_kernel(
             for (int i = 0; i < IPB; ++i) {
                 const int it = b * IPB + i;
                 const int r = row0 + it * RP + rr;
-                if (it < nrow) *reinterpret_cast<uint2 *>(k_codes + ((size_t)bh * N + r) * D + co * 8) = code_bytes(x[i], rcp);
+                if (it < nrow) *reinterpret_cast<uint2 *>(k_codes + ((size_t)bh * N + r) * D + co * 8) = int8_codes(x[i], rcp);
             }
         }
     } else {
@@ -1235,7 +1202,7 @@ __global__ __launch_bounds__(256) void chunk_codes_kernel(const uint16_t *__rest
         for (int it = 0; it < ITER; ++it) {
             const int r = row0 + it * RP;
             if (r < N)
-                *reinterpret_cast<uint2 *>(k_codes + ((size_t)bh * N + r) * D + co * 8) = code_bytes(y[it], rcp);
+                *reinterpret_cast<uint2 *>(k_codes + ((size_t)bh * N + r) * D + co * 8) = int8_codes(y[it], rcp);
         }
     } else {
         const int row0 = (x - nK) * chunk_tokens<D>(), half = rr >> 2, g = rr & 3;
