@@ -31,6 +31,7 @@ def sources():
     out = [os.path.join(CSRC, u) for u, _ in UNITS]
     out.append(os.path.join(CSRC, "sage_internal.h"))
     out.append(os.path.join(CSRC, "sage_attn_device.h"))
+    out.append(os.path.join(CSRC, "sage_tile_copy.h"))
     out.append(os.path.join(os.path.dirname(HERE), "include", "sage.h"))
     return out
 

@@ -117,7 +117,7 @@ __device__ __forceinline__ void issue_tile_piece(uint8_t *dst, const uint8_t *he
     constexpr int TILE = 128 * D;
     // (piece k of a wavefront lies 4 KB after piece 0 on both sides: the swizzles repeat every 8 rows)
     const int first = j * TILE + k * 4096;
-    lds_copy16(lds_copy_rsrc(head + first, max(head_bytes - first, 0)), voff, lds_address(dst) + (4 * k + w) * 1024);
+    lds_copy16(lds_copy_rsrc(head + first, copy_left(head_bytes, first)), voff, lds_address(dst) + (4 * k + w) * 1024);
 }
 #endif  // __HIP_DEVICE_COMPILE__
 
@@ -197,14 +197,7 @@ __global__ __launch_bounds__(256, (attn_waves_per_simd<D>())) void attn_kernel(
     const int k_bytes = Nk * D, v_bytes = nT * D * 128;
 
     // per-lane source offsets of this wavefront's piece 0 (the LDS side is linear in the lane index)
-    int k_voff, v_voff;
-    {
-        const int slot = wave * 64 + lane;
-        constexpr int CPR = D / 16;  // chunks per K row
-        const int kr = slot / CPR, kc = slot % CPR, vr = slot >> 3, vc = slot & 7;
-        k_voff = kr * D + ((kc ^ k_swz<D>(kr)) << 4);
-        v_voff = vr * 128 + ((vc ^ (vr & 7)) << 4);
-    }
+    const int k_voff = k_source<D>(wave * 64 + lane), v_voff = v_source(wave * 64 + lane);
 
     // key steps [jb, nsteps) of this workgroup (jb = 0 unless SPLIT)
     int nsteps = nT;

@@ -10,6 +10,8 @@
 
 #include <type_traits>
 
+#include "sage_tile_copy.h"
+
 namespace sage {
 namespace {
 
@@ -17,17 +19,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
-
-// 16-byte-chunk swizzles.  K^ tile: row = key, D bytes per row.  V^ tile: row = channel, 128 bytes per row.
-template <int D>
-__device__ __forceinline__ int k_swz(int row) {
-    return D == 128 ? (row & 7) : ((row >> 1) & 3);
-}
-template <int D>
-__device__ __forceinline__ int k_off(int row, int c16) {
-    return row * D + ((c16 ^ k_swz<D>(row)) << 4);
-}
-__device__ __forceinline__ int v_off(int row, int c16) { return row * 128 + ((c16 ^ (row & 7)) << 4); }
 
 __device__ __forceinline__ int imax3(int a, int b, int c) { return max(max(a, b), c); }
 

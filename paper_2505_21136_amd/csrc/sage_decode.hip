@@ -128,12 +128,10 @@ __global__ __launch_bounds__(TOGETHER ? 512 : 256, 2) void decode_kernel(
     // arrive with the last of them (1024 wavefronts x 2 steps, d 128: 18.5 -> 17.6 us). ----
     int koff[NL], voff_[NL];
     {
-        constexpr int CPR = D / 16;  // 16-byte chunks per K row
-        const int kr = lane / CPR, kc = lane % CPR, vr = lane >> 3, vc = lane & 7;
 #pragma unroll
         for (int p = 0; p < NL; ++p) {
-            koff[p] = kr * D + ((kc ^ k_swz<D>(kr)) << 4) + p * 1024;
-            voff_[p] = D == 128 ? koff[p] : vr * 128 + ((vc ^ (vr & 7)) << 4) + p * 1024;
+            koff[p] = k_source<D>(lane) + p * 1024;
+            voff_[p] = D == 128 ? koff[p] : v_source(lane) + p * 1024;
         }
     }
     const int ring = wave * (2 * HALF), ring_lds = lds_address(lds) + ring;
@@ -141,8 +139,8 @@ __global__ __launch_bounds__(TOGETHER ? 512 : 256, 2) void decode_kernel(
     const auto copy_half = [&](int j, auto part_c, int i) {
         constexpr int PART = decltype(part_c)::value;
         if (i < halves) {
-            const int first = (j * 2 + (PART & 1)) * HALF;
-            const v4i r = PART < 2 ? lds_copy_rsrc(Kh + first, max(k_bytes - first, 0)) : lds_copy_rsrc(Vh + first, v_bytes - first);
+            const int first = half_first<D>(j, PART);
+            const v4i r = PART < 2 ? lds_copy_rsrc(Kh + first, copy_left(k_bytes, first)) : lds_copy_rsrc(Vh + first, v_bytes - first);
 #pragma unroll
             for (int p = 0; p < NL; ++p) lds_copy16(r, PART < 2 ? koff[p] : voff_[p], ring_lds + (PART & 1) * HALF + p * 1024);
         }

@@ -122,12 +122,10 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
     constexpr int NVO = D == 128 ? NP : 1;
     int kvoff[NVO], vvoff_ = 0;
     {
-        const int s = wave * 64 + lane;
-        constexpr int CPR = D / 16;  // 16-byte chunks per K row
-        const int kr = s / CPR, kc = s % CPR, vr = s >> 3, vc = s & 7;
+        const int slot = wave * 64 + lane;
 #pragma unroll
-        for (int k = 0; k < NVO; ++k) kvoff[k] = kr * D + ((kc ^ k_swz<D>(kr)) << 4) + k * 4096;
-        if constexpr (D != 128) vvoff_ = vr * 128 + ((vc ^ (vr & 7)) << 4);
+        for (int k = 0; k < NVO; ++k) kvoff[k] = k_source<D>(slot) + k * 4096;
+        if constexpr (D != 128) vvoff_ = v_source(slot);
     }
 
     // key steps [jb, nsteps) of this workgroup (jb = 0 unless SPLIT)
@@ -148,7 +146,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
     // tile) is never fetched and reads as zero; a step the workgroup does not have gets size 0.
     const int lds_piece = lds_address(lds) + wave * 1024;
     const auto copy_piece = [&](const uint8_t *head, int bytes, int voff, int j, int dst, int k) {
-        const int first = j * TILE + (D == 128 ? 0 : k * 4096), left = j < nsteps ? max(bytes - first, 0) : 0;
+        const int first = j * TILE + (D == 128 ? 0 : k * 4096), left = j < nsteps ? copy_left(bytes, first) : 0;
         lds_copy16(lds_copy_rsrc(head + first, left), voff, lds_piece + dst + k * 4096);
     };
     const auto copy_k = [&](int j, int k) { copy_piece(Kh, k_bytes, kvoff[D == 128 ? k : 0], j, (j & 1) * TILE, k); };

@@ -88,10 +88,8 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
         const uint8_t *Kh = reinterpret_cast<const uint8_t *>(Kc) + (size_t)bhk * Nk * D;
         const uint8_t *Vh = Vt + (size_t)bhk * nT * D * 128;
         const int k_bytes = Nk * D, v_bytes = nT * D * 128;
-        constexpr int CPR = D / 16;  // 16-byte chunks per K row
         // (both swizzles repeat every 8 rows, i.e. every 1 KB piece or sooner, so one offset serves all pieces)
-        const int kr = lane / CPR, kc = lane % CPR, vr = lane >> 3, vc = lane & 7;
-        const int kvoff = kr * D + ((kc ^ k_swz<D>(kr)) << 4), vvoff = vr * 128 + ((vc ^ (vr & 7)) << 4);
+        const int kvoff = k_source<D>(lane), vvoff = v_source(lane);
         const int dst0 = lds_address(lds);
         const auto copy = [&](const uint8_t *head, int bytes, int voff, int j, int dst) {
             if (j >= nsteps) return;
@@ -99,7 +97,7 @@ __global__ __launch_bounds__(256 * RG + 128) void spread_kernel(
             for (int k = 0; k < NP; ++k) {
                 const int off = (2 * k + pw) * 1024, first = j * TILE + off;
                 // (bounded to what is left of the head's buffer: rows >= Nk of the last K^ tile read as zero)
-                lds_copy16(lds_copy_rsrc(head + first, max(bytes - first, 0)), voff, dst0 + dst + off);
+                lds_copy16(lds_copy_rsrc(head + first, copy_left(bytes, first)), voff, dst0 + dst + off);
             }
         };
         const auto copy_k = [&](int j) { copy(Kh, k_bytes, kvoff, j, (j & 3) * TILE); };

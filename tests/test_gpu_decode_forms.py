@@ -1,6 +1,6 @@
 """sage_attn_fwd_decode in each of the shapes its launch can take -- the ranges of a K/V head in one workgroup or in workgroups of one
 or four wavefronts with a second launch, one or two row tiles per wavefront, one or two wavefronts per range, the last tiles ragged --
-against the oracle on the same ranges; and, on the CPU, the addresses of its copies into LDS."""
+against the oracle on the same ranges.  (tests/test_tile_copy_bounds.py has the addresses of its copies.)"""
 import numpy as np
 import pytest
 import torch
@@ -69,29 +69,3 @@ def test_one_launch_where_it_pays_and_the_same_bits_either_way(H, rows, Nk, d, s
     few = sage.sage_attn_fwd_decode(q[:, -2:].contiguous(), *(t[:, -2:].contiguous() for t in cache), causal=True, split_keys=split)
     assert torch.isfinite(out.float()).all()
     assert torch.equal(out[:, -2:].view(torch.int16), few.view(torch.int16))
-
-
-@pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("Nk", [1, 63, 64, 65, 127, 128, 129, 200, 1000])
-def test_half_tile_copies_stay_inside_the_buffer_and_cover_it(Nk, D):
-    """copy_half of decode_kernel: lane l of piece p fetches 16 bytes at voff[p] of a descriptor that begins with the half tile and ends
-    with the head's buffer (a chunk that does not fit is not fetched), and puts them at 1024 p + 16 l of the slot."""
-    half, lanes = 64 * D, np.arange(64)
-    nT = -(-Nk // 128)
-    for is_v in (False, True):
-        row_bytes = 128 if is_v else D
-        cpr = row_bytes // 16
-        row, c = lanes // cpr, lanes % cpr
-        swizzle = (lambda r: r & 7) if row_bytes == 128 else (lambda r: (r >> 1) & 3)
-        total = nT * D * 128 if is_v else Nk * D
-        for i in range(2 * nT):
-            first, src, dst = i * half, [], []
-            for p in range(half // 1024):
-                voff = row * row_bytes + ((c ^ swizzle(row)) << 4) + 1024 * p
-                ok = voff + 16 <= max(total - first, 0)
-                src.append(voff[ok])
-                dst.append((1024 * p + 16 * lanes)[ok])
-            src, dst = np.concatenate(src), np.concatenate(dst)
-            assert np.array_equal(np.sort(src), np.arange(0, min(half, max(total - first, 0)), 16)), (is_v, i)
-            r = src // row_bytes
-            assert np.array_equal(dst, r * row_bytes + (((src % row_bytes // 16) ^ swizzle(r)) << 4)), (is_v, i)
