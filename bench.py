@@ -45,21 +45,21 @@ PROFILED = {
 }
 
 
-def alu_bound(prof):
-    """The co-limit of the MFMA roofline: vector instruction issue, with every instruction issued alone.
-    Cycles per wavefront-step from the measured instruction mix -- 4 cycles per
-    full-rate instruction and per MFMA, 8 per half-rate instruction (which adds up to the measured SQ_ACTIVE_INST_VALU within
-    1 %; two wavefronts of a SIMD can issue an FP32 addition, multiplication or FMA together with an instruction of 4 cycles, which
-    they do where the kernel raises their priority around the exponentials) -- against the MFMA pipe's own cycles for the
-    same step (32 per INT8 32x32x32, 64 per FP8 32x32x64): their ratio is the fraction of the MFMA peak this instruction mix can reach at equal clock."""
+def one_by_one(prof):
+    """Beside the MFMA roofline: vector instruction issue, with every instruction issued alone.
+    Cycles per wavefront-step from the measured instruction mix -- 4 cycles per full-rate instruction and per MFMA, 8 per half-rate
+    instruction (which adds up to the measured SQ_ACTIVE_INST_VALU within 1 %) -- against the MFMA pipe's own cycles for the same step (32
+    per INT8 32x32x32, 64 per FP8 32x32x64).  Their ratio is the fraction of the MFMA peak that this mix reaches at equal clock if no two
+    instructions are ever issued together.  That is not a bound: two wavefronts of a SIMD can issue an FP32 addition, multiplication or FMA
+    together with an instruction of 4 cycles, and do where the kernel raises their priority around the exponentials (valu_busy above 1)."""
     if not prof:
         return None
     n_mfma = prof["mfma_i8"] + prof["mfma_f8"]
     other = prof["valu_per_step"] - n_mfma
-    port = 4.0 * (other - prof["half_rate"]) + 8.0 * prof["half_rate"] + 4.0 * n_mfma
+    issue = 4.0 * (other - prof["half_rate"]) + 8.0 * prof["half_rate"] + 4.0 * n_mfma
     pipe = 32.0 * prof["mfma_i8"] + 64.0 * prof["mfma_f8"]
-    return {"port_cycles_per_wavefront_step": round(port, 1), "mfma_cycles_per_wavefront_step": pipe,
-            "frac_of_peak_allowed": round(pipe / port, 4), "peak_allowed": round(PEAK_MFMA_8BIT / 1e12 * pipe / port, 1),
+    return {"issue_cycles_per_wavefront_step": round(issue, 1), "mfma_cycles_per_wavefront_step": pipe,
+            "frac_of_peak": round(pipe / issue, 4), "rate": round(PEAK_MFMA_8BIT / 1e12 * pipe / issue, 1),
             "unit": "TFLOP/s", "instruction_mix_from": prof["source"]}
 
 
@@ -225,7 +225,7 @@ def main():
             "peak_measured": round(peak_measured, 1) if peak_measured else None,
             "frac_of_peak_measured": round(attn_tops / peak_measured, 4) if peak_measured else None,
             # from the rocprofv3 counters of this workload (null for a workload that was not profiled)
-            "alu_bound": alu_bound(prof),
+            "issue_one_by_one": one_by_one(prof),
             "limiter": (f"vector instruction issue (softmax arithmetic and MFMA), at d = 128 also power: "
                         f"issue cycles one by one {100 * prof['valu_busy']:.0f} % of the time, MFMA pipe {100 * prof['mfma_busy']:.0f} % "
                         f"[{prof['source']}]") if prof else None,

@@ -337,8 +337,8 @@ int sage_attn_fwd_4bit(const void *q, const void *k, const void *v, void *out,
  * one range (split_keys >= Nk) the result is that of sage_attn_fwd_kvquantized_gqa bit for bit; with more it differs
  * from it by FP8 rounding decisions only.
  * Up to (Hq/Hkv) * Nq = 64 query rows per K/V head, the rows of all query heads that share a K/V head are packed
- * into MFMA tiles of 16 and one wavefront takes one (K/V head, range, row tile), reading K^ and V^ straight from
- * global memory; above that the kernel that sage_attn_fwd_kvquantized_gqa would run for that many rows runs with its key steps
+ * into MFMA tiles of 16 and one wavefront takes one K/V head's range for one or two row tiles, copying K^ and V^ to
+ * LDS; above that the kernel that sage_attn_fwd_kvquantized_gqa would run for that many rows runs with its key steps
  * cut into ranges, one workgroup per (head, query tile, range).
  *   q, out      device, [B,Hq,Nq,d] contiguous, 16-bit type `dt`; Q is quantised inside (per head and block of 128
  *               rows, as everywhere)

@@ -93,7 +93,7 @@ def build(verbose: bool = False) -> str:
             f.write(f"{name} {u}\n")
     # a kernel that spills registers to scratch memory still computes the right result, only slowly:
     # nothing else would notice, so the build refuses it (scalar registers spill to lanes of vector registers, not to
-    # memory; the 4+8 kernels spill one or two)
+    # memory; most decode kernels spill 4 to 18, a few of them read back in a key step, the quantisers and 4+8 kernels one or two)
     bad = {n: u for n, u in usage.items() if u.get("ScratchSize", 0) or u.get("VGPRs Spill", 0)}
     if bad:
         raise RuntimeError("kernels spill registers to scratch memory: " + repr(bad))

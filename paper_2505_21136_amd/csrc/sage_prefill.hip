@@ -28,10 +28,11 @@
 // the maximum and the first exponentials of step j.  The step is cut into slots of about 18 vector instructions with
 // one or two MFMAs each (sched_barrier keeps the compiler from moving work between slots): a wavefront that
 // issues an MFMA while the matrix pipe is busy waits, and nothing behind it can issue.  One barrier per step.
-// RAISE: left alone the wavefronts of a SIMD take turns, one's exponentials against another's additions, and nothing is issued together
-// (64 scores: 1664 cycles).  With the priority raised around the exponentials and packs, and the MFMAs issued first thing in there, the
-// rest of two wavefronts meets: 1360 cycles without MFMAs, 1480 against 1860 with 16.  In this kernel, d = 64: 1904 -> 1821 cycles per step and
-// SIMD at the same clock with the MFMAs behind the exponentials, and with them in front 24 heads x 16384 1282 -> 1233 us, 9 x 8192 171 -> 158; d = 128, 10 x 4480 rows 7 % less, full
+// RAISE: left alone the wavefronts of a SIMD take turns, one's exponentials against another's additions, and next to nothing is issued
+// together (64 scores of two wavefronts: 1657 cycles measured, 1664 if every instruction were issued alone).  With the priority raised around
+// the exponentials and packs the rest of the two meets: 1344 cycles, with 16 MFMAs 1484 against 1781 (profiles/vector_issue_microbenchmark.hip).
+// In this kernel, d = 64: 1904 -> 1821 cycles per step and SIMD at the same clock with the MFMAs behind the exponentials, and with them first
+// thing in the raised part 24 heads x 16384 1282 -> 1233 us, 9 x 8192 171 -> 158; d = 128, 10 x 4480 rows 7 % less, full
 // chip 1 % (the clock falls with every cycle saved).  raise_pays has the rule.
 // The accumulator is rescaled only in steps after which some row maximum has moved (multiplying by 1 is the identity).
 #include "sage_attn_device.h"
@@ -638,7 +639,7 @@ __global__ __launch_bounds__(256, (prefill_waves_per_simd<D, Q4>())) void prefil
 //   * d = 128, two workgroups per CU, rounds of 512: the last one more than half full or full 1.08 .. 1.02 (257 .. 512 workgroups), 1.04 (808
 //     .. 832), 1.02 (1296 .. 1363), 1.00 (2445 .. 2496, 6144); less than half full 0.94 (544 .. 612), 0.97 (1044 .. 1136), 0.98 (1584 ..
 //     1776), 0.99 (2050 .. 2752);
-//   * d = 64, three per CU: 1.06 .. 1.10 up to 748, 0.98 .. 1.01 in 780 .. 952, 1.02 .. 1.05 from 1178 on (6144: 1.06);
+//   * d = 64, three per CU: 1.04 .. 1.10 up to 768, 0.93 .. 1.01 in 776 .. 1024, 1.03 .. 1.05 in 1032 .. 1160, 1.01 .. 1.05 from there on (6144: 1.06);
 //   * causal calls end on lone wavefronts: d = 64 0.92 .. 0.96 at 1280 .. 1920 workgroups, 1.00 .. 1.06 from 1980 on, d = 128 0.94 .. 1.006
 //     up to 4096.  Key ranges do not (512 workgroups: d = 128 1.02, d = 64 1.06).
 bool raise_pays(int wgs, int d, bool causal, bool ranges) {
