@@ -1310,7 +1310,8 @@ inline int resident_threads(Quantise what, int groups, int N, int d) {
 // (256 workgroups) 18.4 / 20.0; d = 64, H 2, G 4 13.7 / 8.1, H 32, G 4 14.2 / 12.3.  A head that one workgroup holds meets nobody: K and V,
 // G 1 7.4 / 7.8.  K alone d = 128, H 8, G 32 14.3 / 12.5, H 32, G 16 (512) 18.7 / 19.0; d = 64, H 2, G 1 8.5 / 6.7, H 128, G 2 13.4 / 12.5.
 // V alone G 2 7.0 / 7.5, H 32, G 4 10.7 / 8.2, G 16 (512) 16.4 / 13.9, H 32, G 32 (1024) 24.7 / 29.2.  K with Q, d = 128, H 2, G 4
-// 12.0 / 8.6, H 32, G 4 13.4 / 12.1, H 8, G 32 17.1 / 18.3, H 64, G 2 (300 tokens; the single read meets nobody) 9.5 / 10.0; d = 64,
+// 11.3 / 7.6, H 48, G 4 (192) 16.0 / 14.9, H 64, G 4 (256) 17.2 / 17.2, H 8, G 32 18.3 / 18.4, H 64, G 2 12.7 / 11.9, H 100, G 2 13.9 / 15.0 (the single
+// read of G 2 meets nobody); d = 64, H 48, G 4 16.9 / 15.5, H 64, G 4 in the last-level cache 15.8 / 16.6, H 96, G 2 15.9 / 15.0, H 2, G 100 19.3 / 20.9,
 // H 32, G 1 8.8 / 7.2, but with few K blocks in the one workgroup of a head (one launch / two) K alone H 8 x 64 tokens 5.0 / 6.1, x 256
 // 6.2 / 6.5, H 1 x 320 6.4 / 6.3, H 32 x 512 8.0 / 6.8.  Every workgroup of a head reads the G partials: K alone, d = 64, H 2, G 118 16.4 / 17.6; V alone, beyond one
 // workgroup per CU and where the single read has 512 threads, d = 128, H 4, G 96 18.3 / 17.3, G 120 17.5 / 19.9, H 2, G 160 16.5 / 17.3, G 256 18.8 /
@@ -1324,6 +1325,7 @@ inline bool chunks_pay(Quantise what, int heads, int N, int d) {
     switch (what) {
         case Quantise::kOnlyK: return wgs <= kCUs / 2 || (wgs <= kCUs && G <= 64);
         case Quantise::kOnlyV: return G > 2 && (wgs <= kCUs || (wgs <= 2 * kCUs && (G <= wide_above(d) || G > kResidentMaxGroup)));
+        case Quantise::kKWithQ: return wgs <= kCUs / 2 || (wgs <= 3 * kCUs / 4 && G <= 64 && (G > 2 || d == 64));
         default: return wgs <= (G == 2 ? kCUs / 4 : kCUs / 2);
     }
 }

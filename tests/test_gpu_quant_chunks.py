@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1, (1, 2, 257, 128)), (2, (1, 3, 512, 128)), (5, (1, 2, 513, 128)), (1, (2, 2, 1024, 128)), (5, (1, 1, 1089, 128)),
           (2, (1, 1, 32768, 128)), (5, (1, 2, 16129, 128)), (2, (1, 128, 769, 128)),
           (4, (1, 2, 200, 64)), (3, (1, 2, 512, 64)), (4, (2, 3, 513, 64)), (3, (1, 2, 1537, 64)), (4, (1, 32, 2048, 64)),
-          (3, (1, 64, 300, 64))]
+          (3, (1, 64, 300, 64)),
+          # K with Q: its own lines
+          (2, (1, 48, 1000, 128)), (5, (1, 64, 400, 128)), (4, (1, 24, 4001, 64)), (3, (1, 96, 900, 64))]
 
 
 @pytest.mark.parametrize("idx,shape", SHAPES)
